@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <atomic>
 #include <cstring>
@@ -30,6 +31,13 @@ static __device__ __align__(256) unsigned char scratch[BZ_NOALLOC_SCRATCH_BYTES]
 namespace {
 
 constexpr int MAX_DEV = 16;
+
+// A shape's round table on the device (fill_round_table, take_triples) and
+// whether its calls build triple tables.
+struct Shape {
+    RoundTable *rounds = nullptr;
+    bool triples = false;
+};
 
 struct DevCtx {
     bool ready = false;
@@ -62,12 +70,12 @@ struct DevCtx {
     BatchState *b_state = nullptr;
     CodeResult *b_host_res = nullptr;
     BatchState *b_host_state = nullptr;
-    // the rounds' task counts per shape (p, k, W, grid, task size), on the
-    // device, built once on first use (fill_round_table)
-    std::map<u64, RoundTable *> rounds;  // key: (p, k, W, grid, task size) in 64 bits
+    // what plain calls of one shape share, built once on first use (get_shape)
+    std::map<std::array<int, 7>, Shape> shapes;  // key: p, n, k, W, columns, grid, table layout
     // the second information set computed ahead by a second workgroup of the
     // decomposition launch, and the value its flag takes in this call
     SpecBuf *spec = nullptr;
+    ReportState *reports = nullptr;  // the copies that workgroups report to
     uint32_t spec_epoch = 0;
     // ordering of plain calls across streams: done_ev is recorded after the
     // enumeration launch of the last plain call, on last_stream (its late
@@ -100,29 +108,78 @@ const u64 *host_binom() {
         if ((expr) != hipSuccess) return BZ_ERR_DEVICE; \
     } while (0)
 
-// 16-byte units of the pair tables of one code: every set it can produce
-// (slots 0 .. pair_sets - 1), plus, on the plain path, the slot pair_sets
-// that the workgroup computing the second set ahead builds its table in
-u64 code_pair_units(int p, int n, int k, int W, bool ahead_slot) {
-    return (u64)(pair_sets(n, k) + (ahead_slot ? 1 : 0)) * pair_table_units(p, k, W);
-}
+// the columns processed per combination
+int processed_columns(int n, int k, bool skip) { return skip ? n - k : n; }
 
-// the largest code_pair_units of any code with n <= max_n (p = 7 has the
-// larger tables; W as the enumeration takes it: with the identity skip when
-// skip is 1, without it when 0, either when -1)
-u64 max_pair_units(int max_n, int skip, bool ahead_slot) {
+// 16-byte words between the tables of two sets of a code: the pair table and,
+// with triples, the triple table behind it
+u64 set_table_size(int p, int k, int nsym, bool triples) {
+    return unit_table_size(p, k, nsym) + (triples ? triple_table_size(p, k, nsym) : 0);
+}
+// of every set a code can produce (slots 0 .. pair_sets - 1), plus, on the
+// plain path, the slot pair_sets that the workgroup computing the second set
+// ahead builds its table in
+u64 code_table_size(int p, int n, int k, int nsym, bool triples, bool ahead_slot) {
+    return (u64)(pair_sets(n, k) + (ahead_slot ? 1 : 0)) * set_table_size(p, k, nsym, triples);
+}
+// Triples only where a set's table is at most an XCD's L2 (4 MB): every
+// wavefront streams it again for each of its tasks.
+bool triples_fit(int p, int k, int nsym) { return k >= TRIPLE_G && triple_table_size(p, k, nsym) * 16 <= (4u << 20); }
+
+// the largest code_table_size of any code with n <= max_n (with the identity
+// skip when skip is 1, without it when 0, either when -1)
+u64 max_table_size(int max_n, int skip, bool triples, bool ahead_slot) {
     u64 best = 0;
-    for (int n = 1; n <= max_n; n++)
-        for (int k = 1; k <= n && k <= BZ_MAX_K; k++) {
-            const int WF = (n + 31) / 32, Ws = (n - k + 31) / 32 < 1 ? 1 : (n - k + 31) / 32;
-            for (int W : {WF, Ws}) {
-                if ((skip == 1 && W != Ws) || (skip == 0 && W != WF)) continue;
-                const u64 u = code_pair_units(7, n, k, W, ahead_slot);
-                if (u > best) best = u;
-            }
-        }
+    for (int p : {3, 7})
+        for (int n = 1; n <= max_n; n++)
+            for (int k = 1; k <= n && k <= BZ_MAX_K; k++)
+                for (int sk = 0; sk < 2; sk++) {
+                    const int nsym = processed_columns(n, k, sk != 0);
+                    if (skip < 0 || skip == sk)
+                        best = std::max(best, code_table_size(p, n, k, nsym, triples && triples_fit(p, k, nsym), ahead_slot));
+                }
     return best;
 }
+
+// The last round that a random [n, k] code is expected to run: its minimum
+// weight d is about the least with p^(n-k) words within distance d, and round
+// g raises the lower bound to about (g + 1) n / k.  Only used to decide
+// whether triple tables are worth building.
+int expected_rounds(int p, int n, int k) {
+    const double goal = (n - k) * std::log((double)p) + std::log((double)(p - 1));
+    double lc = 0, sum = 0;  // ln of C(n, d) (p-1)^d, and of their sum
+    int d = 0;
+    while (d < n && (d == 0 || sum < goal)) {
+        d++;
+        lc += std::log((double)(n - d + 1) / d * (p - 1));
+        sum = d == 1 ? lc : std::max(sum, lc) + std::log1p(std::exp(-std::fabs(sum - lc)));
+    }
+    d = std::min(d, n - k + 1);
+    const int g = (d * k + n - 1) / n - 1;
+    return std::min(std::max(g, 1), k);
+}
+// Triple tables pay when the expected rounds save more tiles than the tables
+// take to build (a unit costs about 200 VALU instructions, a tile of 64 bases
+// 100: one tile per 32 units) and, on the plain path, than their launch takes:
+// about 8 us, 40000 tiles.
+bool triples_worth(int p, int n, int k, int nsym, uint32_t cap, u64 launch_tiles) {
+    if (!triples_fit(p, k, nsym)) return false;
+    const int sets = n / k + (n % k != 0), gm = expected_rounds(p, n, k);
+    u64 build = sat_mul(triple_tiles(p, k, -1), (u64)sets) + launch_tiles, saved = 0;
+    for (int g = TRIPLE_G; g <= gm && round_combos(p, g) < (1ull << 32); g++) {
+        u64 c3;
+        triple_round(p, k, g, cap, host_binom(), &c3);
+        const u64 c2 = pair_round_cost(p, k, g, cap, host_binom());
+        if (c2 > c3) saved = sat_add(saved, sat_mul(c2 - c3, (u64)sets));
+    }
+    return saved > build;
+}
+constexpr u64 TRIPLE_LAUNCH_TILES = 40000;
+// workgroups per code of a triple-table launch: about eight per compute unit in all
+int triple_blocks_per_code(int ncodes, int cu) { return std::max(1, std::min(8 * cu / std::max(ncodes, 1), 2 * cu)); }
+// the most 16-byte words a batch's or a server's tables may take with triples
+// (24 GiB); what is beyond has pair tables only
+constexpr u64 TRIPLE_BUDGET = (24ull << 30) / 16;
 
 int init_ctx(int dev) {
     DevCtx &c = g_ctx[dev];
@@ -143,11 +200,12 @@ int init_ctx(int dev) {
     if (hipMalloc(&c.g_buf, (size_t)BZ_MAX_K * BZ_MAX_N) != hipSuccess) return BZ_ERR_NOMEM;
     if (hipMalloc(&c.cs, sizeof(CodeState)) != hipSuccess) return BZ_ERR_NOMEM;
     if (hipMalloc(&c.rows, sizeof(u32) * BZ_MAX_M * BZ_MAX_K * ROW_WORDS) != hipSuccess) return BZ_ERR_NOMEM;
-    if (hipMalloc(&c.pairs, sizeof(uint4) * (max_pair_units(BZ_MAX_N, -1, true) + PAIR_PAD_UNITS)) != hipSuccess)
+    if (hipMalloc(&c.pairs, sizeof(uint4) * max_table_size(BZ_MAX_N, -1, true, true)) != hipSuccess)
         return BZ_ERR_NOMEM;
     if (hipMalloc(&c.binom, sizeof(u64) * 65 * 65) != hipSuccess) return BZ_ERR_NOMEM;
     if (hipMalloc(&c.hist, sizeof(u64) * BZ_MAX_STAGES * (BZ_MAX_N + 1)) != hipSuccess) return BZ_ERR_NOMEM;
     if (hipMalloc(&c.spec, sizeof(SpecBuf)) != hipSuccess) return BZ_ERR_NOMEM;
+    if (hipMalloc(&c.reports, sizeof(ReportState)) != hipSuccess) return BZ_ERR_NOMEM;
     HIP_OK(hipMemset(c.spec, 0, sizeof(SpecBuf)));
     if (hipHostMalloc(&c.host_res, sizeof(CodeResult), hipHostMallocDefault) != hipSuccess) return BZ_ERR_NOMEM;
     if (hipHostMalloc(&c.host_hist, sizeof(u64) * BZ_MAX_STAGES * (BZ_MAX_N + 1), hipHostMallocDefault) !=
@@ -177,10 +235,10 @@ void release_ctx(DevCtx &c) {
     // teardown: errors are not actionable here
     if (c.stream) (void)hipStreamSynchronize(c.stream);
     if (c.have_last && c.done_ev) (void)hipEventSynchronize(c.done_ev);
-    for (auto &kv : c.rounds) (void)hipFree(kv.second);
-    c.rounds.clear();
+    for (auto &kv : c.shapes) (void)hipFree(kv.second.rounds);
+    c.shapes.clear();
     for (void *p : {(void *)c.g_buf, (void *)c.cs, (void *)c.rows, (void *)c.pairs, (void *)c.binom, (void *)c.hist,
-                    (void *)c.spec, (void *)c.b_cs, (void *)c.b_claims, (void *)c.b_codes, (void *)c.b_rows,
+                    (void *)c.spec, (void *)c.reports, (void *)c.b_cs, (void *)c.b_claims, (void *)c.b_codes, (void *)c.b_rows,
                     (void *)c.b_pairs, (void *)c.b_g, (void *)c.b_state})
         if (p) (void)hipFree(p);
     for (void *p : {(void *)c.host_res, (void *)c.host_hist, (void *)c.host_trace, (void *)c.res_map,
@@ -197,6 +255,7 @@ void release_ctx(DevCtx &c) {
     c.binom = nullptr;
     c.hist = nullptr;
     c.spec = nullptr;
+    c.reports = nullptr;
     c.b_cs = nullptr;
     c.b_claims = nullptr;
     c.b_codes = nullptr;
@@ -241,11 +300,12 @@ hipError_t launch_decompose(int WF, const uint8_t *G, CodeState *cs, u32 *rows, 
     // workgroup 1 computes the second information set ahead; one more builds
     // the first set's pair table (see ROLE_TABLE0)
     const int nb = 1 + (a.spec ? 1 : 0) + (a.pairs && a.pair_t0 ? 1 : 0);
+    const int nt = a.pairs ? DECOMP_THREADS : 64;  // only the tables (and what goes with them) take more than one wavefront
     switch (WF) {
-    case 1: decompose_kernel<P, 1><<<nb, 64, 0, s>>>(G, cs, rows, a); break;
-    case 2: decompose_kernel<P, 2><<<nb, 64, 0, s>>>(G, cs, rows, a); break;
-    case 3: decompose_kernel<P, 3><<<nb, 64, 0, s>>>(G, cs, rows, a); break;
-    default: decompose_kernel<P, 4><<<nb, 64, 0, s>>>(G, cs, rows, a); break;
+    case 1: decompose_kernel<P, 1><<<nb, nt, 0, s>>>(G, cs, rows, a); break;
+    case 2: decompose_kernel<P, 2><<<nb, nt, 0, s>>>(G, cs, rows, a); break;
+    case 3: decompose_kernel<P, 3><<<nb, nt, 0, s>>>(G, cs, rows, a); break;
+    default: decompose_kernel<P, 4><<<nb, nt, 0, s>>>(G, cs, rows, a); break;
     }
     return hipGetLastError();
 }
@@ -254,65 +314,52 @@ hipError_t launch_decompose(int WF, const uint8_t *G, CodeState *cs, u32 *rows, 
 // so on an otherwise idle device every workgroup is resident at once, which
 // its waits for earlier stages rely on (plain calls hold the device's server
 // rounds off while they run).
-template <int P, int W, bool H>
-hipError_t launch_enum_one(int grid, CodeState *cs, const u32 *rows, const uint4 *pairs, const u64 *binom, u64 *hist,
-                           EnumArgs ea, hipStream_t s) {
-    // with pair tables the instantiation that has no prefix path, else the one without tables
-    if (pairs != nullptr) enum_kernel<P, W, H, true><<<grid, 256, 0, s>>>(cs, rows, pairs, binom, hist, ea);
-    else enum_kernel<P, W, H, false><<<grid, 256, 0, s>>>(cs, rows, nullptr, binom, hist, ea);
+using EnumFn = void (*)(CodeState *, const u32 *, const uint4 *, const u64 *, u64 *, EnumArgs);
+
+template <bool H>
+EnumFn enum_fn_h(int p, int W, int sch) {
+    if (p == 3) {
+        if (sch == NO_TABLE)
+            return W == 1 ? enum_kernel<3, 1, H, NO_TABLE> : W == 2 ? enum_kernel<3, 2, H, NO_TABLE>
+                 : W == 3 ? enum_kernel<3, 3, H, NO_TABLE> : enum_kernel<3, 4, H, NO_TABLE>;
+        return W == 1 ? enum_kernel<3, 1, H, 0> : W == 2 ? enum_kernel<3, 2, H, 0>
+             : W == 3 ? enum_kernel<3, 3, H, 0> : enum_kernel<3, 4, H, 0>;
+    }
+    switch (sch) {
+    case 1: return enum_kernel<7, 1, H, 1>;
+    case 2: return enum_kernel<7, 1, H, 2>;
+    case 3: return enum_kernel<7, 2, H, 3>;
+    case 4: return enum_kernel<7, 2, H, 4>;
+    case 5: return W == 3 ? enum_kernel<7, 3, H, 5> : enum_kernel<7, 4, H, 5>;
+    default:
+        return W == 1 ? enum_kernel<7, 1, H, NO_TABLE> : W == 2 ? enum_kernel<7, 2, H, NO_TABLE>
+             : W == 3 ? enum_kernel<7, 3, H, NO_TABLE> : enum_kernel<7, 4, H, NO_TABLE>;
+    }
+}
+// the enumeration kernel for a field, words per plane, table layout (or NO_TABLE) and histograms
+EnumFn enum_fn(int p, bool hist, int sch, int W) { return hist ? enum_fn_h<true>(p, W, sch) : enum_fn_h<false>(p, W, sch); }
+
+hipError_t launch_enum(int p, bool hist_mode, int sch, int W, int grid, CodeState *cs, const u32 *rows,
+                       const uint4 *pairs, const u64 *binom, u64 *hist, EnumArgs ea, hipStream_t s) {
+    enum_fn(p, hist_mode, sch, W)<<<grid, 256, 0, s>>>(cs, rows, pairs, binom, hist, ea);
     return hipGetLastError();
 }
 
-template <int P, bool H>
-hipError_t launch_enum_h(int W, int grid, CodeState *cs, const u32 *rows, const uint4 *pairs, const u64 *binom,
-                         u64 *hist, EnumArgs ea, hipStream_t s) {
-    switch (W) {
-    case 1: return launch_enum_one<P, 1, H>(grid, cs, rows, pairs, binom, hist, ea, s);
-    case 2: return launch_enum_one<P, 2, H>(grid, cs, rows, pairs, binom, hist, ea, s);
-    case 3: return launch_enum_one<P, 3, H>(grid, cs, rows, pairs, binom, hist, ea, s);
-    default: return launch_enum_one<P, 4, H>(grid, cs, rows, pairs, binom, hist, ea, s);
-    }
-}
+// workgroups per compute unit a plain call's schedule is made for
+constexpr int DEAL_GROUPS = 5;
 
-template <int P>
-hipError_t launch_enum(bool hist_mode, int W, int grid, CodeState *cs, const u32 *rows, const uint4 *pairs,
-                       const u64 *binom, u64 *hist, EnumArgs ea, hipStream_t s) {
-    return hist_mode ? launch_enum_h<P, true>(W, grid, cs, rows, pairs, binom, hist, ea, s)
-                     : launch_enum_h<P, false>(W, grid, cs, rows, pairs, binom, hist, ea, s);
-}
-
-// Largest grid the enumeration kernel may get for (p, W, histograms, pair
-// tables): the schedule is dealt to exactly this many workgroups.
-template <int P, int W, bool H, bool T>
-int grid_for(int cu, int bpc) {
-    static int max_bpc = -1;
-    if (max_bpc < 0) {
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, enum_kernel<P, W, H, T>, 256, 0) != hipSuccess || nb < 1)
+// Largest grid the enumeration kernel may get for (p, W, histograms, table
+// layout): unless it is made for more (DEAL_GROUPS), the schedule is dealt to exactly this many workgroups.
+int enum_grid(int p, bool hist, int sch, int W, int cu, int bpc) {
+    static std::atomic<int> max_bpc[2][2][5][8];  // 0: not asked yet
+    std::atomic<int> &m = max_bpc[p == 7][hist][W][sch + 1];
+    int nb = m.load(std::memory_order_relaxed);
+    if (nb == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, enum_fn(p, hist, sch, W), 256, 0) != hipSuccess || nb < 1)
             return -1;
-        max_bpc = nb;
+        m.store(nb, std::memory_order_relaxed);
     }
-    return cu * (bpc < max_bpc ? bpc : max_bpc);
-}
-
-template <int P, bool H, bool T>
-int grid_for_w(int W, int cu, int bpc) {
-    switch (W) {
-    case 1: return grid_for<P, 1, H, T>(cu, bpc);
-    case 2: return grid_for<P, 2, H, T>(cu, bpc);
-    case 3: return grid_for<P, 3, H, T>(cu, bpc);
-    default: return grid_for<P, 4, H, T>(cu, bpc);
-    }
-}
-
-template <int P, bool T>
-int enum_grid_t(bool hist, int W, int cu, int bpc) {
-    return hist ? grid_for_w<P, true, T>(W, cu, bpc) : grid_for_w<P, false, T>(W, cu, bpc);
-}
-
-int enum_grid(int p, bool hist, bool tables, int W, int cu, int bpc) {
-    if (p == 3) return tables ? enum_grid_t<3, true>(hist, W, cu, bpc) : enum_grid_t<3, false>(hist, W, cu, bpc);
-    return tables ? enum_grid_t<7, true>(hist, W, cu, bpc) : enum_grid_t<7, false>(hist, W, cu, bpc);
+    return cu * (bpc < nb ? bpc : nb);
 }
 
 // A plain call needs every workgroup of its persistent launch resident: it
@@ -397,6 +444,28 @@ void launch_op(int op, int blocks, hipStream_t s, int nvec, int words, const u32
     }
 }
 
+// sch: the table layout of the launch, or NO_TABLE
+int get_shape(DevCtx &c, int p, int n, int k, int W, int nsym, int grid, int sch, const Shape **out) {
+    const std::array<int, 7> key = {p, n, k, W, nsym, grid, sch};
+    auto it = c.shapes.find(key);
+    if (it == c.shapes.end()) {
+        RoundTable t;
+        Shape sh;
+        const uint32_t ops = plain_sweep_ops(p), cap = sweep_cap_for(p, W, ops);
+        fill_round_table(p, k, W, (uint32_t)grid, ops, host_binom(), &t);
+        sh.triples = sch != NO_TABLE && triples_worth(p, n, k, nsym, cap, TRIPLE_LAUNCH_TILES);
+        if (sh.triples) take_triples(p, k, cap, host_binom(), &t);
+        HIP_OK(hipMalloc(&sh.rounds, sizeof(RoundTable)));
+        if (hipMemcpy(sh.rounds, &t, sizeof(RoundTable), hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipFree(sh.rounds);
+            return BZ_ERR_DEVICE;
+        }
+        it = c.shapes.emplace(key, sh).first;
+    }
+    *out = &it->second;
+    return BZ_OK;
+}
+
 // ---- batches
 template <int WMAX>
 int batch_grid_w(int cu, int bpc) {
@@ -422,7 +491,7 @@ u64 batch_row_words(int n, int k) {
     return (u64)m * 64 * ROW_WORDS;
 }
 
-int grow_batch(DevCtx &c, size_t ncodes, size_t row_words, size_t pair_units, size_t g_bytes) {
+int grow_batch(DevCtx &c, size_t ncodes, size_t row_words, size_t table_words, size_t g_bytes) {
     if (ncodes > c.b_codes_cap) {
         // (errors of the frees are not actionable here; every pointer is reset so
         // that a failed allocation below leaves nothing to free twice)
@@ -449,12 +518,12 @@ int grow_batch(DevCtx &c, size_t ncodes, size_t row_words, size_t pair_units, si
         if (hipMalloc(&c.b_rows, sizeof(u32) * row_words) != hipSuccess) return BZ_ERR_NOMEM;
         c.b_rows_cap = row_words;
     }
-    if (pair_units > c.b_pairs_cap) {
+    if (table_words > c.b_pairs_cap) {
         if (c.b_pairs) (void)hipFree(c.b_pairs);
         c.b_pairs = nullptr;
         c.b_pairs_cap = 0;
-        if (hipMalloc(&c.b_pairs, sizeof(uint4) * (pair_units + PAIR_PAD_UNITS)) != hipSuccess) return BZ_ERR_NOMEM;
-        c.b_pairs_cap = pair_units;
+        if (hipMalloc(&c.b_pairs, sizeof(uint4) * table_words) != hipSuccess) return BZ_ERR_NOMEM;
+        c.b_pairs_cap = table_words;
     }
     if (g_bytes > c.b_g_cap) {
         if (c.b_g) (void)hipFree(c.b_g);
@@ -536,9 +605,19 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     // faster with them (their enumeration is bound by latency, not by the
     // prefixes)
     const bool tables = o.pair_tables > 0 || (o.pair_tables == 0 && p == 7);
-    const int grid = enum_grid(p, o.histograms != 0, tables, W, c->cu, bpc);
+    const int nsym = processed_columns(n, k, o.identity_skip != 0), sch = tables ? unit_scheme(p, nsym) : NO_TABLE;
+    const int grid = enum_grid(p, o.histograms != 0, sch, W, c->cu, bpc);
     if (grid < 1) return BZ_ERR_DEVICE;
     const u64 timeout = c->ticks_per_s * (u64)(o.wait_timeout_s > 0 ? o.wait_timeout_s : 120);
+    // the grid the schedule is made for: the stages that fit it start at once,
+    // as one pool.  The matrix sweeps' registers allow two workgroups per
+    // compute unit; with a schedule for those, the rounds of a small code waited
+    // for each other's checks ([45, 13] over F_7: 73 us of enumeration against
+    // 58 us for five workgroups of the earlier kernel)
+    const int deal = tables ? std::max(grid, c->cu * std::min(bpc, DEAL_GROUPS)) : grid;
+    const Shape *shape = nullptr;
+    st = get_shape(*c, p, n, k, W, nsym, deal, sch, &shape);
+    if (st != BZ_OK) return st;
 
     const uint8_t *Gd = G;
     if (!G_is_device) {
@@ -555,44 +634,38 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     a.flags = flags;
     a.U0 = n - k + 1;
     a.max_codewords = max_cw;
-    a.grid = (uint32_t)grid;
+    a.grid = (uint32_t)deal;
     a.sweep_ops = plain_sweep_ops(p);
     a.timeout_ticks = timeout;
-    {
-        // (p, k, W, grid, task size) packed: 3 + 7 + 3 + 19 + 32 bits
-        const u64 key = ((u64)p << 61) | ((u64)k << 54) | ((u64)W << 51) | ((u64)(grid & 0x7ffff) << 32) |
-                        (u64)a.sweep_ops;
-        auto it = c->rounds.find(key);
-        if (it == c->rounds.end()) {
-            RoundTable t;
-            fill_round_table(p, k, W, (uint32_t)grid, a.sweep_ops, host_binom(), &t);
-            RoundTable *d = nullptr;
-            HIP_OK(hipMalloc(&d, sizeof(RoundTable)));
-            if (hipMemcpy(d, &t, sizeof(RoundTable), hipMemcpyHostToDevice) != hipSuccess) {
-                (void)hipFree(d);
-                return BZ_ERR_DEVICE;
-            }
-            it = c->rounds.emplace(key, d).first;
-        }
-        a.rounds = it->second;
-    }
+    a.rounds = shape->rounds;
     if (++c->spec_epoch == 0) c->spec_epoch = 1;
     a.spec = o.no_ahead ? nullptr : c->spec;
     a.epoch = c->spec_epoch;
+    a.reports = tables ? c->reports : nullptr;
     a.pad = 0;
     a.pairs = tables ? c->pairs : nullptr;
-    a.pair_stride = (uint32_t)pair_table_units(p, k, W);
-    a.pair_w = W;
+    a.pair_stride = (uint32_t)set_table_size(p, k, nsym, shape->triples);
+    a.triples = shape->triples;
+    a.pair_w = (int16_t)W;
+    a.pair_scheme = (int16_t)unit_scheme(p, nsym);
     a.pair_t0 = 1;  // a workgroup of the decomposition launch of its own builds set 0's table
     if (o.timing) HIP_OK(hipEventRecord(c->ev[0], s));
     HIP_OK(p == 3 ? launch_decompose<3>(WF, Gd, c->cs, c->rows, a, s)
                   : launch_decompose<7>(WF, Gd, c->cs, c->rows, a, s));
+    const uint32_t triple_off = (uint32_t)unit_table_size(p, k, nsym);
+    if (shape->triples) {
+        triple_kernel<<<triple_blocks_per_code(1, c->cu), 256, 0, s>>>(c->cs, c->rows, c->pairs, p, k, W, sch,
+                                                                       a.pair_stride, triple_off);
+        HIP_OK(hipGetLastError());
+    }
     if (o.timing) HIP_OK(hipEventRecord(c->ev[1], s));
     EnumArgs ea;
     ea.k = k;
     ea.n = n;
     ea.flags = flags;
     ea.lookahead = LOOKAHEAD;
+    ea.deal_grid = (uint32_t)deal;
+    ea.reports = a.reports;
     ea.timeout_ticks = timeout;
     // without histograms or a trace, the check that ends the run hands the
     // result block to the host itself (mapped memory and a flag): no copy
@@ -602,14 +675,14 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     ea.flag_out = nullptr;
     ea.epoch = 0;
     ea.pair_stride = a.pair_stride;
+    ea.triple_off = triple_off;
     if (mapped) {
         if (++c->epoch == 0) c->epoch = 1;
         ea.res_out = c->res_map_dev;
         ea.flag_out = c->flag_map_dev;
         ea.epoch = c->epoch;
     }
-    HIP_OK(p == 3 ? launch_enum<3>(o.histograms != 0, W, grid, c->cs, c->rows, a.pairs, c->binom, c->hist, ea, s)
-                  : launch_enum<7>(o.histograms != 0, W, grid, c->cs, c->rows, a.pairs, c->binom, c->hist, ea, s));
+    HIP_OK(launch_enum(p, o.histograms != 0, sch, W, grid, c->cs, c->rows, a.pairs, c->binom, c->hist, ea, s));
     if (o.timing) HIP_OK(hipEventRecord(c->ev[2], s));
     HIP_OK(hipEventRecord(c->done_ev, s));
     c->last_stream = s;
@@ -703,8 +776,9 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     const u64 max_cw = o.max_codewords ? o.max_codewords : DEFAULT_LIMIT;
     // validate every code and lay out its rows
     std::vector<BatchCode> bc((size_t)ncodes);
-    u64 row_words = 0, pair_units = 0;
+    u64 row_words = 0, table_words = 0;
     int wmax = 1;
+    bool any_triples = false;
     for (int i = 0; i < ncodes; i++) {
         const bz_code &cd = codes[i];
         if (check_args(cd.p, cd.n, cd.k, G, out) != BZ_OK || cd.sweep_ops < 0) return BZ_ERR_ARG;
@@ -722,11 +796,17 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
         b.W = o.identity_skip ? (cd.n - cd.k + 31) / 32 : b.WF;
         if (b.W < 1) b.W = 1;
         b.sweep_ops = cd.sweep_ops > 0 ? (uint32_t)cd.sweep_ops : DEFAULT_SWEEP_OPS;
-        b.pair_stride = (uint32_t)pair_table_units(cd.p, cd.k, b.W);
-        b.pair_offset = pair_units;
+        const int nsym = processed_columns(cd.n, cd.k, o.identity_skip != 0);
+        b.scheme = unit_scheme(cd.p, nsym);
+        bool triples = triples_worth(cd.p, cd.n, cd.k, nsym, sweep_cap_for(cd.p, b.W, b.sweep_ops), 0);
+        triples = triples && table_words + code_table_size(cd.p, cd.n, cd.k, nsym, true, false) <= TRIPLE_BUDGET;
+        any_triples |= triples;
+        b.triple_off = triples ? (uint32_t)unit_table_size(cd.p, cd.k, nsym) : 0u;
+        b.pair_stride = (uint32_t)set_table_size(cd.p, cd.k, nsym, triples);
+        b.pair_offset = table_words;
         if (b.W > wmax) wmax = b.W;
         row_words += batch_row_words(cd.n, cd.k);
-        pair_units += code_pair_units(cd.p, cd.n, cd.k, b.W, false);
+        table_words += code_table_size(cd.p, cd.n, cd.k, nsym, triples, false);
     }
     DevCtx *c = nullptr;
     int st = get_ctx(o.device, &c);
@@ -734,7 +814,7 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     std::lock_guard<std::mutex> lk(c->mu);
     HIP_OK(hipSetDevice(o.device));
     hipStream_t s = o.hip_stream ? (hipStream_t)o.hip_stream : c->stream;
-    st = grow_batch(*c, (size_t)ncodes, (size_t)row_words, (size_t)pair_units, G_is_device ? 0 : (size_t)g_bytes);
+    st = grow_batch(*c, (size_t)ncodes, (size_t)row_words, (size_t)table_words, G_is_device ? 0 : (size_t)g_bytes);
     if (st != BZ_OK) return st;
     const int bpc = o.blocks_per_cu ? o.blocks_per_cu : 64;  // default: as many as fit
     const int grid = batch_grid(wmax, c->cu, bpc);
@@ -749,9 +829,14 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     zero_batch_state<<<1, 1, 0, s>>>(c->b_state);
     HIP_OK(hipGetLastError());
     if (o.timing) HIP_OK(hipEventRecord(c->ev[0], s));
-    decompose_batch_kernel<<<ncodes, 64, 0, s>>>(Gd, c->b_codes, c->b_cs, c->b_claims, c->b_rows, c->b_pairs,
+    decompose_batch_kernel<<<ncodes, DECOMP_THREADS, 0, s>>>(Gd, c->b_codes, c->b_cs, c->b_claims, c->b_rows, c->b_pairs,
                                                 (uint32_t)grid, c->b_state, nullptr, nullptr, nullptr);
     HIP_OK(hipGetLastError());
+    if (any_triples) {
+        triple_batch_kernel<<<dim3(triple_blocks_per_code(ncodes, c->cu), ncodes), 256, 0, s>>>(
+            c->b_cs, c->b_codes, c->b_rows, c->b_pairs, nullptr);
+        HIP_OK(hipGetLastError());
+    }
     if (o.timing) HIP_OK(hipEventRecord(c->ev[1], s));
     {
         CodeState *css = c->b_cs;
@@ -1005,7 +1090,7 @@ extern "C" int bz_min_distance_noalloc(int p, int n, int k, const uint8_t *G, co
     const int WF = (n + 31) / 32;
     int W = o.identity_skip ? (n - k + 31) / 32 : WF;
     if (W < 1) W = 1;
-    const int grid = enum_grid(p, false, false, W, na.cu, o.blocks_per_cu ? o.blocks_per_cu : 64);
+    const int grid = enum_grid(p, false, NO_TABLE, W, na.cu, o.blocks_per_cu ? o.blocks_per_cu : 64);
     if (grid < 1) return BZ_ERR_DEVICE;
     const u64 timeout = na.ticks_per_s * (u64)(o.wait_timeout_s > 0 ? o.wait_timeout_s : 120);
     NoAllocScratch *ws = na.ws;
@@ -1030,13 +1115,15 @@ extern "C" int bz_min_distance_noalloc(int p, int n, int k, const uint8_t *G, co
     ea.n = n;
     ea.flags = flags;
     ea.lookahead = LOOKAHEAD;
+    ea.deal_grid = (uint32_t)grid;
+    ea.reports = nullptr;
     ea.timeout_ticks = timeout;
     ea.res_out = nullptr;
     ea.flag_out = nullptr;
     ea.epoch = 0;
     ea.pair_stride = 0;
-    HIP_OK(p == 3 ? launch_enum<3>(false, W, grid, &ws->cs, ws->rows, nullptr, ws->binom, nullptr, ea, s)
-                  : launch_enum<7>(false, W, grid, &ws->cs, ws->rows, nullptr, ws->binom, nullptr, ea, s));
+    ea.triple_off = 0;
+    HIP_OK(launch_enum(p, false, NO_TABLE, W, grid, &ws->cs, ws->rows, nullptr, ws->binom, nullptr, ea, s));
     CodeResult r;
     HIP_OK(hipMemcpyAsync(&r, &ws->cs.res, sizeof r, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
@@ -1106,6 +1193,7 @@ struct bz_server {
     u64 seq = 0;
     u64 rounds = 0, yields = 0;
     bool running = false;
+    bool triples = false;  // the slots have room for triple tables
     int wmax = 2;
     std::mutex mu;
 };
@@ -1232,6 +1320,7 @@ int server_round(bz_server *s) {
         }
     }
     double admitted_work = 0.0;
+    bool any_triples = false;
     for (int i = 0; i < s->slots && !s->queue.empty(); i++) {
         bz_server::Slot &sl = s->slot[(size_t)i];
         if (sl.state != 0) continue;
@@ -1262,7 +1351,13 @@ int server_round(bz_server *s) {
         b.W = s->o.identity_skip ? (r.n - r.k + 31) / 32 : b.WF;
         if (b.W < 1) b.W = 1;
         b.sweep_ops = DEFAULT_SWEEP_OPS;
-        b.pair_stride = (uint32_t)pair_table_units(r.p, r.k, b.W);
+        const int nsym = processed_columns(r.n, r.k, s->o.identity_skip != 0);
+        b.scheme = unit_scheme(r.p, nsym);
+        const bool triples =
+            s->triples && triples_worth(r.p, r.n, r.k, nsym, sweep_cap_for(r.p, b.W, DEFAULT_SWEEP_OPS), 0);
+        any_triples |= triples;
+        b.triple_off = triples ? (uint32_t)unit_table_size(r.p, r.k, nsym) : 0u;
+        b.pair_stride = (uint32_t)set_table_size(r.p, r.k, nsym, triples);
         b.pair_offset = (u64)i * s->pairs_per_slot;
         s->new_h[fresh.size()] = i;
         fresh.push_back(i);
@@ -1275,10 +1370,15 @@ int server_round(bz_server *s) {
         HIP_OK(hipMemcpyAsync(s->codes, s->codes_h, sizeof(BatchCode) * (size_t)s->slots, hipMemcpyHostToDevice,
                               s->run));
         HIP_OK(hipMemcpyAsync(s->new_d, s->new_h, sizeof(int32_t) * (size_t)nf, hipMemcpyHostToDevice, s->run));
-        decompose_batch_kernel<<<nf, 64, 0, s->run>>>(s->g, s->codes, s->cs, s->claims, s->rows, s->pairs,
+        decompose_batch_kernel<<<nf, DECOMP_THREADS, 0, s->run>>>(s->g, s->codes, s->cs, s->claims, s->rows, s->pairs,
                                                       (uint32_t)s->decomp_grid, s->bs, s->new_d, s->done_dev,
                                                       s->res_dev);
         HIP_OK(hipGetLastError());
+        if (any_triples) {
+            triple_batch_kernel<<<dim3(triple_blocks_per_code(nf, s->c->cu), nf), 256, 0, s->run>>>(
+                s->cs, s->codes, s->rows, s->pairs, s->new_d);
+            HIP_OK(hipGetLastError());
+        }
         if (s->o.policy == BZ_SERVE_PREDICTED) {
             features_kernel<<<(nf + 63) / 64, 64, 0, s->run>>>(s->cs, s->new_d, nf, s->feat_d);
             mlp_forward_kernel<<<(nf + 255) / 256, 256, 0, s->run>>>(s->mlp_d, s->feat_d, nf, s->pred_d, nullptr);
@@ -1358,7 +1458,9 @@ int bz_server_start(const bz_server_options *opt, bz_server **out) {
     const int max_n = o.max_n ? o.max_n : BZ_MAX_N;
     s->wmax = (max_n + 31) / 32 <= 2 ? 2 : 4;
     s->rows_per_slot = batch_row_words(max_n, 1);
-    s->pairs_per_slot = max_pair_units(max_n, o.identity_skip ? 1 : 0, false);
+    s->pairs_per_slot = max_table_size(max_n, o.identity_skip ? 1 : 0, true, false);
+    s->triples = s->pairs_per_slot * (u64)s->slots <= TRIPLE_BUDGET;
+    if (!s->triples) s->pairs_per_slot = max_table_size(max_n, o.identity_skip ? 1 : 0, false, false);
     s->g_per_slot = (u64)(((max_n * BZ_MAX_K) + 255) / 256 * 256);
     s->grid = batch_grid(s->wmax, c->cu, o.blocks_per_cu ? o.blocks_per_cu : 64);  // default: as many as fit
     s->decomp_grid = s->grid * 8;  // smaller parts: a yield waits for at most one short part
@@ -1370,7 +1472,7 @@ int bz_server_start(const bz_server_options *opt, bz_server **out) {
               hipMalloc(&s->claims, sizeof(u64) * ns) == hipSuccess &&
               hipMalloc(&s->codes, sizeof(BatchCode) * ns) == hipSuccess &&
               hipMalloc(&s->rows, sizeof(u32) * s->rows_per_slot * ns) == hipSuccess &&
-              hipMalloc(&s->pairs, sizeof(uint4) * (s->pairs_per_slot * ns + PAIR_PAD_UNITS)) == hipSuccess &&
+              hipMalloc(&s->pairs, sizeof(uint4) * s->pairs_per_slot * ns) == hipSuccess &&
               hipMalloc(&s->g, s->g_per_slot * ns) == hipSuccess && hipMalloc(&s->bs, sizeof(BatchState)) == hipSuccess &&
               hipMalloc(&s->order_d, sizeof(int32_t) * ns) == hipSuccess &&
               hipMalloc(&s->new_d, sizeof(int32_t) * ns) == hipSuccess &&

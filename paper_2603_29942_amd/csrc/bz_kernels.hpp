@@ -24,6 +24,7 @@
 #include "bz_arith.hpp"
 #include "bz_mlp.hpp"
 #include "bz_state.hpp"
+#include "bz_units.hpp"
 
 namespace bz {
 
@@ -67,14 +68,17 @@ __device__ __forceinline__ u32 pick(const u32 (&a)[N], int q) {
 // Launch arguments of the enumeration kernel (known to the host up front).
 struct EnumArgs {
     int32_t k, n, flags, lookahead;
+    uint32_t deal_grid;  // the grid the schedule was made for: at least the launch's (with tables)
     u64 timeout_ticks;
+    ReportState *reports;
     // optional: when a check ends the run (or checks the last stage), the
     // checking wavefront copies the result block to res_out (mapped host
     // memory) and then stores epoch to *flag_out
     CodeResult *res_out;
     uint32_t *flag_out;
     uint32_t epoch;
-    uint32_t pair_stride;  // 16-byte units between the pair tables of two sets (with a table)
+    uint32_t pair_stride;  // 16-byte words between the tables of two sets (with tables)
+    uint32_t triple_off;   // from a set's pair table to its triples (with triples)
 };
 
 // A code's result block to mapped host memory by one whole wavefront:
@@ -128,13 +132,15 @@ struct RunArgs {
     u64 timeout_ticks;   // wall_clock64() ticks a workgroup may wait for earlier stages
     const RoundTable *rounds;  // the rounds' task counts for this shape, or NULL: counted here
     SpecBuf *spec;             // the second information set computed ahead, or NULL
+    ReportState *reports = nullptr;  // cleared by the decomposition's helpers; NULL: no tables
     uint32_t epoch, pad;       // this call's value of spec->flag
-    // the pair table of set j at pairs + j * pair_stride (16-byte units), for
-    // pair_w words per plane; NULL: no tables (the enumeration then builds
-    // its prefixes itself)
+    // the pair table of set j at pairs + j * pair_stride (16-byte words), for
+    // pair_w words per plane in the layout pair_scheme (unit_scheme); NULL: no
+    // tables (the enumeration then builds its prefixes itself)
     uint4 *pairs = nullptr;
     uint32_t pair_stride = 0;
-    int32_t pair_w = 0;
+    int16_t pair_w = 0, pair_scheme = 0;
+    int32_t triples = 0;  // 1: rounds may take triples (their tables are built by triple_kernel)
     int32_t pair_t0 = 0;  // 1: a workgroup of its own builds the first set's table (ROLE_TABLE0)
 };
 
@@ -148,16 +154,23 @@ enum { ROLE_MAIN = 0, ROLE_AHEAD = 1, ROLE_TABLE0 = 2 };
 // q-groups of a stage with g >= 3 computed by the 64 lanes of a wavefront
 // (lane = q - (g-3)); the same values as fill_qtable.  Returns the number of
 // tasks (wave-uniform); with tab != nullptr the lanes also store their entry.
+// With triples (vcap), q = g-4 .. k-4 and the blocks are of triples.
 // The binomials C(q, g-3) come from the workgroup's LDS copy when g-3 < BIN_I
 // (C(c, i) at sbin[c * BIN_I + i]), else from the global table.
 __device__ __forceinline__ u64 wave_qtable(int p, int k, int g, u64 M, uint32_t cap, uint32_t vcap,
                                            const u64 *sbin, const u64 *__restrict__ gbin, QEntry *tab) {
     const int lane = __lane_id();
-    const int q = g - 3 + lane;
-    const bool in = q <= k - 3;
+    const bool triples = vcap == TRIPLES;  // (wave-uniform)
+    const int q = g - (triples ? 4 : 3) + lane;
+    const bool in = lane <= k - g;
     u64 bases = 0, val = 0;
     uint32_t nb = 0, vd = 0;
-    if (in) {
+    if (in && triples) {
+        const u64 c = (g - 4 < BIN_I) ? sbin[q * BIN_I + (g - 4)] : gbin[q * 65 + (g - 4)];
+        bases = triple_bases(p, c, M);
+        nb = triple_blocks(triple_tiles(p, k, q), triple_cap(p, cap));
+        val = sat_mul(ceil64(bases), nb);
+    } else if (in) {
         // the values of qgroup
         const u64 c = (g - 3 < BIN_I) ? sbin[q * BIN_I + (g - 3)] : gbin[q * 65 + (g - 3)];
         bases = sat_mul(c, M);
@@ -195,41 +208,196 @@ struct DecompLDS {
     uint32_t s_combos[BZ_MAX_K];
     uint32_t s_nb[BZ_MAX_K];  // blocks of rows s of the q-group with top row q, at [q]
     uint32_t s_dt[BZ_MAX_K];  // digits_by_steps of the q-group with top row q, at [q]
+    uint32_t s_nb3[BZ_MAX_K];  // blocks of the triples above row q, at [q]
     uint4 prow[BZ_MAX_K * 4];  // the packed rows of the set whose pair table is built, row i word w at [i * 4 + w]
+    uint4 *table;              // where that table goes; nullptr: no more tables (see help_tables)
 };
 
-// The pair table of one information set (see pair_units) from its packed rows
-// in LDS, lane t taking the pairs t, t + 64, ...  Plain stores: the
-// enumeration reads the table in a later launch.
-template <int P>
-__device__ void build_pair_table(uint4 *__restrict__ ptab, int k, int W, const uint4 *prow) {
-    const int lane = threadIdx.x;
-    const int np = k * (k - 1) / 2;
-    // (s, rem): pair e is (s, s + 1 + rem); advanced by 64 pairs per step
-    int s = 0, rem = 0;
-    pair_advance(k, s, rem, lane);
-    for (int e = lane; e < np; e += 64) {
-        const int L = s + 1 + rem;
+// L of the pair s' < L of colex rank r (L(L-1)/2 <= r < L(L+1)/2), r < 2016:
+// the root of the quadratic, corrected by at most one step
+__device__ __forceinline__ int tri_root(int r) {
+    int L = (int)((1.0f + __builtin_sqrtf(1.0f + 8.0f * (float)r)) * 0.5f);
+    L -= L * (L - 1) / 2 > r;
+    L += L * (L + 1) / 2 <= r;
+    return L;
+}
+
+// the records of both halves of unit u
+template <int P, int W, int SCH>
+__device__ __forceinline__ void store_unit(u32 *__restrict__ tab, int u, const u32 (&y)[3][W]) {
+    constexpr int REC = unit_rec_words(SCH, W);
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        u32 rec[REC];
+        unit_record<P, W, SCH>(y, h, rec);
+        u32 *dst = tab + (size_t)((u >> 5) * 64 + (u & 31) + 32 * h) * REC;
+        if constexpr (REC == 2) {
+            *reinterpret_cast<uint2 *>(dst) = make_uint2(rec[0], rec[1]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < REC; q += 4)
+                reinterpret_cast<uint4 *>(dst)[q / 4] = make_uint4(rec[q], rec[q + 1], rec[q + 2], rec[q + 3]);
+        }
+    }
+}
+
+// The pair table of one information set (bz_units.hpp) from its packed rows
+// in LDS, one unit per thread and step: its exact sum R_s + c R_L and the
+// records of both halves.  Plain stores: the enumeration reads the table in a
+// later launch.
+template <int P, int W, int SCH>
+__device__ __forceinline__ void build_units(u32 *__restrict__ tab, int k, const uint4 *prow) {
+    constexpr int UP = P - 1;
+    const int nu = k * (k - 1) / 2 * UP;
+    for (int u = (int)threadIdx.x; u < nu; u += (int)blockDim.x) {
+        const int r = u / UP, c = u - r * UP + 1, i = tri_root(r);
+        const int s = k - 1 - i, L = k - 1 - (r - i * (i - 1) / 2);
+        u32 y[3][W];
+#pragma unroll
         for (int w = 0; w < W; w++) {
             const uint4 a = prow[s * 4 + w], b = prow[L * 4 + w];
             if constexpr (P == 3) {
-                u32 t0, t1, u0, u1;
-                f3_add(a.x, a.y, b.x, b.y, t0, t1);  // R_s + R_L
-                f3_add(a.x, a.y, b.y, b.x, u0, u1);  // R_s - R_L (= R_s + 2 R_L: planes swapped)
-                ptab[(size_t)e * W + w] = make_uint4(t0, t1, u0, u1);
+                f3_add(a.x, a.y, c == 1 ? b.x : b.y, c == 1 ? b.y : b.x, y[0][w], y[1][w]);
+                y[2][w] = 0;
             } else {
                 const u32 bl[3] = {b.x, b.y, b.z};
-#pragma unroll
-                for (int c = 1; c < 7; c++) {
-                    u32 sc[3], t[3];
-                    scale<7>(c, bl, sc);
-                    f7_add(a.x, a.y, a.z, sc[0], sc[1], sc[2], t[0], t[1], t[2]);
-                    ptab[((size_t)e * 6 + (c - 1)) * W + w] = make_uint4(t[0], t[1], t[2], t[0] | t[1] | t[2]);
-                }
+                u32 sc[3];
+                scale<7>(c, bl, sc);
+                f7_add(a.x, a.y, a.z, sc[0], sc[1], sc[2], y[0][w], y[1][w], y[2][w]);
             }
         }
-        pair_advance(k, s, rem, 64);
+        store_unit<P, W, SCH>(tab, u, y);
     }
+}
+
+// build_units for the words per plane and the layout of this code, by every
+// thread of the workgroup
+template <int P>
+__device__ void build_pair_table(uint4 *ptab, int k, int W, int sch, const uint4 *prow) {
+    u32 *tab = reinterpret_cast<u32 *>(ptab);
+    if constexpr (P == 3) {
+        if (W == 1) build_units<3, 1, 0>(tab, k, prow);
+        else if (W == 2) build_units<3, 2, 0>(tab, k, prow);
+        else if (W == 3) build_units<3, 3, 0>(tab, k, prow);
+        else build_units<3, 4, 0>(tab, k, prow);
+    } else {
+        if (sch == 1) build_units<7, 1, 1>(tab, k, prow);
+        else if (sch == 2) build_units<7, 1, 2>(tab, k, prow);
+        else if (sch == 3) build_units<7, 2, 3>(tab, k, prow);
+        else if (sch == 4) build_units<7, 2, 4>(tab, k, prow);
+        else if (W == 3) build_units<7, 3, 5>(tab, k, prow);
+        else build_units<7, 4, 5>(tab, k, prow);
+    }
+}
+
+// The triple tables of a code's sets, one unit per thread and step.  A table
+// has 36 (F_7) or 4 (F_3) units per triple, up to 130000: a launch of its own
+// spreads it over the chip (blockIdx.x of gridDim.x workgroups per code).
+template <int P, int W, int SCH>
+__device__ __forceinline__ void build_triples(u32 *__restrict__ tab, int k, const uint4 *prow) {
+    constexpr int UP = (P - 1) * (P - 1);
+    const int nu = choose3(k) * UP;
+    for (int u = (int)(blockIdx.x * blockDim.x + threadIdx.x); u < nu; u += (int)(gridDim.x * blockDim.x)) {
+        const int r = u / UP, cc = u - r * UP, c1 = cc / (P - 1) + 1, c2 = cc % (P - 1) + 1;
+        // i: the largest with C(i, 3) <= r, from the cube root of 6 r
+        int i = (int)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf(6.0f * (float)r + 1.0f) * (1.0f / 3.0f)) + 1;
+        while (choose3(i) > r) i--;
+        while (choose3(i + 1) <= r) i++;
+        const int r2 = r - choose3(i), j = r2 ? tri_root(r2) : 1, l = r2 - choose2(j);
+        const int a = k - 1 - i, b = k - 1 - j, c = k - 1 - l;
+        u32 y[3][W];
+#pragma unroll
+        for (int w = 0; w < W; w++) {
+            const uint4 ra = prow[a * 4 + w], rb = prow[b * 4 + w], rc = prow[c * 4 + w];
+            u32 x[3] = {ra.x, ra.y, ra.z};
+            const u32 vb[3] = {rb.x, rb.y, rb.z}, vc[3] = {rc.x, rc.y, rc.z};
+            u32 sc[3] = {0, 0, 0};
+            scale<P>(c1, vb, sc);
+            if constexpr (P == 3) f3_add(x[0], x[1], sc[0], sc[1], x[0], x[1]);
+            else f7_add(x[0], x[1], x[2], sc[0], sc[1], sc[2], x[0], x[1], x[2]);
+            scale<P>(c2, vc, sc);
+            if constexpr (P == 3) f3_add(x[0], x[1], sc[0], sc[1], y[0][w], y[1][w]);
+            else f7_add(x[0], x[1], x[2], sc[0], sc[1], sc[2], y[0][w], y[1][w], y[2][w]);
+            if constexpr (P == 3) y[2][w] = 0;
+        }
+        store_unit<P, W, SCH>(tab, u, y);
+    }
+}
+
+__device__ void triple_tables(const CodeState *cs, const u32 *__restrict__ rows, uint4 *tables, int p, int k, int W,
+                              int sch, uint32_t stride, uint32_t off, uint4 *prow) {
+    if (uni(cs->res.status) != BZ_OK) return;
+    const int m = uni(cs->res.m), slot1 = uni(cs->pair_slot1);
+    for (int j = 0; j < m; j++) {
+        for (int t = (int)threadIdx.x; t < k * 4; t += (int)blockDim.x)
+            prow[t] = reinterpret_cast<const uint4 *>(rows + (size_t)(j * BZ_MAX_K + t / 4) * ROW_WORDS)[t & 3];
+        __syncthreads();
+        u32 *tab = reinterpret_cast<u32 *>(tables + (size_t)(j == 1 ? slot1 : j) * stride + off);
+        if (p == 3) {
+            if (W == 1) build_triples<3, 1, 0>(tab, k, prow);
+            else if (W == 2) build_triples<3, 2, 0>(tab, k, prow);
+            else if (W == 3) build_triples<3, 3, 0>(tab, k, prow);
+            else build_triples<3, 4, 0>(tab, k, prow);
+        } else {
+            if (sch == 1) build_triples<7, 1, 1>(tab, k, prow);
+            else if (sch == 2) build_triples<7, 1, 2>(tab, k, prow);
+            else if (sch == 3) build_triples<7, 2, 3>(tab, k, prow);
+            else if (sch == 4) build_triples<7, 2, 4>(tab, k, prow);
+            else if (W == 3) build_triples<7, 3, 5>(tab, k, prow);
+            else build_triples<7, 4, 5>(tab, k, prow);
+        }
+        __syncthreads();
+    }
+}
+
+// one code (the plain path)
+__global__ __launch_bounds__(256) void triple_kernel(const CodeState *cs, const u32 *__restrict__ rows, uint4 *tables,
+                                                     int p, int k, int W, int sch, uint32_t stride, uint32_t off) {
+    __shared__ uint4 prow[BZ_MAX_K * 4];
+    triple_tables(cs, rows, tables, p, k, W, sch, stride, off, prow);
+}
+// the codes of a batch (or the listed slots): blockIdx.y
+__global__ __launch_bounds__(256) void triple_batch_kernel(const CodeState *css, const BatchCode *__restrict__ codes,
+                                                           const u32 *__restrict__ rows, uint4 *tables,
+                                                           const int32_t *__restrict__ slots) {
+    __shared__ uint4 prow[BZ_MAX_K * 4];
+    const int c = slots ? slots[blockIdx.y] : (int)blockIdx.y;
+    const BatchCode bc = codes[c];
+    if (bc.triple_off == 0) return;
+    triple_tables(css + c, rows + bc.row_offset, tables + bc.pair_offset, bc.p, bc.k, bc.W, bc.scheme, bc.pair_stride,
+                  bc.triple_off, prow);
+}
+
+// The first wavefront of a decomposition workgroup eliminates; the others
+// only help to build the pair tables.  It calls share_table for each table
+// (its rows are in lds.prow) and ends with release_helpers, which lets the
+// waiting wavefronts go; both sides pass the same barriers.
+template <int P>
+__device__ __forceinline__ void share_table(DecompLDS &lds, uint4 *ptab, int k, int W, int sch) {
+    if (threadIdx.x == 0) lds.table = ptab;
+    __syncthreads();
+    build_pair_table<P>(ptab, k, W, sch, lds.prow);
+    __syncthreads();
+}
+__device__ __forceinline__ void release_helpers(DecompLDS &lds) {
+    if (threadIdx.x == 0) lds.table = nullptr;
+    __syncthreads();
+}
+template <int P>
+__device__ __forceinline__ void help_tables(DecompLDS &lds, int k, int W, int sch) {
+    for (;;) {
+        __syncthreads();
+        uint4 *const t = lds.table;
+        if (t == nullptr) return;
+        build_pair_table<P>(t, k, W, sch, lds.prow);
+        __syncthreads();
+    }
+}
+// orders the LDS accesses of one wavefront (they are performed in order; the
+// compiler must not move them)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // One Gauss-Jordan step on the rows held one per lane: row pl (pivot value
@@ -297,7 +465,8 @@ struct RoundPrefetch {
     int cut = 0;
 };
 
-// One code on one wavefront (threads 0..63 of the workgroup).
+// One code on one wavefront (threads 0..63 of the workgroup; with pair tables
+// the others run help_tables, and the caller ends with release_helpers).
 // role ROLE_AHEAD: the elimination of one set with the columns 0 .. k-1 taken
 // as used, packed into args.spec, then (with tables) its pair table in slot
 // pair_sets(n, k), and nothing else.  ROLE_TABLE0: the first set's
@@ -319,9 +488,9 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
     const u64 t_start = tracing ? (u64)wall_clock64() : 0;
     SpecBuf *spec = args.spec;
     uint4 *const pairs = args.pairs;
-    const int pair_w = uni(args.pair_w);
+    const int pair_w = uni((int)args.pair_w), pair_sch = uni((int)args.pair_scheme);
     const uint32_t pair_stride = uni(args.pair_stride);
-    const bool t0_elsewhere = uni(args.pair_t0) != 0;
+    const bool t0_elsewhere = uni(args.pair_t0) != 0, triples = uni(args.triples) != 0;
     const bool have_rt = pre.have;
     const u64 rt_tasks = pre.tasks;
     const uint32_t rt_vcap = pre.vcap;
@@ -401,7 +570,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
 #pragma unroll
             for (int w = 0; w < 4; w++) x[b][w] = (lane < k) ? (x[b][w] & colmask[w]) : 0u;
     }
-    __syncthreads();
+    wave_sync();
     const u64 t_loaded = tracing ? (u64)wall_clock64() : 0;
 
     int status = BZ_OK;
@@ -586,18 +755,12 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
             }
         }
         if (role == ROLE_TABLE0) {
-            if (pairs != nullptr) {
-                __syncthreads();
-                build_pair_table<P>(pairs, k, pair_w, lds.prow);
-            }
+            if (pairs != nullptr) share_table<P>(lds, pairs, k, pair_w, pair_sch);
             return;
         }
         // (m < pair_sets(n, k) always holds, see pair_sets)
-        if (main_wg && pairs != nullptr && m < pair_sets(n, k) && !(m == 0 && t0_elsewhere)) {
-            __syncthreads();
-            build_pair_table<P>(pairs + (size_t)m * pair_stride, k, pair_w, lds.prow);
-            __syncthreads();
-        }
+        if (main_wg && pairs != nullptr && m < pair_sets(n, k) && !(m == 0 && t0_elsewhere))
+            share_table<P>(lds, pairs + (size_t)m * pair_stride, k, pair_w, pair_sch);
         if (ahead) {
             // publish: the rows and the set's description, then the flag
             if (lane == 0) {
@@ -608,10 +771,8 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
             }
             __threadfence();
             if (lane == 0) __hip_atomic_store(&spec->flag, args.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            if (pairs != nullptr) {
-                __syncthreads();
-                build_pair_table<P>(pairs + (size_t)pair_sets(n, k) * pair_stride, k, pair_w, lds.prow);
-            }
+            if (pairs != nullptr)
+                share_table<P>(lds, pairs + (size_t)pair_sets(n, k) * pair_stride, k, pair_w, pair_sch);
             return;
         }
         if (lane == 0) sranks[m] = kj;
@@ -628,7 +789,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
         if (lane == 0) __hip_atomic_store(&spec->flag, args.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    __syncthreads();
+    wave_sync();
 
     const u64 t_reduced = tracing ? (u64)wall_clock64() : 0;
     // -- schedule (the stage order of Alg. 6): one round g per lane, a
@@ -665,7 +826,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
             s_tasks[lane] = (g <= SUBSET_G) ? small_stage_tasks(k, g) : 0;
             lds.s_vcap[lane] = 0;
         }
-        __syncthreads();
+        wave_sync();
         // task counts of the rounds g > SUBSET_G that the table reaches, one
         // round per lane: tasks(g) = sum over q of ceil(bases(q, g) / 64) nb(q),
         // the blocks nb(q) of a q-group being the same in every round (the sum
@@ -676,8 +837,9 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
         if (!have_rt && lane <= k - 3) {
             lds.s_nb[lane] = qgroup_blocks(k, cap, lane);
             lds.s_dt[lane] = digits_by_steps(P, k, lane, budget);
+            lds.s_nb3[lane] = triple_blocks(triple_tiles(P, k, lane), triple_cap(P, cap));
         }
-        __syncthreads();
+        wave_sync();
         const bool counted = in && g > SUBSET_G && g <= last_g;
         u64 tg = 0, tgv = 0;  // without and with runs of bases
         if (have_rt) {
@@ -691,6 +853,8 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
             // q runs over a wave-uniform range (rows q < g-3 add nothing) so
             // that the unrolled LDS reads overlap
             const int q0 = uni(SUBSET_G - 2);  // the smallest g - 3 of a counted round
+            const bool try3 = triples && g >= TRIPLE_G;
+            u64 t3 = 0, cost2 = 0, cost3 = 0;  // with triples: tasks; the costs of both
 #pragma unroll 4
             for (int q = q0; q <= k - 3; q++) {
                 if (q < g - 3) continue;
@@ -699,12 +863,23 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
                 const uint32_t nb = lds.s_nb[q];
                 tg = sat_add(tg, qgroup_tasks(P, bases, nb, 0));
                 tgv = sat_add(tgv, qgroup_tasks(P, bases, nb, digits_of(P, g, lds.s_dt[q], bases)));
+                if (try3) cost2 = sat_add(cost2, pair_group_cost(P, k, q, bases, nb));
+            }
+            if (try3) {
+                for (int q = uni(TRIPLE_G - 4); q <= k - 4; q++) {
+                    if (q < g - 4) continue;
+                    const u64 bases = triple_bases(P, binom[q * 65 + (g - 4)], combos);
+                    const uint32_t nb = lds.s_nb3[q];
+                    t3 = sat_add(t3, sat_mul(ceil64(bases), nb));
+                    cost3 = sat_add(cost3, triple_group_cost(triple_tiles(P, k, q), bases, nb));
+                }
             }
             // the round takes runs of bases where they pay (qgroup_digits with
             // the run budget, as a table of digits_by_steps)
             const bool runs = runs_pay(tgv, args.grid);
-            s_tasks[lane] = runs ? tgv : tg;
-            lds.s_vcap[lane] = runs ? budget : 0u;
+            const bool use3 = try3 && cost3 < cost2;
+            s_tasks[lane] = use3 ? t3 : runs ? tgv : tg;
+            lds.s_vcap[lane] = use3 ? TRIPLES : runs ? budget : 0u;
         }
         // the first round with 2^62 tasks or more cuts the table before it
         const u64 over = __ballot(counted && tg >= (1ull << 62));
@@ -716,7 +891,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
             ns = BZ_MAX_STAGES;
             complete = 0;
         }
-        __syncthreads();
+        wave_sync();
         // tiles of the rounds before each round (exclusive saturating scan)
         {
             const u64 mine_t = in ? (s_tasks[lane] + WAVES_PER_GROUP - 1) / WAVES_PER_GROUP : 0;
@@ -729,7 +904,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
             if (lane == 0) tb = 0;
             if (in) lds.s_tbefore[lane] = tb;
         }
-        __syncthreads();
+        wave_sync();
     }
     {
         const uint32_t cap = sweep_cap_for(P, W, args.sweep_ops);
@@ -788,10 +963,27 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
     if (lane < (int)POOL_SLICES) cs->pool_next[lane][0] = 0;
 }
 
+// Wavefronts of a decomposition workgroup that builds tables: a table of 2000
+// units takes one wavefront about 20 us, more than the elimination; eight
+// build it in about 3 us.
+constexpr int DECOMP_THREADS = 512;
+
 template <int P, int WF>
-__global__ __launch_bounds__(64) void decompose_kernel(const uint8_t *__restrict__ G, CodeState *cs,
-                                                       u32 *__restrict__ rows, RunArgs args) {
+__global__ __launch_bounds__(DECOMP_THREADS) void decompose_kernel(const uint8_t *__restrict__ G, CodeState *cs,
+                                                                   u32 *__restrict__ rows, RunArgs args) {
     __shared__ DecompLDS lds;
+    if (threadIdx.x >= 64) {
+        if (blockIdx.x == 0 && args.reports != nullptr) {
+            ReportState &rep = *args.reports;
+            constexpr int N = (int)REPORT_COPIES * BZ_MAX_STAGES;
+            for (int i = (int)threadIdx.x - 64; i < N; i += DECOMP_THREADS - 64) {
+                (&rep.word[0][0])[i] = 0;
+                (&rep.min[0][0])[i] = (int)BIG;
+            }
+        }
+        help_tables<P>(lds, args.k, args.pair_w, args.pair_scheme);
+        return;
+    }
     RoundPrefetch pre;
     if (args.rounds != nullptr && blockIdx.x == 0) {
         const int lane = __lane_id();
@@ -804,6 +996,7 @@ __global__ __launch_bounds__(64) void decompose_kernel(const uint8_t *__restrict
     // the first set's pair table; workgroup 2: the first set's pair table
     const int role = blockIdx.x == 0 ? ROLE_MAIN : (blockIdx.x == 1 && args.spec != nullptr) ? ROLE_AHEAD : ROLE_TABLE0;
     decompose_code<P, WF>(G, cs, rows, args, lds, role, pre);
+    release_helpers(lds);
 }
 
 // =====================================================================
@@ -832,14 +1025,16 @@ __device__ __forceinline__ Row<W> load_row(const u32 *__restrict__ rows, int j, 
 }
 
 // A row at a lane-specific index (decoding a base, the rows of a subset): from
-// the workgroup's LDS copy of the first LROW_SETS matrices when it has one
-// (lrows != nullptr), else from memory.  Wave-uniform rows keep coming from
-// memory through scalar loads.
-constexpr int LROW_SETS = 2;
+// the workgroup's LDS copy of the first matrices when it has one, else from
+// memory.  Wave-uniform rows keep coming from memory through scalar loads.
+struct LdsRows {
+    const uint4 *p;
+    int sets;  // matrices in the copy
+};
 template <int P, int W>
-__device__ __forceinline__ Row<W> load_row_lane(const u32 *__restrict__ rows, const uint4 *lrows, int j, int i) {
-    if (lrows != nullptr && j < LROW_SETS) {
-        const uint4 *src = lrows + (j * BZ_MAX_K + i) * W;
+__device__ __forceinline__ Row<W> load_row_lane(const u32 *__restrict__ rows, LdsRows lrows, int j, int i) {
+    if (lrows.p != nullptr && j < lrows.sets) {
+        const uint4 *src = lrows.p + (j * BZ_MAX_K + i) * W;
         Row<W> r;
 #pragma unroll
         for (int w = 0; w < W; w++) {
@@ -878,9 +1073,15 @@ __device__ __forceinline__ void add_scaled(u32 (&x)[3][W], const u32 (&r)[3][W],
     }
 }
 
+// Eight copies of a wavefront's histogram, side by side: weights crowd into a
+// few bins, and with one copy most of the 64 lanes of an LDS atomic met on the
+// same few addresses, which it serves one after the other.
+constexpr int HIST_COPIES = 8;
+constexpr int HIST_DUMP = (BZ_MAX_N + 1) * HIST_COPIES;  // behind the bins: a word per lane for what is not counted
+constexpr int HIST_WORDS = HIST_DUMP + 64;               // of a wavefront
 template <int P, int W, bool HIST>
 __device__ __forceinline__ void count_hist(u32 *lh, u32 wt) {
-    if constexpr (HIST) atomicAdd(&lh[wt], 1u);
+    if constexpr (HIST) atomicAdd(&lh[wt * HIST_COPIES + (__lane_id() & (HIST_COPIES - 1))], 1u);
 }
 
 // Weights of the combinations prefix + h * row for the p-1 prefixes of one
@@ -962,130 +1163,500 @@ __device__ __forceinline__ int extend_and_sweep(const u32 *__restrict__ rows, in
     });
 }
 
-// One unit of a pair table (see pair_units): W words of 16 bytes at a
-// wave-uniform index, held as a Row (F_3: planes 0, 1 of R_s + R_L in p[0],
-// p[1] and of R_s - R_L in p[2], any).
-// (through the constant address space: the table is read-only while the
-// enumeration runs, so the wave-uniform loads are scalar loads)
-typedef const __attribute__((address_space(4))) u32 *const_u32_ptr;
-template <int W>
-__device__ __forceinline__ Row<W> load_unit(const uint4 *__restrict__ ptab, int u) {
-    const_u32_ptr src = (const_u32_ptr)(ptab + (size_t)u * W);
-    Row<W> r;
-#pragma unroll
-    for (int w = 0; w < W; w++) {
-        r.p[0][w] = src[4 * w];
-        r.p[1][w] = src[4 * w + 1];
-        r.p[2][w] = src[4 * w + 2];
-        r.any[w] = src[4 * w + 3];
-    }
-    return r;
+// ---- the sweep over a pair table on the matrix cores (see bz_units.hpp)
+typedef int v8i_t __attribute__((ext_vector_type(8)));
+typedef float v16f_t __attribute__((ext_vector_type(16)));
+typedef u32 fp4x32[4];  // 32 FP4 values: one lane's share of an operand
+
+// D = A B + C for 32 x 32 x 64 FP4 products with FP32 sums, block scales 1.
+// D's register r, lane l: unit 8 (r / 4) + 4 (l / 32) + r % 4, base l % 32.
+__device__ __forceinline__ v16f_t mfma_fp4(const fp4x32 &a, const fp4x32 &b, v16f_t c) {
+    const v8i_t av = {(int)a[0], (int)a[1], (int)a[2], (int)a[3], 0, 0, 0, 0};
+    const v8i_t bv = {(int)b[0], (int)b[1], (int)b[2], (int)b[3], 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 4, 0, 0, 0, 0);
+}
+// x as a value of its own here: what is computed from it is not hoisted out of
+// the enclosing loops into registers held for the whole kernel
+template <typename T>
+__device__ __forceinline__ T here(T x) {
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
-template <int W>
-__device__ __forceinline__ void pin_unit(const Row<W> &r) {
-#pragma unroll
-    for (int w = 0; w < W; w++) asm volatile("" ::"s"(r.p[0][w]), "s"(r.p[1][w]), "s"(r.p[2][w]), "s"(r.any[w]));
+// a, b -> (the low halves of a and b, the high halves of a and b)
+__device__ __forceinline__ void swap_halves(u32 &a, u32 &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
 }
 
-// The combinations of an exact sum Q (its planes in Pv[0], nonzero mask in
-// anyQ[0]) and one unit T of a pair table, through isometric additions and
-// subtractions only: F_3 Q +- (R_s + R_L) and Q +- (R_s - R_L) (4); F_7
-// Q + h T_c, h = +-2^e (complete_all with one prefix; 6).
-template <int P, int W, bool HIST>
-__device__ __forceinline__ void complete_unit(const u32 (&Pv)[1][3][W], const u32 (&anyQ)[1][W], const Row<W> &T,
-                                              u32 &lmin, u32 *lh, u32 woff, u32 cap) {
-    if constexpr (P == 3) {
-        u32 wa = 0, ws = 0, wb = 0, wt = 0;
+// max of m and the 16 values of d + |o|, and of d alone
+__device__ __forceinline__ float max_abs(float m, const v16f_t &d, const v16f_t &o) {
 #pragma unroll
-        for (int w = 0; w < W; w++) {
-            wa += __builtin_popcount(f3_iso_add(Pv[0][0][w], Pv[0][1][w], T.p[0][w], T.p[1][w]));
-            ws += __builtin_popcount(f3_iso_sub(Pv[0][0][w], Pv[0][1][w], T.p[0][w], T.p[1][w]));
-            wb += __builtin_popcount(f3_iso_add(Pv[0][0][w], Pv[0][1][w], T.p[2][w], T.any[w]));
-            wt += __builtin_popcount(f3_iso_sub(Pv[0][0][w], Pv[0][1][w], T.p[2][w], T.any[w]));
-        }
-        lmin = min(lmin, min(min(wa, ws), min(wb, wt)));
-        if constexpr (HIST) {
-            count_hist<P, W, HIST>(lh, min(wa + woff, cap));
-            count_hist<P, W, HIST>(lh, min(ws + woff, cap));
-            count_hist<P, W, HIST>(lh, min(wb + woff, cap));
-            count_hist<P, W, HIST>(lh, min(wt + woff, cap));
-        }
+    for (int r = 0; r < 16; r += 2)
+        m = fmaxf(fmaxf(m, d[r] + fabsf(o[r])), d[r + 1] + fabsf(o[r + 1]));
+    return m;
+}
+__device__ __forceinline__ float max_of(float m, const v16f_t &d) {
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) m = fmaxf(fmaxf(m, d[r]), d[r + 1]);
+    return m;
+}
+
+// One lane's record of tile t
+template <int REC>
+__device__ __forceinline__ void load_record(const u32 *__restrict__ tab, int t, int lane, u32 (&rec)[REC]) {
+    const u32 *src = tab + (size_t)(uni(t) * 64) * REC + (u32)(lane * REC);
+    if constexpr (REC == 2) {
+        const uint2 v = *reinterpret_cast<const uint2 *>(src);
+        rec[0] = v.x;
+        rec[1] = v.y;
     } else {
-        complete_all<P, W, 1, HIST>(Pv, anyQ, T, lmin, lh, woff, cap);
-    }
-}
-
-// Every combination Q + h_s R_s + h_L R_L of the pairs [e0, e1) of a pair
-// table with the lane's exact base Q, (p-1)^2 per pair: complete_unit for
-// every unit of those pairs, UR units per step with their loads issued before
-// the first is used; the last step's loads may run past the pairs' range into
-// the next set's table or the buffer's PAIR_PAD_UNITS.  GROUPS: whole steps
-// are one basic block each, so that the units' instructions interleave (the
-// batched kernel: +0.9%; the plain kernel, bound by latency, ran 1% slower
-// with the longer code).
-template <int P, int W, bool HIST, bool GROUPS = false>
-__device__ __forceinline__ void sweep_pairs(const uint4 *__restrict__ ptab, int e0, int e1, const u32 (&Q)[3][W],
-                                            u32 &lmin, u32 *lh, u32 woff, u32 cap) {
-    constexpr int UN = (P == 3) ? 1 : P - 1;
-    constexpr int UR = (W <= 2) ? 4 : 2;
-    u32 Pv[1][3][W], anyQ[1][W];
 #pragma unroll
-    for (int w = 0; w < W; w++) {
-#pragma unroll
-        for (int b = 0; b < 3; b++) Pv[0][b][w] = Q[b][w];
-        anyQ[0][w] = Q[0][w] | Q[1][w] | Q[2][w];
-    }
-    const int u1 = uni(e1 * UN);
-    int u = uni(e0 * UN);
-    for (; GROUPS && u + UR <= u1; u += UR) {
-        Row<W> T[UR];
-#pragma unroll
-        for (int i = 0; i < UR; i++) T[i] = load_unit<W>(ptab, u + i);
-#pragma unroll
-        for (int i = 0; i < UR; i++) pin_unit<W>(T[i]);
-#pragma unroll
-        for (int i = 0; i < UR; i++) complete_unit<P, W, HIST>(Pv, anyQ, T[i], lmin, lh, woff, cap);
-    }
-    for (; u < u1; u += UR) {
-        Row<W> T[UR];
-#pragma unroll
-        for (int i = 0; i < UR; i++) T[i] = load_unit<W>(ptab, u + i);
-#pragma unroll
-        for (int i = 0; i < UR; i++) pin_unit<W>(T[i]);
-#pragma unroll
-        for (int i = 0; i < UR; i++) {
-            if (u + i >= u1) break;
-            complete_unit<P, W, HIST>(Pv, anyQ, T[i], lmin, lh, woff, cap);
+        for (int q = 0; q < REC; q += 4) {
+            const uint4 v = reinterpret_cast<const uint4 *>(src)[q / 4];
+            rec[q] = v.x;
+            rec[q + 1] = v.y;
+            rec[q + 2] = v.z;
+            rec[q + 3] = v.w;
         }
     }
 }
 
-// F_7: sweep_pairs for the NA exact sums of a run of bases at once (their
-// planes in Pv, nonzero masks in anyP): each unit, loaded once, serves all of
-// them (complete_all with NA prefixes), so the run's loads, loop control and
-// waits are paid once instead of NA times.
-template <int P, int W, bool HIST, int NA>
-__device__ __forceinline__ void sweep_pairs_multi(const uint4 *__restrict__ ptab, int e0, int e1,
-                                                  const u32 (&Pv)[NA][3][W], const u32 (&anyP)[NA][W], u32 &lmin,
-                                                  u32 *lh, u32 woff, u32 cap) {
-    static_assert(P == 7, "F_7 units");
-    constexpr int UN = P - 1, UR = 4;
-    const int u1 = uni(e1 * UN);
-    int u = uni(e0 * UN);
-    for (; u + UR <= u1; u += UR) {
-        Row<W> T[UR];
+// Between two scheduling barriers: n times one matrix instruction and VALU
+// vector instructions.  A wavefront issues in order and waits at a matrix
+// instruction until the unit is free: with all of them first, the vector
+// instructions behind them wait as well (signed sums of 40 columns over F_7,
+// per tile and SIMD: 1477 cycles in that order, 1381 interleaved; the bound
+// loop, with half the vector work, measured no faster and is left as it is).
+template <int VALU>
+__device__ __forceinline__ void interleave(int n) {
 #pragma unroll
-        for (int i = 0; i < UR; i++) T[i] = load_unit<W>(ptab, u + i);
-#pragma unroll
-        for (int i = 0; i < UR; i++) pin_unit<W>(T[i]);
-#pragma unroll
-        for (int i = 0; i < UR; i++) complete_all<P, W, NA, HIST>(Pv, anyP, T[i], lmin, lh, woff, cap);
+    for (int i = 0; i < n; i++) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);
     }
-    for (; u < u1; u++) {
-        const Row<W> T = load_unit<W>(ptab, u);
-        pin_unit<W>(T);
-        complete_all<P, W, NA, HIST>(Pv, anyP, T, lmin, lh, woff, cap);
+}
+
+constexpr float MASKED = -4096.0f;  // added to the rows of a tile outside the swept range
+
+// minimum over the wavefront, in every lane
+__device__ __forceinline__ u32 wave_min(u32 v) {
+    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false));  // row_shr:1
+    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xf, 0xf, false));
+    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xf, 0xf, false));
+    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xf, 0xf, false));
+    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+    return (u32)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The smallest weight known in a stage, in LDS (F_7 sweeps skip what cannot
+// beat it): the workgroup's findings and, through exchange, the whole
+// device's, which a wavefront's own would lag far behind.  Only one lane of
+// the workgroup talks to memory, once per tile: with every wavefront polling
+// and updating the stage's minimum, the atomics on that one address took 60 us
+// at the start of a stage.  A stale value only costs time.  Weights with the
+// stage's offset woff.
+typedef __attribute__((address_space(3))) u32 lds_u32;
+struct StageBound {
+    lds_u32 *wg;
+    __device__ __forceinline__ u32 best() const { return uni(*(volatile lds_u32 *)wg); }
+    __device__ __forceinline__ u32 lower(u32 w) const {
+        return __hip_atomic_fetch_min(wg, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    // the lanes' weights w, best the value read last
+    __device__ __forceinline__ void offer(u32 w, u32 best) const {
+        if (!__any(w < best)) return;
+        w = wave_min(w);
+        if (__lane_id() == 0) lower(w);
+    }
+    // by one lane after a tile: seen = the stage's minimum as it was read before it
+    __device__ __forceinline__ void publish(int *smin, int seen) const {
+        const u32 mine = *(volatile lds_u32 *)wg;
+        if ((int)mine < seen) atomicMin(smin, (int)mine);
+    }
+    // the same through the workgroup's copy (see ReportState): most of the
+    // values that a first look at the stage lets pass stop there
+    __device__ __forceinline__ void publish(int *smin, int *copy, int seen) const {
+        const u32 mine = *(volatile lds_u32 *)wg;
+        if ((int)mine < seen && atomicMin(copy, (int)mine) > (int)mine) atomicMin(smin, (int)mine);
+    }
+};
+// Whether the bound of a tile (32 units and 32 bases) is worth computing before
+// the signed sums: a unit's symbol reaches it (both zero, or equal exponents)
+// with probability 13/49, so over nsym columns the bound has mean 13/49 nsym
+// and variance nsym 66/343; it takes agreements above nsym - best to pass, and
+// 3000 values pass less often than not four deviations above the mean.  Below
+// that (small stages, whose minimum is still high) most tiles would be summed
+// twice.  (4 x 0.4387 = 1.755)
+__device__ __forceinline__ bool bound_pays(int nsym, int best) {
+    return (float)(nsym - best) + 0.5f - 0.2653f * (float)nsym > 1.755f * __builtin_sqrtf((float)nsym);
+}
+
+// Every combination Q + h T of the lanes' exact bases Q (lane l < ncol has
+// one) and the units T in [u0, u1) of a pair table, through 32 x 32 tiles of
+// units and bases: 64 bases are two column tiles, whose operands stay in
+// registers while the units stream by, one record of 8 to 32 bytes per lane
+// and tile, the next one loaded ahead.  A unit's own weight enters as the
+// start value of the sums, A times a constant operand, once per tile.
+// The last tile may hold units below the range's rows (their sums start at
+// MASKED); the first one may hold units of rows above it, which belong to the
+// same stage: they are counted by the block that owns them and here can only
+// repeat a weight (with histograms they are masked too).
+//
+// F_3: two products per tile pair, 3 S and the signed D;
+// wt = wt(x) - max(-2 wt(y) + 3 S + |D|) / 2.
+// F_7: first an upper bound of the agreements, S + E_t for t = 0, 1, 2 (every
+// sign taken to agree): only a tile in which that bound beats the smallest
+// weight known in the stage is finished with the signed sums,
+// wt = wt(x) - max(-2 wt(y) + 2 S + E_t + |O_t|) / 2.
+// The bound is shared: see StageBound.
+// sweep_units for CT column tiles (32 bases each): their slots, weights and
+// whether a lane's column holds a base.
+template <int P, int W, int SCH, bool HIST, int CT>
+__device__ __forceinline__ void sweep_columns(const u32 *__restrict__ tab, int u0, int u1, int nsym,
+                                              const u32 (&pl)[CT][unit_pieces(SCH, W)],
+                                              const u32 (&nz)[CT][unit_pieces(SCH, W)],
+                                              const u32 (&sg)[CT][unit_pieces(SCH, W)], const u32 (&wx)[CT],
+                                              const bool (&in)[CT], int lane, u32 &lmin, StageBound bound, u32 *lh,
+                                              u32 woff, u32 cap) {
+    constexpr int NP = unit_pieces(SCH, W), REC = unit_rec_words(SCH, W);
+    const int half = lane >> 5;
+    const u32 low_half = half ? 0u : ~0u;
+    const int t0 = uni(u0 >> 5), t1 = uni((u1 + 31) >> 5);
+    u32 ra[REC], rb[REC];
+    load_record<REC>(tab, t0, lane, ra);
+    // The start value of the sums of tile t: `times` the units' own weights
+    // (-1 or -2), and MASKED for the units outside the range, which only the
+    // range's first and last tile can have.  w(i): the unit's word of piece i.
+    auto biased = [&](int t, int times, auto &&w) {
+        v16f_t c;
+#pragma unroll
+        for (int r = 0; r < 16; r++) c[r] = 0.0f;
+        fp4x32 a[NP], kb[NP];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            // (made here: held across the loop they cost registers)
+            const u32 v = here(times == -1 ? fp4_minus1(r) : fp4_minus2(r));
+#pragma unroll
+            for (int i = 0; i < NP; i++) {
+                a[i][r] = fp4_unit(w(i), r);
+                kb[i][r] = slot_used(SCH, i, 1) ? v : v & low_half;
+            }
+        }
+        if (32 * t + 32 > u1 || (HIST && 32 * t < u0)) {
+            const int ub = here(32 * t + 4 * half);
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int u = ub + 8 * (r / 4) + r % 4;
+                c[r] = u < u1 && (!HIST || u >= u0) ? 0.0f : MASKED;
+            }
+            c = mfma_fp4(a[0], kb[0], c);
+        } else {
+            c = mfma_fp4(a[0], kb[0], c);
+        }
+#pragma unroll
+        for (int i = 1; i < NP; i++) c = mfma_fp4(a[i], kb[i], c);
+        return c;
+    };
+    // every tile in turn: body(t, its record).  The next record is on its way
+    // meanwhile; the body is compiled once (the copy at the end waits for the
+    // load, a whole tile after it was issued): a small stage runs each line of
+    // code a few times only, and fetching it costs more than the copies.
+    auto tiles = [&](auto &&body) {
+#pragma unroll 1
+        for (int t = t0; t < t1; t++) {
+            load_record<REC>(tab, min(t + 1, t1 - 1), lane, rb);
+            __builtin_amdgcn_sched_barrier(0);
+            body(t, ra);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < REC; q++) ra[q] = rb[q];
+        }
+    };
+    // one weight of the histogram from its sum v = 2 (wt(x) - wt): its byte
+    // offset among the copies; masked units and columns without a base go to
+    // the lane's own word behind the bins (one word for all lanes would be
+    // served lane by lane)
+    [[maybe_unused]] float hist0[CT];
+    if constexpr (HIST) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ct++)
+            hist0[ct] = in[ct] ? (float)(((wx[ct] + woff) * HIST_COPIES + (u32)(lane & (HIST_COPIES - 1))) * 4) : -8.0f * MASKED;
+    }
+    auto count = [&](int ct, float v) {
+        const u32 at = min((u32)fmaf(v, -2.0f * HIST_COPIES, hist0[ct]), (u32)(HIST_DUMP + lane) * 4u);
+        __hip_atomic_fetch_add((lds_u32 *)((__attribute__((address_space(3))) char *)(lds_u32 *)lh + at), 1u,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    u32 known = BIG;  // bound.best()
+    float m[CT];      // the largest sums, m = 2 (wt(x) - wt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ct++) m[ct] = 4.0f * MASKED;
+    if constexpr (P == 3) {
+        fp4x32 be[CT][NP], bo[CT][NP];
+#pragma unroll
+        for (int ct = 0; ct < CT; ct++)
+#pragma unroll
+            for (int i = 0; i < NP; i++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    be[ct][i][r] = fp4_nonzero3(nz[ct][i], r);
+                    bo[ct][i][r] = fp4_one(nz[ct][i], r) | fp4_signs(sg[ct][i], r);
+                }
+        tiles([&](int t, const u32 (&rec)[REC]) {
+            fp4x32 ae[NP], ao[NP];
+#pragma unroll
+            for (int i = 0; i < NP; i++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    ae[i][r] = fp4_unit(rec[2 * i], r);
+                    ao[i][r] = ae[i][r] | fp4_signs(rec[2 * i + 1], r);
+                }
+            const v16f_t c = biased(t, -2, [&](int i) { return rec[2 * i]; });
+            v16f_t e[CT], o[CT];
+#pragma unroll
+            for (int ct = 0; ct < CT; ct++) {
+                e[ct] = c;
+#pragma unroll
+                for (int r = 0; r < 16; r++) o[ct][r] = 0.0f;
+#pragma unroll
+                for (int i = 0; i < NP; i++) {
+                    e[ct] = mfma_fp4(ae[i], be[ct][i], e[ct]);
+                    o[ct] = mfma_fp4(ao[i], bo[ct][i], o[ct]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ct = 0; ct < CT; ct++) {
+                if constexpr (HIST) {
+#pragma unroll
+                    for (int r = 0; r < 16; r++) {
+                        count(ct, e[ct][r] + o[ct][r]);
+                        count(ct, e[ct][r] - o[ct][r]);
+                    }
+                }
+                m[ct] = max_abs(m[ct], e[ct], o[ct]);
+            }
+        });
+    } else {
+        // piece i of the unit times 2^tt from the record
+        auto unit = [&](const u32 (&rec)[REC], int tt, int i, fp4x32 &a) {
+#pragma unroll
+            for (int r = 0; r < 4; r++) a[r] = fp4_unit(rec[unit_word(SCH, tt, i)], r);
+        };
+        auto biased7 = [&](int t, const u32 (&rec)[REC], int times) {
+            return biased(t, times, [&](int i) { return rec[unit_word(SCH, 0, i)]; });
+        };
+        // the signed sums of N base tiles and tile t: take(its number, d, o)
+        // with d + |o| the largest; the sums of one step are taken while the
+        // products of the next one run (the barriers keep this order)
+        auto signed_sums = [&](int t, const u32 (&rec)[REC], auto &bf, auto &bo, auto &&take) {
+            constexpr int N = sizeof(bf) / sizeof(bf[0]);
+            const v16f_t c = biased7(t, rec, -2);
+            v16f_t d[2], o[2];
+            auto step = [&](int n, v16f_t &dn, v16f_t &on) {
+                dn = c;
+#pragma unroll
+                for (int r = 0; r < 16; r++) on[r] = 0.0f;
+#pragma unroll
+                for (int i = 0; i < NP; i++) {
+                    fp4x32 a, ao;
+                    unit(rec, n / N, i, a);
+#pragma unroll
+                    for (int r = 0; r < 4; r++) ao[r] = a[r] | fp4_signs(rec[unit_sign_word(SCH, i)], r);
+                    dn = mfma_fp4(a, bf[n % N][i], dn);
+                    on = mfma_fp4(ao, bo[n % N][i], on);
+                }
+            };
+            constexpr bool AHEAD = NP <= 2;  // (three pieces and more: not enough registers)
+            if (AHEAD) step(0, d[0], o[0]);
+#pragma unroll
+            for (int n = 0; n < 3 * N; n++) {
+                if (!AHEAD) {
+                    step(n, d[n & 1], o[n & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                } else if (n + 1 < 3 * N) {
+                    step(n + 1, d[(n + 1) & 1], o[(n + 1) & 1]);
+                }
+                take(n % N, d[n & 1], o[n & 1]);
+                if (AHEAD && n + 1 < 3 * N) interleave<6>(2 * NP);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto signed_operands = [&](const u32 (&plc)[NP], const u32 (&nzc)[NP], const u32 (&sgc)[NP], fp4x32 (&bf)[NP],
+                                   fp4x32 (&bo)[NP]) {
+#pragma unroll
+            for (int i = 0; i < NP; i++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    bf[i][r] = fp4_matched(nzc[i], plc[i], r);
+                    bo[i][r] = fp4_one(plc[i], r) | fp4_signs(sgc[i], r);
+                }
+        };
+        // (six pieces: the operands of both passes do not fit the registers)
+        constexpr bool BOUND = !HIST && NP <= 3;
+        bool filter = false;  // (wave-uniform)
+        if constexpr (BOUND) {
+            known = bound.best();
+            filter = bound_pays(nsym, (int)(known - woff));
+        }
+        if (!filter) {
+            fp4x32 bf[CT][NP], bo[CT][NP];
+#pragma unroll
+            for (int ct = 0; ct < CT; ct++) signed_operands(pl[ct], nz[ct], sg[ct], bf[ct], bo[ct]);
+            tiles([&](int t, const u32 (&rec)[REC]) {
+                signed_sums(t, rec, bf, bo, [&](int ct, const v16f_t &d, const v16f_t &o) {
+                    if constexpr (HIST) {
+#pragma unroll
+                        for (int r = 0; r < 16; r++) {
+                            count(ct, d[r] + o[r]);
+                            count(ct, d[r] - o[r]);
+                        }
+                    }
+                    m[ct] = max_abs(m[ct], d, o);
+                });
+            });
+        } else if constexpr (BOUND) {
+            fp4x32 bb[CT][NP];
+            float thr[CT];
+#pragma unroll
+            for (int ct = 0; ct < CT; ct++)
+#pragma unroll
+                for (int i = 0; i < NP; i++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) bb[ct][i][r] = fp4_bound(nz[ct][i], pl[ct][i], r);
+            // the bound wt(x) - v beats best
+            auto thresholds = [&]() {
+#pragma unroll
+                for (int ct = 0; ct < CT; ct++)
+                    thr[ct] = in[ct] ? (float)(wx[ct] + woff) - (float)known : -4.0f * MASKED;
+            };
+            thresholds();
+            tiles([&](int t, const u32 (&rec)[REC]) {
+                const v16f_t c = biased7(t, rec, -1);
+                // 3 CT chains of products; the maxima of one are taken while
+                // the next one runs (the barriers keep this order)
+                float mb[CT];
+#pragma unroll
+                for (int ct = 0; ct < CT; ct++) mb[ct] = 4.0f * MASKED;
+                v16f_t d[2];
+                auto chain = [&](int n) {
+                    v16f_t x = c;
+#pragma unroll
+                    for (int i = 0; i < NP; i++) {
+                        fp4x32 a;
+                        unit(rec, n % 3, i, a);
+                        x = mfma_fp4(a, bb[n / 3][i], x);
+                    }
+                    return x;
+                };
+                d[0] = chain(0);
+#pragma unroll
+                for (int n = 0; n < 3 * CT; n++) {
+                    if (n + 1 < 3 * CT) d[(n + 1) & 1] = chain(n + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mb[n / 3] = max_of(mb[n / 3], d[n & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                u64 hit[CT], any = 0;
+#pragma unroll
+                for (int ct = 0; ct < CT; ct++) {
+                    hit[ct] = __ballot(mb[ct] > thr[ct]);
+                    any |= hit[ct];
+                }
+                if (any) {
+                    known = bound.best();
+                    thresholds();
+#pragma unroll
+                    for (int ct = 0; ct < CT; ct++) hit[ct] = __ballot(mb[ct] > thr[ct]);
+#pragma unroll 1
+                    for (int ct = 0; ct < CT; ct++) {
+                        if (!(ct ? hit[CT - 1] : hit[0])) continue;
+                        // rare: the operands are built here and kept out of the
+                        // loop's registers (here)
+                        u32 rc[REC], plc[NP], nzc[NP], sgc[NP];
+#pragma unroll
+                        for (int q = 0; q < REC; q++) rc[q] = here(rec[q]);
+#pragma unroll
+                        for (int i = 0; i < NP; i++) {
+                            plc[i] = here(ct ? pl[CT - 1][i] : pl[0][i]);
+                            nzc[i] = here(ct ? nz[CT - 1][i] : nz[0][i]);
+                            sgc[i] = here(ct ? sg[CT - 1][i] : sg[0][i]);
+                        }
+                        fp4x32 bf[1][NP], bo[1][NP];
+                        signed_operands(plc, nzc, sgc, bf[0], bo[0]);
+                        float mf = 4.0f * MASKED;
+                        signed_sums(t, rc, bf, bo, [&](int, const v16f_t &dd, const v16f_t &o) { mf = max_abs(mf, dd, o); });
+                        const u32 w = (ct ? in[CT - 1] : in[0]) ? (ct ? wx[CT - 1] : wx[0]) - (u32)(int)(0.5f * mf) : BIG;
+                        lmin = min(lmin, w);
+                        bound.offer(w + woff, known);
+                    }
+                    known = bound.best();
+                    thresholds();
+                }
+            });
+            return;
+        }
+    }
+    u32 w = BIG;
+#pragma unroll
+    for (int ct = 0; ct < CT; ct++)
+        if (in[ct]) w = min(w, wx[ct] - (u32)(int)(0.5f * m[ct]));
+    lmin = min(lmin, w);
+    if constexpr (P == 7 && !HIST) bound.offer(w + woff, known);
+}
+
+template <int P, int W, int SCH, bool HIST>
+__device__ __forceinline__ void sweep_units(const u32 *__restrict__ tab, int u0, int u1, int nsym,
+                                            const u32 (&Q)[3][W], int ncol, u32 &lmin, StageBound bound, u32 *lh,
+                                            u32 woff, u32 cap) {
+    constexpr int NP = unit_pieces(SCH, W);
+    const int lane = here((int)__lane_id());
+    // the bases' slots: tile ct holds the bases of lanes 32 ct .. 32 ct + 31
+    u32 pl[2][NP], nz[2][NP], sg[2][NP], wx[2];
+    {
+        u32 p2[NP][2], n2[NP][2], s2[NP][2];
+        base_slots<P, W, SCH>(Q, p2, n2, s2);
+#pragma unroll
+        for (int i = 0; i < NP; i++) {
+            swap_halves(p2[i][0], p2[i][1]);
+            swap_halves(n2[i][0], n2[i][1]);
+            swap_halves(s2[i][0], s2[i][1]);
+#pragma unroll
+            for (int ct = 0; ct < 2; ct++) {
+                pl[ct][i] = p2[i][ct];
+                nz[ct][i] = n2[i][ct];
+                sg[ct][i] = s2[i][ct];
+            }
+        }
+        u32 wt = 0;
+#pragma unroll
+        for (int w = 0; w < W; w++) wt += __builtin_popcount(Q[0][w] | Q[1][w] | Q[2][w]);
+        wx[0] = wx[1] = wt;
+        swap_halves(wx[0], wx[1]);
+    }
+    const bool in[2] = {(lane & 31) < ncol, 32 + (lane & 31) < ncol};
+    if constexpr (NP <= 3 && !HIST) {
+        sweep_columns<P, W, SCH, HIST, 2>(tab, u0, u1, nsym, pl, nz, sg, wx, in, lane, lmin, bound, lh, woff, cap);
+    } else {
+        // six pieces: the operands of two column tiles do not fit the registers;
+        // histograms: their code is long (two additions and an LDS operation
+        // per weight), and two column tiles of it overflow the instruction cache
+#pragma unroll 1
+        for (int ct = 0; ct < 2; ct++) {
+            u32 p1[1][NP], n1[1][NP], s1[1][NP];
+#pragma unroll
+            for (int i = 0; i < NP; i++) {
+                p1[0][i] = ct ? pl[1][i] : pl[0][i];
+                n1[0][i] = ct ? nz[1][i] : nz[0][i];
+                s1[0][i] = ct ? sg[1][i] : sg[0][i];
+            }
+            const u32 w1[1] = {ct ? wx[1] : wx[0]};
+            const bool i1[1] = {ct ? in[1] : in[0]};
+            sweep_columns<P, W, SCH, HIST, 1>(tab, u0, u1, nsym, p1, n1, s1, w1, i1, lane, lmin, bound, lh, woff, cap);
+        }
     }
 }
 
@@ -1138,7 +1709,7 @@ __device__ __forceinline__ void prefixes_then_complete(const u32 (&Q)[3][W], con
 // multiplier through complete_all.
 // Adds the combinations completed to the lane's count ncomb.
 template <int P, int W, int G, bool HIST>
-__device__ __forceinline__ void run_subset(const u32 *__restrict__ rows, const uint4 *lrows, int j,
+__device__ __forceinline__ void run_subset(const u32 *__restrict__ rows, LdsRows lrows, int j,
                                            const int (&r)[G], u32 &lmin, u32 &ncomb, u32 *lh, u32 woff, u32 cap) {
     constexpr int NA = 1;  // one prefix at a time (registers)
     const Row<W> R0 = load_row_lane<P, W>(rows, lrows, j, r[0]);
@@ -1169,7 +1740,7 @@ __device__ __forceinline__ void run_subset(const u32 *__restrict__ rows, const u
 // g <= SUBSET_G: one item per lane (a row, a pair of rows, a triple; colex
 // rank task * 64 + lane).  Adds the combinations the lane evaluated to lcnt.
 template <int P, int W, bool HIST>
-__device__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows, const uint4 *lrows,
+__device__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
                                const u64 *sbin, const u64 *__restrict__ gbin, u64 task, u32 &lmin, u64 &lcnt,
                                u32 *lh, u32 woff, u32 cap) {
     const int lane = __lane_id();
@@ -1234,28 +1805,51 @@ __device__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows
 // 1 -> 2) or subtracted (2 -> 1) per step; F_7 (vd = 1) through the
 // coefficients 1 .. 6 of row q, one addition of row q per step.  Adds the
 // combinations the lane evaluated (the rows its sweeps combined) to lcnt.
-// TABLE_ONLY: every caller passes a pair table, and the path without one is
-// not compiled (it would hold the p-1 prefixes in registers).  GROUPS: see
-// sweep_pairs.
-template <int P, int W, bool HIST, bool TABLE_ONLY = false, bool GROUPS = false>
-__device__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__restrict__ rows, const uint4 *lrows,
-                              const uint4 *__restrict__ ptab, const u64 *sbin, const u64 *__restrict__ gbin,
-                              const QEntry *qtab, int nq, u64 task, u32 &lmin, u64 &lcnt, u32 *lh, u32 woff,
-                              u32 cap) {
+// SCH: the layout of the set's pair table (unit_scheme), or NO_TABLE: the
+// prefixes are built here.  bound, seen (thread 0): F_7 with a table, see StageBound.
+constexpr int NO_TABLE = -1;
+template <int P, int W, bool HIST, int SCH>
+__device__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
+                              const u32 *__restrict__ ptab, uint32_t triple_off, const u64 *sbin,
+                              const u64 *__restrict__ gbin, const QEntry *qtab, int nq, u64 task, StageBound bound, int seen, int nsym, u32 &lmin, u64 &lcnt, u32 *lh,
+                              u32 woff, u32 cap) {
     const int lane = __lane_id();
-    const int g = uni(sd.g);
-    const u64 M = uni(sd.coef_combos);
-    const int qi = uni(qtable_find(qtab, nq, task));
+    const bool triples = SCH != NO_TABLE && uni(sd.vcap) == TRIPLES;
+    const int g = uni(sd.g) - (triples ? 1 : 0);  // the base has g - 2 rows
+    const u64 M = triples ? uni(sd.coef_combos) / (u32)(P - 1) : uni(sd.coef_combos);
+    // the q-group of the task: lane l looks at entry l, the last one that
+    // starts at or before the task is it (a binary search reads LDS six times
+    // in a row, 100 cycles each)
+    const QEntry &qe = qtab[min(lane, nq - 1)];
+    const u64 l_first = qe.first, l_bases = qe.bases;
+    const uint32_t l_nb = qe.nb, l_vd = qe.vd;
+    const int qi = 63 - __builtin_clzll(__ballot(lane < nq && l_first <= task));
     const int q = g - 3 + qi;
-    // the q-group's entry as wave-uniform (scalar) values
-    const u64 e_first = uni64(qtab[qi].first), e_bases = uni64(qtab[qi].bases);
-    const uint32_t e_nb = uni(qtab[qi].nb);
-    const int vd = uni(qtab[qi].vd);
-    const u64 local = task - e_first;
-    const u64 chunk = local / e_nb;
+    auto entry64 = [&](u64 v) {
+        return ((u64)(u32)__builtin_amdgcn_readlane((int)(v >> 32), qi) << 32) |
+               (u32)__builtin_amdgcn_readlane((int)(u32)v, qi);
+    };
+    const u64 e_first = entry64(l_first), e_bases = entry64(l_bases);
+    const uint32_t e_nb = (uint32_t)__builtin_amdgcn_readlane((int)l_nb, qi);
+    const int vd = __builtin_amdgcn_readlane((int)l_vd, qi);
+    const u64 local = uni64(task - e_first);
+    const u64 chunk = (local >> 32) == 0 ? (u64)((u32)local / e_nb) : local / e_nb;
     const int block = (int)(local - chunk * e_nb);
-    const int s_lo = q + 1 + uni(qgroup_block_start(k, q, e_nb, (uint32_t)block));
-    const int s_hi = q + 1 + uni(qgroup_block_start(k, q, e_nb, (uint32_t)block + 1));
+    int s_lo = 0, s_hi = 0;  // rows s of the block (pairs)
+    int u0 = 0, u1 = 0;      // units of the block (with a table)
+    if (triples) {
+        const uint32_t tiles = triple_tiles(P, k, q);
+        u0 = 32 * (int)triple_block_start(tiles, e_nb, (uint32_t)block);
+        u1 = min(32 * (int)triple_block_start(tiles, e_nb, (uint32_t)block + 1), triple_units(P, k, q));
+        ptab += (size_t)triple_off * 4;
+    } else {
+        s_lo = q + 1 + uni(qgroup_block_start(k, q, e_nb, (uint32_t)block));
+        s_hi = q + 1 + uni(qgroup_block_start(k, q, e_nb, (uint32_t)block + 1));
+        u0 = first_unit(P, k, (int)pair_first(s_hi, k));
+        u1 = first_unit(P, k, (int)pair_first(s_lo, k));
+    }
+    u0 = uni(u0);
+    u1 = uni(u1);
     const u64 bi = (chunk * 64 + (u64)lane) * (u64)run_len(P, (uint32_t)vd);
     const bool valid = bi < e_bases;  // the bases of a lane's run are valid together (its length divides bases)
     u32 Q[3][W];
@@ -1264,22 +1858,18 @@ __device__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__re
 #pragma unroll
         for (int w = 0; w < W; w++) Q[b][w] = 0;
     // combinations this lane completes: p-1 coefficients of row s times p-1
-    // multipliers of every last row its sweeps combine
+    // multipliers of every last row its sweeps combine (p-1 multiples of a unit)
     constexpr u32 PER_ROW = (u32)((P - 1) * (P - 1));
     u32 ncomb = 0;
     // every row s of the block and every last row L > s for the lane's base Q:
     // from the set's pair table when it has one, else through the exact
     // prefixes Q + h R_s
+    const int ncol = __builtin_popcountll(__ballot(valid));  // the valid lanes are the first ones
     auto sweep_block = [&]() {
-        if (TABLE_ONLY || ptab != nullptr) {
-            const int e0 = uni((int)pair_first(s_lo, k)), e1 = uni((int)pair_first(s_hi, k));
-            if (valid) {
-                sweep_pairs<P, W, HIST, GROUPS>(ptab, e0, e1, Q, lmin, lh, woff, cap);
-                ncomb += PER_ROW * (u32)(e1 - e0);
-            }
-            return;
-        }
-        if constexpr (!TABLE_ONLY) {
+        if constexpr (SCH != NO_TABLE) {
+            sweep_units<P, W, SCH, HIST>(ptab, u0, u1, nsym, Q, ncol, lmin, bound, lh, woff, cap);
+            if (valid) ncomb += (u32)(P - 1) * (u32)(u1 - u0);
+        } else {
             for (int s = s_lo; s < s_hi; s++) {
                 const Row<W> Rs = load_row<P, W>(rows, j, uni(s));
                 if (valid)
@@ -1288,75 +1878,35 @@ __device__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__re
             }
         }
     };
-    if (vd == 0) {
-        // one base per lane
-        if (valid) {
-            decode_base<P>(g, q, M, bi, [&](int c, int i) { return binom_at(sbin, gbin, c, i); },
-                           [&](int row, int coef) {
-                               const Row<W> r = load_row_lane<P, W>(rows, lrows, j, row);
-                               add_scaled<P, W>(Q, r.p, coef);
-                           });
-        }
-        sweep_block();
-        lcnt += ncomb;
-        return;
-    }
-    if constexpr (P == 7) {
-        // a run of 6 bases per lane: the first has coefficient 1 on row q (its
-        // digit 0 is 0, the run being aligned), the next ones 2, ..., 6, each
-        // one addition of row q (wave-uniform) away from the previous
-        if (valid) {
-            decode_base<P>(g, q, M, bi, [&](int c, int i) { return binom_at(sbin, gbin, c, i); },
-                           [&](int row, int coef) {
-                               const Row<W> r = load_row_lane<P, W>(rows, lrows, j, row);
-                               add_scaled<P, W>(Q, r.p, coef);
-                           });
-        }
-        const Row<W> Rq = load_row<P, W>(rows, j, q);
-        if constexpr (TABLE_ONLY && W == 1) {
-            // the six sums of the run at once (sweep_pairs_multi)
-            u32 Pv[P - 1][3][W], anyP[P - 1][W];
-#pragma unroll
-            for (int v = 0; v < P - 1; v++) {
-                if (v > 0) add_scaled<P, W>(Q, Rq.p, 1);
-#pragma unroll
-                for (int w = 0; w < W; w++) {
-#pragma unroll
-                    for (int b = 0; b < 3; b++) Pv[v][b][w] = Q[b][w];
-                    anyP[v][w] = Q[0][w] | Q[1][w] | Q[2][w];
-                }
-            }
-            const int e0 = uni((int)pair_first(s_lo, k)), e1 = uni((int)pair_first(s_hi, k));
-            if (valid) {
-                sweep_pairs_multi<P, W, HIST, P - 1>(ptab, e0, e1, Pv, anyP, lmin, lh, woff, cap);
-                ncomb += (P - 1) * PER_ROW * (u32)(e1 - e0);
-            }
-        } else {
-            for (int v = 0; v < P - 1; v++) {
-                if (v > 0 && valid) add_scaled<P, W>(Q, Rq.p, 1);
-                sweep_block();
-            }
-        }
-    }
-    if constexpr (P == 3) {
-        // a run of 2^vd bases per lane; the rows of digits 1 and 2 are held
-        // (lane-specific), row q (digit 0) is loaded again (wave-uniform)
-        Row<W> Rd1, Rd2;
-        if (valid) {
-            int vi = 0;
-            decode_base<P>(g, q, M, bi, [&](int c, int i) { return binom_at(sbin, gbin, c, i); },
-                           [&](int row, int coef) {
-                               const Row<W> r = load_row_lane<P, W>(rows, lrows, j, row);
-                               add_scaled<P, W>(Q, r.p, coef);
+    // the first base of the lane's run; F_3 holds the rows of digits 1 and 2
+    // (lane-specific), row q (digit 0) is loaded again (wave-uniform)
+    Row<W> Rd1, Rd2;
+    if (valid) {
+        int vi = 0;
+        decode_base<P>(g, q, M, bi, [&](int c, int i) { return binom_at(sbin, gbin, c, i); },
+                       [&](int row, int coef) {
+                           const Row<W> r = load_row_lane<P, W>(rows, lrows, j, row);
+                           add_scaled<P, W>(Q, r.p, coef);
+                           if constexpr (P == 3) {
                                if (vi == 1) Rd1 = r;
                                if (vi == 2) Rd2 = r;
                                vi++;
-                           });
-        }
-        const int nv = 1 << vd;
-        uint32_t cur = 0;  // bit t: digit t's row has coefficient 2 (wave-uniform)
-        for (int v = 0; v < nv; v++) {
-            if (v > 0) {
+                           }
+                       });
+    }
+    // thread 0's look at the stage's minimum, on its way since the tile began
+    if (P == 7 && SCH != NO_TABLE && !HIST && threadIdx.x == 0) bound.lower((u32)seen);
+    const int nv = (int)run_len(P, (uint32_t)vd);
+    uint32_t cur = 0;  // F_3: bit t: digit t's row has coefficient 2 (wave-uniform)
+    for (int v = 0; v < nv; v++) {
+        if (v > 0) {
+            if constexpr (P == 7) {
+                // the first base has coefficient 1 on row q (its digit 0 is 0,
+                // the run being aligned), the next ones 2, ..., 6, each one
+                // addition of row q (wave-uniform) away from the previous
+                const Row<W> Rq = load_row<P, W>(rows, j, q);
+                if (valid) add_scaled<P, W>(Q, Rq.p, 1);
+            } else {
                 const int t = __builtin_ctz((uint32_t)v);
                 const int h = ((cur >> t) & 1u) ? 2 : 1;  // 1 -> 2: + row; 2 -> 1: - row = + 2 row
                 cur ^= 1u << t;
@@ -1369,8 +1919,8 @@ __device__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__re
                     if (valid) add_scaled<P, W>(Q, Rd2.p, h);
                 }
             }
-            sweep_block();
         }
+        sweep_block();
     }
     lcnt += ncomb;
 }
@@ -1420,28 +1970,33 @@ __device__ void run_checker(CodeState *cs, const StageDesc *sdesc, int ns, const
     }
 }
 
-// TAB: the launch has pair tables (the base rounds take their two highest
-// rows from them; no prefix path is compiled), or has none.
-template <int P, int W, bool HIST, bool TAB>
-__global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__restrict__ rows,
+// SCH: the layout of the launch's pair tables (the base rounds take their two
+// highest rows from them; no prefix path is compiled), or NO_TABLE.
+// (workgroups per compute unit: what the registers allow without spills)
+template <int P, int W, bool HIST, int SCH>
+__global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2) void enum_kernel(CodeState *cs, const u32 *__restrict__ rows,
                                                    const uint4 *__restrict__ pairs, const u64 *__restrict__ gbin,
                                                    u64 *__restrict__ hist, EnumArgs ea) {
+    constexpr bool TAB = SCH != NO_TABLE;
     const int lookahead = ea.lookahead;
     const u64 timeout_ticks = ea.timeout_ticks;
     const int pslot1 = TAB ? uni(cs->pair_slot1) : 1;  // slot of set 1's pair table
     __shared__ u64 sbin[BZ_MAX_K * BIN_I];
     __shared__ StageDesc sdesc[BZ_MAX_STAGES];
     __shared__ QEntry qtab[BZ_MAX_K];
-    __shared__ u32 lhist[HIST ? WAVES_PER_GROUP * (BZ_MAX_N + 1) : 1];
+    __shared__ u32 lhist[HIST ? WAVES_PER_GROUP * HIST_WORDS : 1];
     __shared__ u32 red_min[WAVES_PER_GROUP];
     __shared__ u64 red_cnt[WAVES_PER_GROUP];
+    __shared__ u32 s_best;  // see StageBound
     __shared__ int s_term;
     __shared__ int s_crit;
     __shared__ u64 s_claim[2];
     __shared__ int s_cterm[2];
-    // F_3: the rows of the first matrices, for the loads at lane-specific rows
-    // (measured: 2-3% faster F_3 codes; F_7 codes slightly slower)
-    __shared__ uint4 lrow_buf[P == 3 ? LROW_SETS * BZ_MAX_K * W : 1];
+    // the rows of the first matrices, for the loads at lane-specific rows (with
+    // tables, two workgroups per compute unit leave room for four; without, the
+    // third would cost F_3 a workgroup, and F_7 measured none faster)
+    constexpr int LSETS = TAB ? 4 : P == 3 ? 2 : 0;
+    __shared__ uint4 lrow_buf[LSETS ? LSETS * BZ_MAX_K * W : 1];
     const int lane = __lane_id();
     const int wid = threadIdx.x >> 6;
     const uint32_t grid = gridDim.x, b = blockIdx.x;
@@ -1461,22 +2016,21 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
     const int status0 = cs->res.status, ns0 = cs->res.n_table;
     constexpr int EARLY = 32;  // descriptors loaded before the table size is known
     if (threadIdx.x < EARLY) sdesc[threadIdx.x] = cs->stages[threadIdx.x];
-    if constexpr (P == 3) {
-        // the rows of the first LROW_SETS matrices (the row buffer holds every
+    if constexpr (LSETS != 0) {
+        // the rows of the first LSETS matrices (the row buffer holds every
         // set, so the sets past m read unused rows): loads issued before any store
-        constexpr int NR = LROW_SETS * BZ_MAX_K * W, PER = (NR + 255) / 256;
-        uint4 v[PER];
+        constexpr int NR = LSETS * BZ_MAX_K * W, PER = (NR + 255) / 256;
+        typedef u32 v4u_t __attribute__((ext_vector_type(4)));
+        v4u_t v[PER];
 #pragma unroll
         for (int r = 0; r < PER; r++) {
             const int t = (int)threadIdx.x + r * 256;
             const int jj = t / (BZ_MAX_K * W), rem = t - jj * (BZ_MAX_K * W), i = rem / W, w = rem - i * W;
-            if (t < NR) v[r] = reinterpret_cast<const uint4 *>(rows + (size_t)(jj * BZ_MAX_K + i) * ROW_WORDS)[w];
+            if (t < NR) v[r] = reinterpret_cast<const v4u_t *>(rows + (size_t)(jj * BZ_MAX_K + i) * ROW_WORDS)[w];
         }
 #pragma unroll
-        for (int r = 0; r < PER; r++) {
-            const int t = (int)threadIdx.x + r * 256;
-            if (t < NR) lrow_buf[t] = v[r];
-        }
+        for (int r = 0; r < PER; r++)
+            if ((int)threadIdx.x + r * 256 < NR) reinterpret_cast<v4u_t *>(lrow_buf)[(int)threadIdx.x + r * 256] = v[r];
     }
     stage_binomials(sbin, gbin, k);  // the rows c < k: every binomial the stages read
     if (threadIdx.x >= EARLY && (int)threadIdx.x < ns0) sdesc[threadIdx.x] = cs->stages[threadIdx.x];
@@ -1485,39 +2039,54 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
     const int ns = uni(ns0);
     const bool skip = (ea.flags & FLAG_SKIP) != 0;
     u64 *wake = &cs->wake[b % WAKE_COPIES][0];
-    u32 *lh = HIST ? &lhist[wid * (BZ_MAX_N + 1)] : nullptr;
+    u32 *lh = HIST ? &lhist[wid * HIST_WORDS] : nullptr;
     const u32 cap = (u32)n;
-    const uint4 *lrows = nullptr;
-    if constexpr (P == 3) lrows = lrow_buf;  // (filled before the first barrier)
+    const LdsRows lrows{lrow_buf, LSETS};  // (filled before the first barrier)
     // the pool (see pool_stages): its stages complete when all their tiles
     // are done, so their part count in this workgroup's copy is the tile count
     u64 pool_tiles;
-    const int sp = uni(pool_stages(sdesc, ns, grid, &pool_tiles));
+    const uint32_t deal = TAB ? ea.deal_grid : grid;
+    ReportState *const rep = ea.reports;
+    const uint32_t copies = report_copies(grid), rcopy = b % copies;
+    const int sp = uni(pool_stages(sdesc, ns, deal, &pool_tiles));
     pool_tiles = uni64(pool_tiles);
-    if ((int)threadIdx.x < sp) sdesc[threadIdx.x].parts = (uint32_t)sdesc[threadIdx.x].tiles;
+    if ((int)threadIdx.x < sp) {
+        sdesc[threadIdx.x].parts = (uint32_t)sdesc[threadIdx.x].tiles;
+    } else if (TAB && (int)threadIdx.x < ns) {
+        // dealt to the workgroups there are
+        StageDesc &d = sdesc[threadIdx.x];
+        d.parts = (uint32_t)(d.tiles < (u64)grid ? d.tiles : (u64)grid);
+        d.rot %= grid;
+    }
     __syncthreads();
 
+    auto reset_best = [&]() {  // by one thread, before the barrier that starts the stage
+        if constexpr (P == 7 && TAB && !HIST) s_best = BIG;
+    };
     // one tile of stage s: wavefront wid runs task tile * 4 + wid
-    auto run_tile = [&](const StageDesc &sd, int s, u64 tile, u32 &lmin, u64 &lcnt) {
+    auto run_tile = [&](const StageDesc &sd, int s, u64 tile, StageBound bound, int seen, u32 &lmin, u64 &lcnt) {
         const int sg = uni(sd.g);
         const u64 tasks = uni64(sd.tasks);
         const u64 task = tile * WAVES_PER_GROUP + (u64)wid;
         if (task >= tasks) return;  // a missing task only happens in the last tile
         const u32 woff = skip ? (u32)sg : 0u;
         if constexpr (HIST) {
-            for (int w = lane; w <= n; w += 64) lh[w] = 0;
+            for (int w = lane; w < (n + 1) * HIST_COPIES; w += 64) lh[w] = 0;
         }
         if (sg > SUBSET_G) {
             const int sj = uni(sd.j - 1);
-            const uint4 *ptab = TAB ? pairs + (size_t)(sj == 1 ? pslot1 : sj) * ea.pair_stride : nullptr;
-            run_base_task<P, W, HIST, TAB>(sd, k, sj, rows, lrows, ptab, sbin, gbin, qtab, k - 2 - (sg - 3), task,
-                                           lmin, lcnt, lh, woff, cap);
+            const u32 *ptab =
+                TAB ? reinterpret_cast<const u32 *>(pairs + (size_t)(sj == 1 ? pslot1 : sj) * ea.pair_stride) : nullptr;
+            run_base_task<P, W, HIST, SCH>(sd, k, sj, rows, lrows, ptab, ea.triple_off, sbin, gbin, qtab, k + 1 - sg, task,
+                                           bound, seen, skip ? n - k : n, lmin, lcnt, lh, woff, cap);
         }
         else
             run_small_task<P, W, HIST>(sg, k, uni(sd.j - 1), rows, lrows, sbin, gbin, task, lmin, lcnt, lh, woff, cap);
         if constexpr (HIST) {
             for (int w = lane; w <= n; w += 64) {
-                const u32 c = lh[w];
+                u32 c = 0;
+#pragma unroll
+                for (int i = 0; i < HIST_COPIES; i++) c += lh[w * HIST_COPIES + i];
                 if (c) atomicAdd((unsigned long long *)&hist[(size_t)s * (BZ_MAX_N + 1) + w], (unsigned long long)c);
             }
         }
@@ -1543,16 +2112,34 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
         if (wid == 0) {
             uint32_t done = 0;
             if (lane == 0) {
+                bool last = true;
                 u32 bm = red_min[0];
                 u64 bc = red_cnt[0];
                 for (int w = 1; w < WAVES_PER_GROUP; w++) {
                     bm = min(bm, red_min[w]);
                     bc += red_cnt[w];
                 }
-                if (bm != BIG) atomicMin(&cs->res.stage_min[s], (int)(bm + woff));
-                atomicAdd((unsigned long long *)&cs->res.stage_count[s], (unsigned long long)bc);
-                drain_vmem();  // minimum and count performed before done counts this workgroup
-                done = __hip_atomic_fetch_add(&cs->stage_done[s], add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+                if constexpr (TAB) {
+                    // to this workgroup's copy; its last report carries the sums on (see ReportState)
+                    if (bm != BIG) atomicMin(&rep->min[rcopy][s], (int)(bm + woff));
+                    const u64 rest = bc >> REPORT_COUNT_BITS << REPORT_COUNT_BITS;
+                    if (rest) atomicAdd((unsigned long long *)&cs->res.stage_count[s], (unsigned long long)rest);
+                    drain_vmem();  // minimum and count performed before the report counts
+                    const u64 mine = (bc - rest) | ((u64)add << 48);
+                    const u64 sum =
+                        __hip_atomic_fetch_add(&rep->word[rcopy][s], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
+                    add = s < sp ? report_pool_tiles((uint32_t)nowait_offset(sd.rot, deal), (uint32_t)sd.tiles, grid, rcopy, copies)
+                                 : report_groups(sd.rot, sd.parts, grid, rcopy, copies);
+                    last = (uint32_t)(sum >> 48) == add;
+                    bc = sum & ((1ull << 48) - 1);
+                    if (last) bm = (u32)rd_atomic(&rep->min[rcopy][s]) - woff;
+                }
+                if (last) {
+                    if (bm + woff != BIG) atomicMin(&cs->res.stage_min[s], (int)(bm + woff));
+                    atomicAdd((unsigned long long *)&cs->res.stage_count[s], (unsigned long long)bc);
+                    drain_vmem();  // minimum and count performed before done counts them
+                    done = __hip_atomic_fetch_add(&cs->stage_done[s], add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+                }
                 if (tr_wg || (tracing && done == sd.parts))  // the last one always
                     atomicMax((unsigned long long *)&cs->trace[2 + s][1], (unsigned long long)wall_clock64());
             }
@@ -1563,10 +2150,14 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
             }
         } else if (wid == 1 && next >= 0 && sdesc[next].g > SUBSET_G) {
             const StageDesc &nd = sdesc[next];
+            if (lane == 0) reset_best();
             wave_qtable(P, k, nd.g, nd.coef_combos, nd.sweep_cap, nd.vcap, sbin, gbin, qtab);
         }
         __syncthreads();  // qtab and red_* are rewritten next
     };
+
+    const StageBound bound{(lds_u32 *)&s_best};
+    constexpr bool BOUND = P == 7 && TAB && !HIST;
 
     if (sp > 0) {
         // the pool: workgroup b runs pool tile b first, then claims the
@@ -1588,6 +2179,7 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
             // the next claim and the progress word, read while the tile runs
             uint32_t ci = 0;
             u64 wk = 0;
+            int seen = (int)BIG;
             if (threadIdx.x == 0 && u != ~0ull) {
                 ci = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 wk = ld_poll(wake);
@@ -1595,7 +2187,7 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
             int sn = ps < 0 ? 0 : ps;
             bool end = u == ~0ull;
             if (!end) {
-                sn = uni(pool_stage_of(sdesc, sp, sn, u, grid));
+                sn = uni(pool_stage_of(sdesc, sp, sn, u, deal));
                 // the run ended before this stage (the claim just made is of a
                 // later stage still, and is dropped)
                 end = t2 >= 0 && sn > t2;
@@ -1608,6 +2200,7 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
             } else if (!end && sn != ps) {
                 // the first stage of this workgroup
                 const StageDesc &sd = sdesc[sn];
+                if (threadIdx.x == 0) reset_best();
                 if (wid == 0 && sd.g > SUBSET_G)
                     wave_qtable(P, k, sd.g, sd.coef_combos, sd.sweep_cap, sd.vcap, sbin, gbin, qtab);
                 __syncthreads();
@@ -1615,16 +2208,19 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
             if (end) break;
             if (sn != ps) {
                 ps = sn;
-                pbase = nowait_offset(uni(sdesc[sn].rot), grid);
+
+                pbase = nowait_offset(uni(sdesc[sn].rot), deal);
                 if (tr_wg && threadIdx.x == 0) {
                     const unsigned long long now = (unsigned long long)wall_clock64();
                     atomicMin((unsigned long long *)&cs->trace[2 + sn][0], now);
                     atomicMax((unsigned long long *)&cs->trace[2 + sn][3], now);
                 }
             }
-            run_tile(sdesc[ps], ps, u - pbase, lmin, lcnt);
+            if (BOUND && threadIdx.x == 0) seen = ld_poll(&cs->res.stage_min[ps]);
+            run_tile(sdesc[ps], ps, u - pbase, bound, seen, lmin, lcnt);
             pheld++;
             if (threadIdx.x == 0) {
+                if (BOUND) bound.publish(&cs->res.stage_min[ps], &rep->min[rcopy][ps], seen);
                 const u64 nu = (u64)grid + pool_tile(slice, ci, C);
                 s_claim[it & 1] = nu < pool_tiles ? nu : ~0ull;
                 s_cterm[it & 1] = wake_term(wk);
@@ -1677,6 +2273,7 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
                 atomicMin((unsigned long long *)&cs->trace[2 + s][0], now);
                 atomicMax((unsigned long long *)&cs->trace[2 + s][3], now);
             }
+            reset_best();
             s_crit = wake_checked(st) >= s;  // the earliest unchecked stage: no later stage can wait on it
         }
         if (wid == 0 && sd.g > SUBSET_G) {
@@ -1702,7 +2299,10 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
                 const int t2 = uni(lane == 0 ? wake_term(ld_poll(wake)) : 0);
                 if (t2 >= 0 && s > t2) break;
             }
-            run_tile(sd, s, tile, lmin, lcnt);
+            int seen = (int)BIG;
+            if (BOUND && threadIdx.x == 0) seen = ld_poll(&cs->res.stage_min[s]);
+            run_tile(sd, s, tile, bound, seen, lmin, lcnt);
+            if (BOUND && threadIdx.x == 0) bound.publish(&cs->res.stage_min[s], &rep->min[rcopy][s], seen);
         }
         flush_stage(s, lmin, lcnt, 1u, -1);
     }
@@ -1717,7 +2317,7 @@ __global__ __launch_bounds__(256) void enum_kernel(CodeState *cs, const u32 *__r
 // One workgroup (one wavefront) per code (or per listed slot).  Also
 // publishes the code's first claim word and counts it in
 // BatchState::remaining.
-__global__ __launch_bounds__(64) void decompose_batch_kernel(const uint8_t *__restrict__ G,
+__global__ __launch_bounds__(DECOMP_THREADS) void decompose_batch_kernel(const uint8_t *__restrict__ G,
                                                              const BatchCode *__restrict__ codes, CodeState *css,
                                                              u64 *claims, u32 *__restrict__ rows,
                                                              uint4 *__restrict__ pairs, uint32_t grid,
@@ -1727,6 +2327,11 @@ __global__ __launch_bounds__(64) void decompose_batch_kernel(const uint8_t *__re
     if (threadIdx.x == 0) atomicMin((unsigned long long *)&bs->t0, (unsigned long long)wall_clock64());
     const int c = slots ? slots[blockIdx.x] : (int)blockIdx.x;  // a list of slots, or every code
     const BatchCode bc = codes[c];
+    if (threadIdx.x >= 64) {
+        if (bc.p == 3) help_tables<3>(lds, bc.k, bc.W, bc.scheme);
+        else help_tables<7>(lds, bc.k, bc.W, bc.scheme);
+        return;
+    }
     CodeState *cs = css + c;
     RunArgs a;
     a.n = bc.n;
@@ -1743,7 +2348,9 @@ __global__ __launch_bounds__(64) void decompose_batch_kernel(const uint8_t *__re
     a.pad = 0;
     a.pairs = pairs + bc.pair_offset;  // every code of a batch or a serving slot has its tables
     a.pair_stride = bc.pair_stride;
-    a.pair_w = bc.W;
+    a.pair_w = (int16_t)bc.W;
+    a.pair_scheme = (int16_t)bc.scheme;
+    a.triples = bc.triple_off != 0;
     const uint8_t *g = G + bc.g_offset;
     u32 *r = rows + bc.row_offset;
     if (bc.p == 3) {
@@ -1761,6 +2368,7 @@ __global__ __launch_bounds__(64) void decompose_batch_kernel(const uint8_t *__re
         default: decompose_code<7, 4>(g, cs, r, a, lds); break;
         }
     }
+    release_helpers(lds);
     int work = 0;
     if (threadIdx.x == 0) {
         // lane 0 wrote the status, the table size and stage 0 itself
@@ -1793,12 +2401,12 @@ __global__ void features_kernel(const CodeState *__restrict__ css, const int32_t
 
 // The tiles of one part of a stage: tile_of(r, part, parts, rot) for r = 0, 1, ...
 // The lane's combinations are added to lcnt.
-template <int P, int W>
-__device__ void run_part(const StageDesc &sd, int s, uint32_t part, int k, const u32 *__restrict__ rows,
-                         const uint4 *__restrict__ ptab, const u64 *sbin, const u64 *__restrict__ gbin,
-                         const QEntry *qtab, u32 woff, u32 cap, u32 &lmin, u64 &lcnt) {
+template <int P, int W, int SCH>
+__device__ void run_part(const StageDesc &sd, StageBound bound, int *smin, uint32_t part, int k, const u32 *__restrict__ rows,
+                         const u32 *__restrict__ ptab, uint32_t triple_off, const u64 *sbin,
+                         const u64 *__restrict__ gbin, const QEntry *qtab, int nsym, u32 woff, u32 cap, u32 &lmin, u64 &lcnt) {
     const int wid = threadIdx.x >> 6;
-    const int g = uni(sd.g), j = uni(sd.j - 1), nq = k - 2 - (g - 3);
+    const int g = uni(sd.g), j = uni(sd.j - 1), nq = k + 1 - g;
     const u64 tiles = uni64(sd.tiles), tasks = uni64(sd.tasks);
     const uint32_t parts = uni(sd.parts);
     for (u64 r = 0;; r++) {
@@ -1806,11 +2414,14 @@ __device__ void run_part(const StageDesc &sd, int s, uint32_t part, int k, const
         if (tile >= tiles) break;
         const u64 task = tile * WAVES_PER_GROUP + (u64)wid;
         if (task >= tasks) continue;
+        int seen = (int)BIG;
+        if (P == 7 && threadIdx.x == 0) seen = ld_poll(smin);
         if (g > SUBSET_G)
-            run_base_task<P, W, false, true, true>(sd, k, j, rows, nullptr, ptab, sbin, gbin, qtab, nq, task, lmin, lcnt, nullptr, woff,
-                                      cap);
+            run_base_task<P, W, false, SCH>(sd, k, j, rows, LdsRows{nullptr, 0}, ptab, triple_off, sbin, gbin, qtab, nq, task, bound, seen, nsym, lmin, lcnt,
+                                            nullptr, woff, cap);
         else
-            run_small_task<P, W, false>(g, k, j, rows, nullptr, sbin, gbin, task, lmin, lcnt, nullptr, woff, cap);
+            run_small_task<P, W, false>(g, k, j, rows, LdsRows{nullptr, 0}, sbin, gbin, task, lmin, lcnt, nullptr, woff, cap);
+        if (P == 7 && threadIdx.x == 0) bound.publish(smin, seen);
     }
 }
 
@@ -1850,7 +2461,7 @@ __device__ void batch_check(CodeState *cs, u64 *claim, int s, const StageDesc &s
 // progress in its claim word for the next launch) and done_flags (mapped host
 // flags raised as codes end).
 template <int WMAX>
-__global__ __launch_bounds__(256) void enum_batch_kernel(CodeState *css, u64 *claims,
+__global__ __launch_bounds__(256, WMAX <= 2 ? 2 : 1) void enum_batch_kernel(CodeState *css, u64 *claims,
                                                          const BatchCode *__restrict__ codes,
                                                          int ncodes, const u32 *__restrict__ rows,
                                                          const uint4 *__restrict__ pairs,
@@ -1862,6 +2473,7 @@ __global__ __launch_bounds__(256) void enum_batch_kernel(CodeState *css, u64 *cl
     __shared__ QEntry qtab[BZ_MAX_K];
     __shared__ u32 red_min[WAVES_PER_GROUP];
     __shared__ u64 red_cnt[WAVES_PER_GROUP];
+    __shared__ u32 s_best;  // see StageBound
     __shared__ int s_code, s_stage;
     __shared__ uint32_t s_part;
     const int lane = __lane_id();
@@ -1931,6 +2543,7 @@ __global__ __launch_bounds__(256) void enum_batch_kernel(CodeState *css, u64 *cl
             }
             if (code >= 0) scan = (uint32_t)code + 1u;
             if (lane == 0) {
+                s_best = BIG;
                 s_code = code;
                 s_stage = stage;
                 s_part = part;
@@ -1948,24 +2561,37 @@ __global__ __launch_bounds__(256) void enum_batch_kernel(CodeState *css, u64 *cl
         const StageDesc sd = cs->stages[s];
         if (wid == 0 && sd.g > SUBSET_G) wave_qtable(p, k, sd.g, sd.coef_combos, sd.sweep_cap, sd.vcap, sbin, gbin, qtab);
         __syncthreads();
-        const u32 woff = (uni(codes[code].flags) & FLAG_SKIP) ? (u32)sd.g : 0u;
+        const bool skip = (uni(codes[code].flags) & FLAG_SKIP) != 0;
+        const u32 woff = skip ? (u32)sd.g : 0u;
+        const int nsym = skip ? n - k : n;
         const u32 cap = (u32)n;
         const u32 *r = rows + row_off;
         // (every code of a batch or a serving slot has its pair tables)
-        const uint4 *pt = pairs + uni64(codes[code].pair_offset) + (size_t)uni(sd.j - 1) * uni(codes[code].pair_stride);
+        const u32 *pt = reinterpret_cast<const u32 *>(pairs + uni64(codes[code].pair_offset) +
+                                                      (size_t)uni(sd.j - 1) * uni(codes[code].pair_stride));
+        const StageBound bound{(lds_u32 *)&s_best};
+        int *smin = &cs->res.stage_min[s];
+        const uint32_t toff = uni(codes[code].triple_off);
         u32 lmin = BIG;
         u64 lcnt = 0;
+        const int sch = uni(codes[code].scheme);
+#define BZ_PART(P, W, SCH) run_part<P, W, SCH>(sd, bound, smin, part, k, r, pt, toff, sbin, gbin, qtab, nsym, woff, cap, lmin, lcnt)
         if (p == 3) {
-            if (W == 1) run_part<3, 1>(sd, s, part, k, r, pt, sbin, gbin, qtab, woff, cap, lmin, lcnt);
-            if constexpr (WMAX >= 2) if (W == 2) run_part<3, 2>(sd, s, part, k, r, pt, sbin, gbin, qtab, woff, cap, lmin, lcnt);
-            if constexpr (WMAX >= 3) if (W == 3) run_part<3, 3>(sd, s, part, k, r, pt, sbin, gbin, qtab, woff, cap, lmin, lcnt);
-            if constexpr (WMAX >= 4) if (W == 4) run_part<3, 4>(sd, s, part, k, r, pt, sbin, gbin, qtab, woff, cap, lmin, lcnt);
+            if (W == 1) BZ_PART(3, 1, 0);
+            if constexpr (WMAX >= 2) if (W == 2) BZ_PART(3, 2, 0);
+            if constexpr (WMAX >= 3) if (W == 3) BZ_PART(3, 3, 0);
+            if constexpr (WMAX >= 4) if (W == 4) BZ_PART(3, 4, 0);
         } else {
-            if (W == 1) run_part<7, 1>(sd, s, part, k, r, pt, sbin, gbin, qtab, woff, cap, lmin, lcnt);
-            if constexpr (WMAX >= 2) if (W == 2) run_part<7, 2>(sd, s, part, k, r, pt, sbin, gbin, qtab, woff, cap, lmin, lcnt);
-            if constexpr (WMAX >= 3) if (W == 3) run_part<7, 3>(sd, s, part, k, r, pt, sbin, gbin, qtab, woff, cap, lmin, lcnt);
-            if constexpr (WMAX >= 4) if (W == 4) run_part<7, 4>(sd, s, part, k, r, pt, sbin, gbin, qtab, woff, cap, lmin, lcnt);
+            if (sch == 1) BZ_PART(7, 1, 1);
+            else if (sch == 2) BZ_PART(7, 1, 2);
+            if constexpr (WMAX >= 2) {
+                if (sch == 3) BZ_PART(7, 2, 3);
+                else if (sch == 4) BZ_PART(7, 2, 4);
+            }
+            if constexpr (WMAX >= 3) if (W == 3) BZ_PART(7, 3, 5);
+            if constexpr (WMAX >= 4) if (W == 4) BZ_PART(7, 4, 5);
         }
+#undef BZ_PART
         for (int off = 32; off >= 1; off >>= 1) {
             lmin = min(lmin, (u32)__shfl_xor((int)lmin, off));
             lcnt += __shfl_xor(lcnt, off);

@@ -89,7 +89,7 @@ struct StageDesc {
     uint32_t sweep_cap;    // g >= 3: target (s, L) steps per lane and task
     uint32_t rot;          // (grid - off_s mod grid) mod grid, see tile_of
     uint32_t vcap;         // step budget of a lane's run of bases (qgroup_digits);
-                           // 0: one base per lane
+                           // 0: one base per lane; TRIPLES: bases of g-3 rows
     uint32_t pad;
 };
 
@@ -170,8 +170,10 @@ struct BatchCode {
     int32_t p, n, k, flags;
     int32_t U0, WF, W;    // words per plane of G, and processed per combination
     uint32_t sweep_ops;  // VALU operations per lane and task
-    uint32_t pair_stride;  // 16-byte units per pair table (pair_table_units(p, k, W))
-    u64 pair_offset;       // 16-byte offset of its first pair table
+    uint32_t pair_stride;  // 16-byte words between the tables of two sets
+    u64 pair_offset;       // 16-byte offset of its first table
+    int32_t scheme;        // layout of its tables (unit_scheme)
+    uint32_t triple_off;   // 16-byte words from a set's pair table to its triples; 0: no triples
 };
 
 // Batch-wide state: codes with stages left, the error flag of a time-out, and
@@ -681,6 +683,47 @@ BZ_HD int pool_stages(const StageDesc *st, int ns, uint32_t grid, u64 *tiles) {
     if (sp > 0 && st[sp - 1].tiles > pool_stage_cap(grid)) sp--;
     *tiles = sp > 0 ? nowait_offset(st[sp - 1].rot, grid) + st[sp - 1].tiles : 0;
     return sp;
+}
+// Reports of the matrix-sweep kernel's workgroups on a stage meet in copies,
+// one per slice of the workgroups (workgroup b reports to copy b mod C, C =
+// report_copies), and the last report of a copy carries the copy's sums on to
+// the stage: atomics on one address are served one after the other, 11 ns
+// each, and five hundred workgroups that leave a stage together queued for
+// 5.6 us per atomic on the stage's own words (0.4 us on sixteen copies;
+// [48, 24] over F_7: 1307 -> 1166 us for 8 codes).  The kernel without tables
+// reports to the stage directly: its workgroups leave a stage one by one, and
+// the step in between only made the checks later ([89, 29] over F_3: 645 us
+// for 2 codes directly, 705 us through copies).
+// C divides the pool's slices, so a pool tile's copy follows from its number.
+constexpr uint32_t REPORT_COPIES = 16;
+static_assert(POOL_SLICES % REPORT_COPIES == 0, "a slice of the pool has one copy");
+BZ_HD uint32_t report_copies(uint32_t grid) { return grid < POOL_SLICES ? 1u : REPORT_COPIES; }
+struct ReportState {
+    // reports (bits 48-63) and combinations (bits 0-47) of each stage
+    u64 word[REPORT_COPIES][BZ_MAX_STAGES];
+    int32_t min[REPORT_COPIES][BZ_MAX_STAGES];
+};
+// A report adds less than 2^32 combinations to the copy's word (the rest goes
+// to the stage directly), and a copy takes at most 33 reports per workgroup of
+// the schedule's grid over C, so neither field overflows.
+constexpr int REPORT_COUNT_BITS = 32;
+// numbers x in [lo, hi) with x mod C = c
+BZ_HD uint32_t slice_members(uint32_t lo, uint32_t hi, uint32_t c, uint32_t C) {
+    return (hi + C - 1 - c) / C - (lo + C - 1 - c) / C;
+}
+// tiles of a pool stage that copy c's workgroups run: tiles [off, off + tiles)
+// of the pool, the first `grid` of them by workgroup, the others by claim
+BZ_HD uint32_t report_pool_tiles(uint32_t off, uint32_t tiles, uint32_t grid, uint32_t c, uint32_t C) {
+    const uint32_t lo = off, hi = off + tiles;
+    const uint32_t l0 = lo < grid ? lo : grid, h0 = hi < grid ? hi : grid;
+    return slice_members(l0, h0, c, C) + slice_members(lo - l0, hi - h0, c, C);
+}
+// workgroups of copy c with a tile of a dealt stage (see tile_of): those at
+// positions 0 .. parts - 1 of the deal, the first being workgroup off_s mod grid
+BZ_HD uint32_t report_groups(uint32_t rot, uint32_t parts, uint32_t grid, uint32_t c, uint32_t C) {
+    const uint32_t b0 = (grid - rot) % grid, e = b0 + parts;
+    const uint32_t e0 = e < grid ? e : grid;
+    return slice_members(b0, e0, c, C) + slice_members(0, e - e0, c, C);
 }
 // pool tile number i of slice c, counted from the first claimed tile (grid)
 BZ_HD u64 pool_tile(uint32_t c, uint32_t i, uint32_t C) { return (u64)c + (u64)C * i; }

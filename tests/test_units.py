@@ -1,0 +1,55 @@
+"""The pair tables as matrix operands: the operand words and their products on
+the CPU (plain integers as the reference), and the matrix sweep on the GPU at
+the sizes where its layouts and tiles change, against the oracle."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2603_29942_amd", "csrc")
+
+
+def test_operand_words(tmp_path):
+    exe = os.path.join(str(tmp_path), "unit_checks")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-DBZ_HD=inline", "-I", CSRC, "-I",
+                    os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "unit_checks.cpp"), "-o", exe],
+                   check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    assert out.stdout.splitlines() == ["OK weights", "OK order", "OK triples", "OK reports"]
+
+
+# (p, columns processed, k): the first and last column count of every layout
+# (F_7: 21 | 32 | 42 | 64 | 128, F_3: 64 | 128), and k around the tiles of 32
+# units (F_3: 2 units a pair, 17 pairs end in a second tile; F_7: 6 a pair)
+SHAPES = [(3, 1, 5), (3, 31, 6), (3, 32, 7), (3, 33, 8), (3, 64, 9), (3, 65, 7), (3, 96, 6), (3, 97, 6),
+          (7, 1, 5), (7, 20, 5), (7, 21, 6), (7, 22, 5), (7, 32, 6), (7, 33, 5), (7, 42, 6), (7, 43, 5), (7, 64, 5),
+          (7, 65, 5), (7, 96, 5), (7, 97, 5), (7, 122, 6)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,nsym,k", SHAPES)
+def test_sweep_at_layout_edges(p, nsym, k):
+    """Every stage of a code (no early end) on the plain path with tables, with
+    and without histograms, and batched: the oracle's trace, the histograms'
+    lowest weight and their sum being the stage's minimum and count."""
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from oracle import bzref
+    from paper_2603_29942_amd import bz
+    rng = np.random.default_rng([31, p, nsym, k])
+    G = rng.integers(0, p, size=(k, nsym + k), dtype=np.uint8)
+    G[:, :k] = np.eye(k, dtype=np.uint8)  # full rank
+    if nsym > 3:
+        G[:, k + 1] = 0  # a column that no sum fills
+    ref = bzref.min_distance(p, G, no_termination=True)
+    got = [bz.min_distance(p, G, no_termination=True, pair_tables=1),
+           bz.min_distance(p, G, no_termination=True, pair_tables=1, histograms=True)]
+    got += bz.min_distance_batch([(p, G)], no_termination=True, device="cuda:0")
+    for r in got:
+        for key in ("status", "d", "m", "ranks", "stages", "codewords_total"):
+            assert r[key] == ref[key], (key, r[key], ref[key])
+    for stage, h in zip(got[1]["stages"], got[1]["hist"]):
+        assert int(h.sum()) == stage[2] and int(np.nonzero(h)[0][0]) == stage[3]
