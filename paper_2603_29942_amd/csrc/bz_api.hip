@@ -887,7 +887,7 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
 int bz_mlp_forward(const float *params, const float *x, int n, float *y, float *cache, void *stream) {
     if (!params || n < 0 || (n > 0 && (!x || !y))) return BZ_ERR_ARG;
     if (n == 0) return BZ_OK;
-    mlp_forward_kernel<<<(n + 255) / 256, 256, 0, (hipStream_t)stream>>>(params, x, n, y, cache);
+    mlp_forward_kernel<<<(n + MLP_FWD_SAMPLES - 1) / MLP_FWD_SAMPLES, 256, 0, (hipStream_t)stream>>>(params, x, n, y, cache);
     return hipGetLastError() == hipSuccess ? BZ_OK : BZ_ERR_DEVICE;
 }
 
@@ -895,9 +895,9 @@ int bz_mlp_backward(const float *params, const float *x, const float *target, in
                     const float *cache, float *dz, float *grad, float *loss, void *stream) {
     if (!params || !x || !target || n < 1 || !y || !cache || !dz || !grad) return BZ_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
-    mlp_delta_kernel<<<(n + 255) / 256, 256, 0, s>>>(params, target, n, y, cache, dz);
-    mlp_grad_kernel<<<(MLP_NPARAM + 255) / 256, 256, 0, s>>>(x, n, cache, dz, grad);
-    if (loss) mlp_loss_kernel<<<1, 64, 0, s>>>(y, target, n, loss);
+    const int chunks = mlp_chunks(n);
+    mlp_grad_kernel<<<chunks, 256, 0, s>>>(params, x, target, n, y, cache, dz, grad, loss);
+    if (chunks > 1) mlp_sum_kernel<<<(MLP_NSUM + 63) / 64, 256, 0, s>>>(dz, chunks, n, grad, loss);
     return hipGetLastError() == hipSuccess ? BZ_OK : BZ_ERR_DEVICE;
 }
 
@@ -1287,7 +1287,7 @@ int server_queue_predictions(bz_server *s) {
             mlp_features(r.p, r.n, r.k, 0, s->qfeat_h + 4 * j);
         }
         HIP_OK(hipMemcpyAsync(s->feat_d, s->qfeat_h, sizeof(float) * 4 * (size_t)nq, hipMemcpyHostToDevice, s->run));
-        mlp_forward_kernel<<<(nq + 255) / 256, 256, 0, s->run>>>(s->mlp_d, s->feat_d, nq, s->pred_d, nullptr);
+        mlp_forward_kernel<<<(nq + MLP_FWD_SAMPLES - 1) / MLP_FWD_SAMPLES, 256, 0, s->run>>>(s->mlp_d, s->feat_d, nq, s->pred_d, nullptr);
         HIP_OK(hipGetLastError());
         HIP_OK(hipMemcpyAsync(s->pred_h, s->pred_d, sizeof(float) * (size_t)nq, hipMemcpyDeviceToHost, s->run));
         HIP_OK(hipStreamSynchronize(s->run));
@@ -1381,7 +1381,7 @@ int server_round(bz_server *s) {
         }
         if (s->o.policy == BZ_SERVE_PREDICTED) {
             features_kernel<<<(nf + 63) / 64, 64, 0, s->run>>>(s->cs, s->new_d, nf, s->feat_d);
-            mlp_forward_kernel<<<(nf + 255) / 256, 256, 0, s->run>>>(s->mlp_d, s->feat_d, nf, s->pred_d, nullptr);
+            mlp_forward_kernel<<<(nf + MLP_FWD_SAMPLES - 1) / MLP_FWD_SAMPLES, 256, 0, s->run>>>(s->mlp_d, s->feat_d, nf, s->pred_d, nullptr);
             HIP_OK(hipGetLastError());
             HIP_OK(hipMemcpyAsync(s->pred_h, s->pred_d, sizeof(float) * (size_t)nf, hipMemcpyDeviceToHost, s->run));
             HIP_OK(hipStreamSynchronize(s->run));
