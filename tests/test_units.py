@@ -53,3 +53,21 @@ def test_sweep_at_layout_edges(p, nsym, k):
             assert r[key] == ref[key], (key, r[key], ref[key])
     for stage, h in zip(got[1]["stages"], got[1]["hist"]):
         assert int(h.sum()) == stage[2] and int(np.nonzero(h)[0][0]) == stage[3]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,n,k,hist,tables", [(3, 30, 13, False, False), (3, 30, 14, False, True),
+                                               (3, 30, 14, True, False), (7, 16, 5, True, True)])
+def test_default_tables(p, n, k, hist, tables):
+    """Which plain calls take tables by default, and that both ways agree."""
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2603_29942_amd import bz
+    G = np.random.default_rng([32, p, n, k]).integers(0, p, size=(k, n), dtype=np.uint8)
+    G[:, :k] = np.eye(k, dtype=np.uint8)
+    r = bz.min_distance(p, G, histograms=hist)
+    assert bool(r["info"] & bz.INFO_PAIRS) == tables
+    for pt in (-1, 1):
+        o = bz.min_distance(p, G, histograms=hist, pair_tables=pt)
+        for key in ("status", "d", "m", "ranks", "stages", "codewords_total"):
+            assert o[key] == r[key], (key, o[key], r[key])
