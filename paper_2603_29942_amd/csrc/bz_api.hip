@@ -1161,7 +1161,8 @@ struct bz_server {
     hipStream_t run = nullptr;  // the launches
     hipEvent_t round_done = nullptr;
     bz_server_options o{};
-    int slots = 0, grid = 0, decomp_grid = 0, flags = 0;
+    int slots = 0, decomp_grid = 0, flags = 0;
+    int grid = 0, grid2 = 0;  // workgroups of a round: any words, up to two words
     u64 max_cw = 0, timeout = 0, rows_per_slot = 0, g_per_slot = 0, pairs_per_slot = 0;
     // device
     CodeState *cs = nullptr;
@@ -1278,7 +1279,8 @@ hipError_t server_launch(bz_server *s, int nactive) {
     uint32_t *done = s->done_dev;
     CodeResult *resm = s->res_dev;
     void *args[] = {&css, &clm, &cds, &nc, &rows, &prs, &bin, &bs, &to, &order, &yield, &done, &resm};
-    return hipLaunchKernel((const void *)enum_batch_kernel<WMAX>, dim3(s->grid), dim3(256), args, 0, s->run);
+    return hipLaunchKernel((const void *)enum_batch_kernel<WMAX>, dim3(WMAX <= 2 ? s->grid2 : s->grid), dim3(256), args, 0,
+                           s->run);
 }
 
 // Predicted policy: the network's work estimate for the queued requests that
@@ -1419,7 +1421,10 @@ int server_round(bz_server *s) {
     if (s->c->plain_active.load()) return BZ_OK;
     HIP_OK(hipMemcpyAsync(s->order_d, s->order_h, sizeof(int32_t) * act.size(), hipMemcpyHostToDevice, s->run));
     __atomic_store_n(s->yield_h, 0u, __ATOMIC_RELEASE);
-    HIP_OK(wmax <= 2 && s->wmax <= 2 ? server_launch<2>(s, (int)act.size()) : server_launch<4>(s, (int)act.size()));
+    // by the codes in hand, not by the longest the server takes: the kernel of
+    // up to two words runs two workgroups per compute unit, the other one (its
+    // operands of six pieces take more registers) a single one
+    HIP_OK(wmax <= 2 ? server_launch<2>(s, (int)act.size()) : server_launch<4>(s, (int)act.size()));
     HIP_OK(hipEventRecord(s->round_done, s->run));
     s->running = true;
     s->rounds++;
@@ -1472,10 +1477,11 @@ int bz_server_start(const bz_server_options *opt, bz_server **out) {
     if (!s->triples) s->pairs_per_slot = max_table_size(max_n, o.identity_skip ? 1 : 0, false, false);
     s->g_per_slot = (u64)(((max_n * BZ_MAX_K) + 255) / 256 * 256);
     s->grid = batch_grid(s->wmax, c->cu, o.blocks_per_cu ? o.blocks_per_cu : 64);  // default: as many as fit
-    s->decomp_grid = s->grid * 8;  // smaller parts: a yield waits for at most one short part
+    s->grid2 = batch_grid(2, c->cu, o.blocks_per_cu ? o.blocks_per_cu : 64);
+    s->decomp_grid = std::max(s->grid, s->grid2) * 8;  // smaller parts: a yield waits for at most one short part
     s->slot.resize((size_t)s->slots);
     const size_t ns = (size_t)s->slots;
-    bool ok = s->grid > 0 && hipStreamCreateWithFlags(&s->run, hipStreamNonBlocking) == hipSuccess &&
+    bool ok = s->grid > 0 && s->grid2 > 0 && hipStreamCreateWithFlags(&s->run, hipStreamNonBlocking) == hipSuccess &&
               hipEventCreateWithFlags(&s->round_done, hipEventDisableTiming) == hipSuccess &&
               hipMalloc(&s->cs, sizeof(CodeState) * ns) == hipSuccess &&
               hipMalloc(&s->claims, sizeof(u64) * ns) == hipSuccess &&
