@@ -168,7 +168,7 @@ bool triples_worth(int p, int n, int k, int nsym, uint32_t cap, u64 launch_tiles
     u64 build = sat_mul(triple_tiles(p, k, -1), (u64)sets) + launch_tiles, saved = 0;
     for (int g = TRIPLE_G; g <= gm && round_combos(p, g) < (1ull << 32); g++) {
         u64 c3;
-        triple_round(p, k, g, cap, host_binom(), &c3);
+        triple_round(p, k, g, cap, false, host_binom(), &c3);
         const u64 c2 = pair_round_cost(p, k, g, cap, host_binom());
         if (c2 > c3) saved = sat_add(saved, sat_mul(c2 - c3, (u64)sets));
     }
@@ -463,7 +463,7 @@ int get_shape(DevCtx &c, int p, int n, int k, int W, int nsym, int grid, int sch
         const uint32_t ops = plain_sweep_ops(p), cap = sweep_cap_for(p, W, ops);
         fill_round_table(p, k, W, (uint32_t)grid, ops, host_binom(), &t);
         sh.triples = sch != NO_TABLE && triples_worth(p, n, k, nsym, cap, TRIPLE_LAUNCH_TILES);
-        if (sh.triples) take_triples(p, k, cap, host_binom(), &t);
+        if (sh.triples) take_triples(p, k, cap, (uint32_t)grid, host_binom(), &t);
         HIP_OK(hipMalloc(&sh.rounds, sizeof(RoundTable)));
         if (hipMemcpy(sh.rounds, &t, sizeof(RoundTable), hipMemcpyHostToDevice) != hipSuccess) {
             (void)hipFree(sh.rounds);

@@ -160,7 +160,7 @@ enum { ROLE_MAIN = 0, ROLE_AHEAD = 1, ROLE_TABLE0 = 2 };
 __device__ __forceinline__ u64 wave_qtable(int p, int k, int g, u64 M, uint32_t cap, uint32_t vcap,
                                            const u64 *sbin, const u64 *__restrict__ gbin, QEntry *tab) {
     const int lane = __lane_id();
-    const bool triples = vcap == TRIPLES;  // (wave-uniform)
+    const bool triples = (vcap & TRIPLES) != 0;  // (wave-uniform)
     const int q = g - (triples ? 4 : 3) + lane;
     const bool in = lane <= k - g;
     u64 bases = 0, val = 0;
@@ -168,8 +168,10 @@ __device__ __forceinline__ u64 wave_qtable(int p, int k, int g, u64 M, uint32_t 
     if (in && triples) {
         const u64 c = (g - 4 < BIN_I) ? sbin[q * BIN_I + (g - 4)] : gbin[q * 65 + (g - 4)];
         bases = triple_bases(p, c, M);
-        nb = triple_blocks(triple_tiles(p, k, q), triple_cap(p, cap));
-        val = sat_mul(ceil64(bases), nb);
+        const uint32_t tiles = triple_tiles(p, k, q);
+        nb = triple_blocks(tiles, triple_cap(p, cap));
+        vd = triple_digits(p, g, tiles, nb, bases, (vcap & 1u) != 0);
+        val = triple_tasks(p, bases, nb, vd);
     } else if (in) {
         // the values of qgroup
         const u64 c = (g - 3 < BIN_I) ? sbin[q * BIN_I + (g - 3)] : gbin[q * 65 + (g - 3)];
@@ -854,7 +856,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
             // that the unrolled LDS reads overlap
             const int q0 = uni(SUBSET_G - 2);  // the smallest g - 3 of a counted round
             const bool try3 = triples && g >= TRIPLE_G;
-            u64 t3 = 0, cost2 = 0, cost3 = 0;  // with triples: tasks; the costs of both
+            u64 t3 = 0, t3v = 0, cost2 = 0, cost3 = 0;  // with triples: tasks without and with runs; the costs of both
 #pragma unroll 4
             for (int q = q0; q <= k - 3; q++) {
                 if (q < g - 3) continue;
@@ -870,16 +872,19 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
                     if (q < g - 4) continue;
                     const u64 bases = triple_bases(P, binom[q * 65 + (g - 4)], combos);
                     const uint32_t nb = lds.s_nb3[q];
-                    t3 = sat_add(t3, sat_mul(ceil64(bases), nb));
-                    cost3 = sat_add(cost3, triple_group_cost(triple_tiles(P, k, q), bases, nb));
+                    const uint32_t tiles = triple_tiles(P, k, q);
+                    t3 = sat_add(t3, triple_tasks(P, bases, nb, 0));
+                    t3v = sat_add(t3v, triple_tasks(P, bases, nb, triple_digits(P, g, tiles, nb, bases, true)));
+                    cost3 = sat_add(cost3, triple_group_cost(tiles, bases, nb));
                 }
             }
             // the round takes runs of bases where they pay (qgroup_digits with
             // the run budget, as a table of digits_by_steps)
             const bool runs = runs_pay(tgv, args.grid);
             const bool use3 = try3 && cost3 < cost2;
-            s_tasks[lane] = use3 ? t3 : runs ? tgv : tg;
-            lds.s_vcap[lane] = use3 ? TRIPLES : runs ? budget : 0u;
+            const bool runs3 = runs_pay(t3v, args.grid);
+            s_tasks[lane] = use3 ? (runs3 ? t3v : t3) : runs ? tgv : tg;
+            lds.s_vcap[lane] = use3 ? TRIPLES | (runs3 ? 1u : 0u) : runs ? budget : 0u;
         }
         // the first round with 2^62 tasks or more cuts the table before it
         const u64 over = __ballot(counted && tg >= (1ull << 62));
@@ -1814,7 +1819,7 @@ __device__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__re
                               const u64 *__restrict__ gbin, const QEntry *qtab, int nq, u64 task, StageBound bound, int seen, int nsym, u32 &lmin, u64 &lcnt, u32 *lh,
                               u32 woff, u32 cap) {
     const int lane = __lane_id();
-    const bool triples = SCH != NO_TABLE && uni(sd.vcap) == TRIPLES;
+    const bool triples = SCH != NO_TABLE && (uni(sd.vcap) & TRIPLES) != 0;
     const int g = uni(sd.g) - (triples ? 1 : 0);  // the base has g - 2 rows
     const u64 M = triples ? uni(sd.coef_combos) / (u32)(P - 1) : uni(sd.coef_combos);
     // the q-group of the task: lane l looks at entry l, the last one that

@@ -74,7 +74,7 @@ BZ_HD int first_unit(int p, int k, int e) { return (k * (k - 1) / 2 - e) * (p - 
 // table per set.  Unit u = r (p-1)^2 + (c1-1)(p-1) + c2-1 of the triple
 // a = k-1-i, b = k-1-j, c = k-1-l with colex rank r = C(i,3) + C(j,2) + l of
 // l < j < i, so that the triples above row q are again the first ones.
-constexpr uint32_t TRIPLES = 1u << 31;  // StageDesc::vcap of a round that takes triples
+constexpr uint32_t TRIPLES = 1u << 31;  // in StageDesc::vcap of a round that takes triples; + 1: in runs
 constexpr int TRIPLE_G = 5;             // the first round that can
 BZ_HD int choose2(int n) { return n * (n - 1) / 2; }
 BZ_HD int choose3(int n) { return n * (n - 1) / 2 * (n - 2) / 3; }
@@ -107,8 +107,27 @@ BZ_HD u64 triple_group_cost(uint32_t tiles, u64 bases, uint32_t nb) {
 }
 // the bases of g-3 rows with top row q; M = (p-1)^(g-3), as for pairs
 BZ_HD u64 triple_bases(int p, u64 binom_q_g4, u64 M) { return sat_mul(binom_q_g4, M / (u64)(p - 1)); }
-// tasks (64 bases by one block) and cost of round g with triples
-BZ_HD u64 triple_round(int p, int k, int g, uint32_t cap, const u64 *binom, u64 *cost) {
+// Low coefficient digits of the bases that a lane runs through itself, as with
+// pairs (see digits_of): most bases meet few triples, and decoding one takes
+// as long as ten tiles, so that a task of short sweeps takes (p-1)^d bases per
+// lane, each one row away from the last, up to RUN_TILES tiles in all (about
+// 30 us).  [56, 28] over F_7: 3.05 -> 1.96 ms; 128 mixed requests, 34 -> 25 ms.
+// runs: the round has enough tasks for it (runs_pay).
+constexpr uint32_t RUN_TILES = 96;
+BZ_HD uint32_t triple_digits(int p, int g, uint32_t tiles, uint32_t nb, u64 bases, bool runs) {
+    const uint32_t fit = runs ? RUN_TILES / ((tiles + nb - 1) / nb) : 0;  // (every group has a tile)
+    if (fit < (uint32_t)(p - 1)) return 0;
+    uint32_t d = p == 3 ? 31u - (uint32_t)__builtin_clz(fit) : 1u;
+    const uint32_t most = (uint32_t)(g - 4) < max_digits(p) ? (uint32_t)(g - 4) : max_digits(p);
+    d = d < most ? d : most;
+    const uint32_t b = digits_by_bases(p, bases);
+    return b < d ? b : d;
+}
+BZ_HD u64 triple_tasks(int p, u64 bases, uint32_t nb, uint32_t vd) {
+    return sat_mul(ceil64(p == 3 ? bases >> vd : (vd ? bases / (u64)(p - 1) : bases)), nb);
+}
+// tasks (64 lanes by one block) and cost of round g with triples
+BZ_HD u64 triple_round(int p, int k, int g, uint32_t cap, bool runs, const u64 *binom, u64 *cost) {
     const uint32_t cap3 = triple_cap(p, cap);
     const u64 M = round_combos(p, g);
     u64 tasks = 0;
@@ -116,7 +135,7 @@ BZ_HD u64 triple_round(int p, int k, int g, uint32_t cap, const u64 *binom, u64 
     for (int q = g - 4; q <= k - 4; q++) {
         const u64 bases = triple_bases(p, binom[q * 65 + (g - 4)], M);
         const uint32_t tiles = triple_tiles(p, k, q), nb = triple_blocks(tiles, cap3);
-        tasks = sat_add(tasks, sat_mul(ceil64(bases), nb));
+        tasks = sat_add(tasks, triple_tasks(p, bases, nb, triple_digits(p, g, tiles, nb, bases, runs)));
         *cost = sat_add(*cost, triple_group_cost(tiles, bases, nb));
     }
     return tasks;
@@ -128,15 +147,18 @@ BZ_HD u64 pair_round_cost(int p, int k, int g, uint32_t cap, const u64 *binom) {
         cost = sat_add(cost, pair_group_cost(p, k, q, sat_mul(binom[q * 65 + (g - 3)], M), qgroup_blocks(k, cap, q)));
     return cost;
 }
-// A round table whose rounds take triples where they cost less.
-BZ_HD void take_triples(int p, int k, uint32_t cap, const u64 *binom, RoundTable *t) {
+// A round table whose rounds take triples where they cost less, in runs where
+// a stage then still has a tile for every workgroup of the grid.
+BZ_HD void take_triples(int p, int k, uint32_t cap, uint32_t grid, const u64 *binom, RoundTable *t) {
     for (int g = TRIPLE_G; g <= k; g++) {
         if (round_combos(p, g) >= (1ull << 32) || g >= t->cut_g) break;
         u64 c3;
-        const u64 tasks = triple_round(p, k, g, cap, binom, &c3);
+        const u64 tasks = triple_round(p, k, g, cap, false, binom, &c3);
         if (c3 >= pair_round_cost(p, k, g, cap, binom)) continue;
-        t->tasks[g - 1] = tasks;
-        t->vcap[g - 1] = TRIPLES;
+        const u64 tv = triple_round(p, k, g, cap, true, binom, &c3);
+        const bool runs = runs_pay(tv, grid);
+        t->tasks[g - 1] = runs ? tv : tasks;
+        t->vcap[g - 1] = TRIPLES | (runs ? 1u : 0u);
     }
 }
 

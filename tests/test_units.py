@@ -71,3 +71,23 @@ def test_default_tables(p, n, k, hist, tables):
         o = bz.min_distance(p, G, histograms=hist, pair_tables=pt)
         for key in ("status", "d", "m", "ranks", "stages", "codewords_total"):
             assert o[key] == r[key], (key, o[key], r[key])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,n,k", [(7, 48, 20), (7, 56, 24), (7, 63, 21), (3, 80, 28), (3, 89, 29), (3, 100, 50)])
+def test_rounds_of_triples(p, n, k):
+    """Rounds far enough up to take triples, in runs and not: batched (a few
+    codes, so that some rounds have too few tasks for runs) and plain with
+    tables, against the kernel without tables."""
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2603_29942_amd import bz
+    G = np.random.default_rng([33, p, n, k]).integers(0, p, size=(k, n), dtype=np.uint8)
+    limit = 1 << 34
+    ref = bz.min_distance(p, G, no_termination=True, max_codewords=limit, pair_tables=-1)
+    assert max(st[0] for st in ref["stages"]) >= 6
+    got = [bz.min_distance(p, G, no_termination=True, max_codewords=limit, pair_tables=1)]
+    got += bz.min_distance_batch([(p, G)] * 2, no_termination=True, max_codewords=limit, device="cuda:0")
+    for r in got:
+        for key in ("status", "d", "m", "ranks", "stages", "codewords_total"):
+            assert r[key] == ref[key], (key, r[key], ref[key])

@@ -179,9 +179,9 @@ static void check_triples() {
                 RoundTable t, t0;
                 fill_round_table(p, k, 2, 768, 4500, binom, &t0);
                 t = t0;
-                take_triples(p, k, cap, binom, &t);
+                take_triples(p, k, cap, 768, binom, &t);
                 for (int g = TRIPLE_G; g <= k && round_combos(p, g) < (1ull << 32); g++) {
-                    u64 tasks = 0, combos = 0, cost;
+                    u64 tasks[2] = {0, 0}, combos = 0, cost;  // without and with runs
                     for (int q = g - 4; q <= k - 4; q++) {
                         const u64 bases = triple_bases(p, binom[q * 65 + g - 4], round_combos(p, g));
                         const uint32_t tiles = triple_tiles(p, k, q), nb = triple_blocks(tiles, cap3);
@@ -190,13 +190,20 @@ static void check_triples() {
                             const uint32_t d = triple_block_start(tiles, nb, b + 1) - triple_block_start(tiles, nb, b);
                             CHECK(d >= 1 && d <= cap3);
                         }
-                        tasks = sat_add(tasks, sat_mul(ceil64(bases), nb));
+                        for (int r = 0; r < 2; r++) {
+                            const uint32_t d = triple_digits(p, g, tiles, nb, bases, r != 0);
+                            CHECK(d <= (uint32_t)(g - 4) && d <= max_digits(p) && (r || d == 0));
+                            // a run is whole (the lanes' bases end together) and bounded
+                            CHECK(bases % run_len(p, d) == 0 || bases == ~0ull);
+                            CHECK(d == 0 || run_len(p, d) * ((tiles + nb - 1) / nb) <= RUN_TILES);
+                            tasks[r] = sat_add(tasks[r], triple_tasks(p, bases, nb, d));
+                        }
                         combos = sat_add(combos, sat_mul(bases, (u64)triple_units(p, k, q) * (u64)(p - 1)));
                     }
-                    CHECK(tasks == triple_round(p, k, g, cap, binom, &cost));
+                    for (int r = 0; r < 2; r++) CHECK(tasks[r] == triple_round(p, k, g, cap, r != 0, binom, &cost));
                     const u64 want = round_codewords(p, k, g, binom);
                     CHECK(combos == want || want == ~0ull || combos == ~0ull);
-                    if (t.vcap[g - 1] == TRIPLES) CHECK(t.tasks[g - 1] == tasks && g < t.cut_g);
+                    if (t.vcap[g - 1] & TRIPLES) CHECK(t.tasks[g - 1] == tasks[t.vcap[g - 1] & 1] && g < t.cut_g);
                     else CHECK(t.tasks[g - 1] == t0.tasks[g - 1] && t.vcap[g - 1] == t0.vcap[g - 1]);
                 }
                 for (int g = 1; g < TRIPLE_G; g++) CHECK(t.tasks[g - 1] == t0.tasks[g - 1]);
