@@ -460,7 +460,7 @@ int get_shape(DevCtx &c, int p, int n, int k, int W, int nsym, int grid, int sch
     if (it == c.shapes.end()) {
         RoundTable t;
         Shape sh;
-        const uint32_t ops = plain_sweep_ops(p), cap = sweep_cap_for(p, W, ops);
+        const uint32_t ops = sch != NO_TABLE ? table_sweep_ops(p) : plain_sweep_ops(p), cap = sweep_cap_for(p, W, ops);
         fill_round_table(p, k, W, (uint32_t)grid, ops, host_binom(), &t);
         sh.triples = sch != NO_TABLE && triples_worth(p, n, k, nsym, cap, TRIPLE_LAUNCH_TILES);
         if (sh.triples) take_triples(p, k, cap, (uint32_t)grid, host_binom(), &t);
@@ -644,7 +644,7 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     a.U0 = n - k + 1;
     a.max_codewords = max_cw;
     a.grid = (uint32_t)deal;
-    a.sweep_ops = plain_sweep_ops(p);
+    a.sweep_ops = tables ? table_sweep_ops(p) : plain_sweep_ops(p);
     a.timeout_ticks = timeout;
     a.rounds = shape->rounds;
     if (++c->spec_epoch == 0) c->spec_epoch = 1;
@@ -729,7 +729,7 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
             HIP_OK(hipMemcpyAsync(c->host_trace, c->cs->trace, sizeof(c->cs->trace), hipMemcpyDeviceToHost, s));
         HIP_OK(hipStreamSynchronize(s));
     }
-    st = finish(p, n, k, flags, max_cw, *c->host_res, out, plain_sweep_ops(p));
+    st = finish(p, n, k, flags, max_cw, *c->host_res, out, a.sweep_ops);
     if (o.timing) {
         HIP_OK(hipEventElapsedTime(&out->decompose_ms, c->ev[0], c->ev[1]));
         HIP_OK(hipEventElapsedTime(&out->enum_ms, c->ev[1], c->ev[2]));

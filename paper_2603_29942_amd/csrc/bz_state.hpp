@@ -245,8 +245,12 @@ BZ_HD int bound_c(int g, int k, int kj) {
 // Target (s, L) steps per lane in one task: about `ops` VALU operations, from
 // the per-step cost of the completions (F_3: two prefixes, add and subtract;
 // F_7: six prefixes, three rotations, add and subtract).
+// The default is the batches' and the server's, whose sweeps all go through
+// matrix operands: short tasks spend their time on the set-up (batches of 8,
+// 24, 64 and 256 codes: 4.3, 6.0, 11.0, 32.3 ms with 4500; 3.0, 4.9, 8.5, 23.3
+// with 18000; 3.2, 5.0, 8.3, 22.7 with 36000).
 #ifndef BZ_SWEEP_OPS
-#define BZ_SWEEP_OPS 4500
+#define BZ_SWEEP_OPS 18000
 #endif
 constexpr uint32_t DEFAULT_SWEEP_OPS = BZ_SWEEP_OPS;
 // Task size of the plain path: F_3 tasks of 3000 operations (the F_3 [72,36]
@@ -254,6 +258,11 @@ constexpr uint32_t DEFAULT_SWEEP_OPS = BZ_SWEEP_OPS;
 // 6000 (with the pair tables the F_7 [48,24] codes run 2% faster than with
 // 4500 or 9000, 18% slower with 3000).
 BZ_HD uint32_t plain_sweep_ops(int p) { return p == 3 ? 3000u : 6000u; }
+// With tables, twice that: a matrix sweep takes a quarter of the time and its
+// set-up the same (per call, 1x -> 2x -> 4x: [48,24] F_7 131 -> 126 -> 134 us,
+// [56,28] F_7 1555 -> 1475 -> 1524, [60,20] F_7 1166 -> 1024 -> 965, [89,29]
+// F_3 148 -> 136 -> 131, [80,40] F_3 119 -> 110 -> 150).
+BZ_HD uint32_t table_sweep_ops(int p) { return 2 * plain_sweep_ops(p); }
 BZ_HD uint32_t sweep_cap_for(int p, int W, uint32_t ops = DEFAULT_SWEEP_OPS) {
     const uint32_t per = (p == 3) ? 2u * (6u * (uint32_t)W + 1u) : 6u * (25u * (uint32_t)W + 3u);
     const uint32_t cap = (ops ? ops : DEFAULT_SWEEP_OPS) / per;
@@ -509,9 +518,7 @@ BZ_HD int sweep_last_rows(int s, int k, Group &&group) {
 // Rounds g <= SUBSET_G give each lane one g-subset of the rows (all its
 // coefficient vectors); larger rounds give it a base of g-2 rows and sweep the
 // last two rows (see StageDesc).  Round 4 takes bases of two rows: with the
-// pair tables its sweep needs no exact addition, and the four-row subsets
-// held the most registers of the batched kernel (119 VGPRs: four workgroups
-// per CU instead of five).
+// pair tables its sweep needs no exact addition.
 constexpr int SUBSET_G = 3;
 
 // Tasks of a stage with g <= SUBSET_G: 64 subsets per task.

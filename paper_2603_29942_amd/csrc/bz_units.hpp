@@ -110,10 +110,10 @@ BZ_HD u64 triple_bases(int p, u64 binom_q_g4, u64 M) { return sat_mul(binom_q_g4
 // Low coefficient digits of the bases that a lane runs through itself, as with
 // pairs (see digits_of): most bases meet few triples, and decoding one takes
 // as long as ten tiles, so that a task of short sweeps takes (p-1)^d bases per
-// lane, each one row away from the last, up to RUN_TILES tiles in all (about
-// 30 us).  [56, 28] over F_7: 3.05 -> 1.96 ms; 128 mixed requests, 34 -> 25 ms.
+// lane, each one row away from the last, up to RUN_TILES tiles in all (a
+// batch of 256: 25.7, 24.9 and 23.3 ms with 48, 96 and 192).  [56, 28] over F_7: 3.05 -> 1.96 ms; 128 mixed requests, 34 -> 25 ms.
 // runs: the round has enough tasks for it (runs_pay).
-constexpr uint32_t RUN_TILES = 96;
+constexpr uint32_t RUN_TILES = 192;
 BZ_HD uint32_t triple_digits(int p, int g, uint32_t tiles, uint32_t nb, u64 bases, bool runs) {
     const uint32_t fit = runs ? RUN_TILES / ((tiles + nb - 1) / nb) : 0;  // (every group has a tile)
     if (fit < (uint32_t)(p - 1)) return 0;
