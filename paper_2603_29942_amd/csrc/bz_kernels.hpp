@@ -2124,7 +2124,7 @@ __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2
                     bm = min(bm, red_min[w]);
                     bc += red_cnt[w];
                 }
-                if constexpr (TAB) {
+                if (TAB && sd.parts > REPORT_DIRECT) {
                     // to this workgroup's copy; its last report carries the sums on (see ReportState)
                     if (bm != BIG) atomicMin(&rep->min[rcopy][s], (int)(bm + woff));
                     const u64 rest = bc >> REPORT_COUNT_BITS << REPORT_COUNT_BITS;

@@ -701,7 +701,9 @@ BZ_HD int pool_stages(const StageDesc *st, int ns, uint32_t grid, u64 *tiles) {
 // reports to the stage directly: its workgroups leave a stage one by one, and
 // the step in between only made the checks later ([89, 29] over F_3: 645 us
 // for 2 codes directly, 705 us through copies).
+// So do the stages of few parts, whose queue is shorter than that step.
 // C divides the pool's slices, so a pool tile's copy follows from its number.
+constexpr uint32_t REPORT_DIRECT = 64;
 constexpr uint32_t REPORT_COPIES = 16;
 static_assert(POOL_SLICES % REPORT_COPIES == 0, "a slice of the pool has one copy");
 BZ_HD uint32_t report_copies(uint32_t grid) { return grid < POOL_SLICES ? 1u : REPORT_COPIES; }
