@@ -139,10 +139,10 @@ typedef struct {
                                  from a second workgroup that computed it in parallel, if it
                                  has finished (BZ_INFO_AHEAD).  Results never depend on it */
     int32_t pair_tables;      /* 0 (default): the decomposition builds each information set's
-                                 table of row-pair sums for F_7 codes, and for F_3 codes of
-                                 14 rows or more without histograms (smaller ones measured
-                                 no faster with it); 1: always; -1: never (BZ_INFO_PAIRS
-                                 tells which ran).  Results never depend on it;
+                                 table of row-pair sums for F_7 codes (with histograms: of 8
+                                 rows or more) and for F_3 codes of 14 rows or more without
+                                 histograms (the others measured no faster with it); 1:
+                                 always; -1: never (BZ_INFO_PAIRS tells which ran).  Results never depend on it;
                                  bz_min_distance_noalloc never builds tables */
 } bz_options;
 

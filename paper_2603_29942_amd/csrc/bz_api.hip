@@ -345,14 +345,18 @@ hipError_t launch_enum(int p, bool hist_mode, int sch, int W, int grid, CodeStat
     return hipGetLastError();
 }
 
-// Rows from which plain F_3 calls take pair tables by default.  Below, the run
-// ends after two or three rounds, which use none, and building them only costs
-// (rates 1/2 and 1/3, without -> with: k = 10 31.0 -> 32.2 us and 35.1 -> 37.3,
-// k = 12 31.9 -> 32.9 and 37.7 -> 40.6; k = 14 39.6 -> 38.0 and 53.3 -> 48.0,
-// k = 16 49.8 -> 42.3 and 55.4 -> 47.5, k = 30 59 -> 49 and 444 -> 183).
+// Whether plain calls take pair tables by default.  Small codes end after the
+// rounds that use none, and building them only costs.
+// F_3 (rates 1/2 and 1/3, without -> with): k = 10 31.0 -> 32.2 us and 35.1 ->
+// 37.3, k = 12 31.9 -> 32.9 and 37.7 -> 40.6; k = 14 39.6 -> 38.0 and 53.3 ->
+// 48.0, k = 16 49.8 -> 42.3 and 55.4 -> 47.5, k = 30 59 -> 49 and 444 -> 183.
 // Histograms count every sum in LDS either way, and measured slower with
-// tables ([45, 15]: 91 -> 116 us).
-constexpr int TABLES_K3 = 14;
+// tables over F_3 ([45, 15]: 91 -> 116 us); over F_7 [20, 4] 68.7 -> 75.6 us,
+// [20, 7] 73.5 -> 75.5, [26, 9] 171 -> 142.
+bool tables_by_default(int p, int k, bool hist) {
+    if (p == 3) return k >= 14 && !hist;
+    return k >= 8 || !hist;
+}
 
 // workgroups per compute unit a plain call's schedule is made for
 constexpr int DEAL_GROUPS = 5;
@@ -610,10 +614,7 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     if (W < 1) W = 1;
     // default: as many workgroups as fit (finer deals of the large stages)
     const int bpc = o.blocks_per_cu ? o.blocks_per_cu : 64;
-    // pair tables by default: always over F_7; over F_3 from TABLES_K3 rows
-    // without histograms
-    const bool tables =
-        o.pair_tables > 0 || (o.pair_tables == 0 && (p == 7 || (k >= TABLES_K3 && !o.histograms)));
+    const bool tables = o.pair_tables > 0 || (o.pair_tables == 0 && tables_by_default(p, k, o.histograms != 0));
     const int nsym = processed_columns(n, k, o.identity_skip != 0), sch = tables ? unit_scheme(p, nsym) : NO_TABLE;
     const int grid = enum_grid(p, o.histograms != 0, sch, W, c->cu, bpc);
     if (grid < 1) return BZ_ERR_DEVICE;

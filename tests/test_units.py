@@ -57,7 +57,8 @@ def test_sweep_at_layout_edges(p, nsym, k):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("p,n,k,hist,tables", [(3, 30, 13, False, False), (3, 30, 14, False, True),
-                                               (3, 30, 14, True, False), (7, 16, 5, True, True)])
+                                               (3, 30, 14, True, False), (7, 16, 5, False, True),
+                                               (7, 20, 7, True, False), (7, 20, 8, True, True)])
 def test_default_tables(p, n, k, hist, tables):
     """Which plain calls take tables by default, and that both ways agree."""
     import torch
