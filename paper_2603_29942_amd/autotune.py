@@ -17,8 +17,8 @@ these knobs (the tests check it); only time does.
 The table is JSON: {"sweep_ops": {"p,W": ops, ...}, "blocks_per_cu": b,
 "kernel_source_hash": h, ...}; it is used only while the kernel sources hash
 to h (a table taken on other kernels is ignored, and load_checked says so).
-The persistent batched kernel fits at most 5 workgroups per compute unit for
-W <= 2 (its registers); larger candidates are clamped to that by the library.
+The persistent batched kernel fits two workgroups per compute unit for W <= 2
+(its registers); larger candidates are clamped to that by the library.
 """
 import argparse
 import hashlib

@@ -839,7 +839,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
         if (!have_rt && lane <= k - 3) {
             lds.s_nb[lane] = qgroup_blocks(k, cap, lane);
             lds.s_dt[lane] = digits_by_steps(P, k, lane, budget);
-            lds.s_nb3[lane] = triple_blocks(triple_tiles(P, k, lane), triple_cap(P, cap));
+            if (triples) lds.s_nb3[lane] = triple_blocks(triple_tiles(P, k, lane), triple_cap(P, cap));
         }
         wave_sync();
         const bool counted = in && g > SUBSET_G && g <= last_g;
@@ -865,9 +865,13 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
                 const uint32_t nb = lds.s_nb[q];
                 tg = sat_add(tg, qgroup_tasks(P, bases, nb, 0));
                 tgv = sat_add(tgv, qgroup_tasks(P, bases, nb, digits_of(P, g, lds.s_dt[q], bases)));
-                if (try3) cost2 = sat_add(cost2, pair_group_cost(P, k, q, bases, nb));
             }
             if (try3) {
+                for (int q = q0; q <= k - 3; q++) {
+                    if (q < g - 3) continue;
+                    const u64 bases = sat_mul32(binom[q * 65 + (g - 3)], (uint32_t)combos);
+                    cost2 = sat_add(cost2, pair_group_cost(P, k, q, bases, lds.s_nb[q]));
+                }
                 for (int q = uni(TRIPLE_G - 4); q <= k - 4; q++) {
                     if (q < g - 4) continue;
                     const u64 bases = triple_bases(P, binom[q * 65 + (g - 4)], combos);
