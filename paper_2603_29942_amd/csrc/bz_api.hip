@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "bz_kernels.hpp"
+#include "bz_plan.hpp"
 #include "bz_mlp.hpp"
 
 using namespace bz;
@@ -372,6 +373,7 @@ int enum_grid(int p, bool hist, int sch, int W, int cu, int bpc) {
             return -1;
         m.store(nb, std::memory_order_relaxed);
     }
+    if (sch == NO_TABLE) nb = std::min(nb, prefix_groups(p, W));
     return cu * (bpc < nb ? bpc : nb);
 }
 
