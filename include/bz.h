@@ -96,6 +96,10 @@ typedef struct {
 /* bz_result.info: the rounds g >= 4 took the sums of their two highest rows
  * from the information sets' pair tables (see bz_options.pair_tables) */
 #define BZ_INFO_PAIRS 2
+/* bz_result.info: the schedule has rounds g >= 5 that take the sums of their
+ * three highest rows from a second table per set (a run that ends before those
+ * rounds has only built it) */
+#define BZ_INFO_TRIPLES 4
 
 typedef struct {
     int32_t check;            /* BZ_CHECK_STAGE (default) or BZ_CHECK_ROUND */

@@ -27,6 +27,7 @@ ENC_NATURAL, ENC_KAT = 0, 1
 
 INFO_AHEAD = 1
 INFO_PAIRS = 2
+INFO_TRIPLES = 4
 NOALLOC_SCRATCH_BYTES = 640 * 1024
 
 EXPORTS = ("bz_default_options", "bz_min_distance", "bz_min_distance_ex", "bz_status_str",

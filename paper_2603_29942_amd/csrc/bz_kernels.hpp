@@ -915,6 +915,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
         }
         wave_sync();
     }
+    uint32_t vcaps = 0;  // of the lane's stages
     {
         const uint32_t cap = sweep_cap_for(P, W, args.sweep_ops);
         for (int s = lane; s < ns; s += 64) {
@@ -933,6 +934,7 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
             d.parts = (uint32_t)(d.tiles < (u64)args.grid ? d.tiles : (u64)args.grid);
             d.sweep_cap = cap;
             d.vcap = lds.s_vcap[g - 1];
+            vcaps |= d.vcap;
             d.pad = 0;
             const u64 off = deal_offset(m, lds.s_tbefore[g - 1], j, d.tiles);
             d.nowait = off < (u64)args.grid;
@@ -958,11 +960,13 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
         cs->trace[1][1] = 0;
     }
     for (int j = lane; j < m; j += 64) res.ranks[j] = sranks[j];
+    const bool any_triples = __any((vcaps & TRIPLES) != 0);
     if (lane == 0) {
         res.status = status;
         res.m = m;
         res.W = W;
-        res.info = (handed ? BZ_INFO_AHEAD : 0) | (pairs != nullptr ? BZ_INFO_PAIRS : 0);
+        res.info = (handed ? BZ_INFO_AHEAD : 0) | (pairs != nullptr ? BZ_INFO_PAIRS : 0) |
+                   (any_triples ? BZ_INFO_TRIPLES : 0);
         res.t_end = 0;
         res.ctl = ctl_make(0, -1, args.U0);
         res.n_table = ns;

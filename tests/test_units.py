@@ -92,3 +92,48 @@ def test_rounds_of_triples(p, n, k):
     for r in got:
         for key in ("status", "d", "m", "ranks", "stages", "codewords_total"):
             assert r[key] == ref[key], (key, r[key], ref[key])
+
+
+# every layout with a table of triples, at the first or last column counts of
+# the layout where a code that takes them has one: (p, n, k, identity skip)
+TRIPLE_SHAPES = [(7, 43, 22, True), (7, 54, 22, True), (7, 55, 22, True), (7, 63, 21, True), (7, 59, 15, True),
+                 (7, 78, 13, True), (7, 109, 12, True), (7, 59, 15, False), (7, 78, 13, False),
+                 (3, 67, 35, True), (3, 80, 28, True), (3, 100, 30, True), (3, 116, 19, True), (3, 116, 19, False)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,n,k,skip", TRIPLE_SHAPES)
+def test_triples_on_every_layout(p, n, k, skip):
+    """Rounds of triples ran (they are in the schedule, and without the bound
+    test every stage of it runs), plain and batched: the kernel without tables
+    gives the same stages."""
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2603_29942_amd import bz
+    G = np.random.default_rng([34, p, n, k]).integers(0, p, size=(k, n), dtype=np.uint8)
+    kw = {"no_termination": True, "identity_skip": skip, "max_codewords": 1 << 31}
+    ref = bz.min_distance(p, G, pair_tables=-1, **kw)
+    assert not ref["info"] & bz.INFO_TRIPLES
+    got = [bz.min_distance(p, G, pair_tables=1, **kw)]
+    got += bz.min_distance_batch([(p, G)] * 2, device="cuda:0", **kw)
+    for r in got:
+        assert r["info"] & bz.INFO_TRIPLES
+        for key in ("status", "d", "m", "ranks", "stages", "codewords_total"):
+            assert r[key] == ref[key], (key, r[key], ref[key])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,n,k,skip", [(7, 43, 22, True), (7, 59, 15, True), (7, 78, 13, True), (7, 78, 13, False),
+                                        (3, 67, 35, True), (3, 116, 19, True)])
+def test_histograms_of_triples(p, n, k, skip):
+    """A spectrum whose rounds take triples (units outside a task's range are
+    masked there too) equals the kernel without tables', bin for bin."""
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2603_29942_amd import bz
+    G = np.random.default_rng([35, p, n, k]).integers(0, p, size=(k, n), dtype=np.uint8)
+    kw = {"no_termination": True, "identity_skip": skip, "max_codewords": 1 << 31, "histograms": True}
+    ref = bz.min_distance(p, G, pair_tables=-1, **kw)
+    got = bz.min_distance(p, G, pair_tables=1, **kw)
+    assert got["info"] & bz.INFO_TRIPLES
+    assert got["stages"] == ref["stages"] and np.array_equal(got["hist"], ref["hist"])
