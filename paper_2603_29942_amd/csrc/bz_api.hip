@@ -72,7 +72,7 @@ struct DevCtx {
     CodeResult *b_host_res = nullptr;
     BatchState *b_host_state = nullptr;
     // what plain calls of one shape share, built once on first use (get_shape)
-    std::map<std::array<int, 7>, Shape> shapes;  // key: p, n, k, W, columns, grid, table layout
+    std::map<std::array<int, 8>, Shape> shapes;  // key: p, n, k, W, columns, grid, table layout, expected rounds
     // the second information set computed ahead by a second workgroup of the
     // decomposition launch, and the value its flag takes in this call
     SpecBuf *spec = nullptr;
@@ -109,73 +109,6 @@ const u64 *host_binom() {
         if ((expr) != hipSuccess) return BZ_ERR_DEVICE; \
     } while (0)
 
-// the columns processed per combination
-int processed_columns(int n, int k, bool skip) { return skip ? n - k : n; }
-
-// 16-byte words between the tables of two sets of a code: the pair table and,
-// with triples, the triple table behind it
-u64 set_table_size(int p, int k, int nsym, bool triples) {
-    return unit_table_size(p, k, nsym) + (triples ? triple_table_size(p, k, nsym) : 0);
-}
-// of every set a code can produce (slots 0 .. pair_sets - 1), plus, on the
-// plain path, the slot pair_sets that the workgroup computing the second set
-// ahead builds its table in
-u64 code_table_size(int p, int n, int k, int nsym, bool triples, bool ahead_slot) {
-    return (u64)(pair_sets(n, k) + (ahead_slot ? 1 : 0)) * set_table_size(p, k, nsym, triples);
-}
-// Triples only where a set's table is at most an XCD's L2 (4 MB): every
-// wavefront streams it again for each of its tasks.
-bool triples_fit(int p, int k, int nsym) { return k >= TRIPLE_G && triple_table_size(p, k, nsym) * 16 <= (4u << 20); }
-
-// the largest code_table_size of any code with n <= max_n (with the identity
-// skip when skip is 1, without it when 0, either when -1)
-u64 max_table_size(int max_n, int skip, bool triples, bool ahead_slot) {
-    u64 best = 0;
-    for (int p : {3, 7})
-        for (int n = 1; n <= max_n; n++)
-            for (int k = 1; k <= n && k <= BZ_MAX_K; k++)
-                for (int sk = 0; sk < 2; sk++) {
-                    const int nsym = processed_columns(n, k, sk != 0);
-                    if (skip < 0 || skip == sk)
-                        best = std::max(best, code_table_size(p, n, k, nsym, triples && triples_fit(p, k, nsym), ahead_slot));
-                }
-    return best;
-}
-
-// The last round that a random [n, k] code is expected to run: its minimum
-// weight d is about the least with p^(n-k) words within distance d, and round
-// g raises the lower bound to about (g + 1) n / k.  Only used to decide
-// whether triple tables are worth building.
-int expected_rounds(int p, int n, int k) {
-    const double goal = (n - k) * std::log((double)p) + std::log((double)(p - 1));
-    double lc = 0, sum = 0;  // ln of C(n, d) (p-1)^d, and of their sum
-    int d = 0;
-    while (d < n && (d == 0 || sum < goal)) {
-        d++;
-        lc += std::log((double)(n - d + 1) / d * (p - 1));
-        sum = d == 1 ? lc : std::max(sum, lc) + std::log1p(std::exp(-std::fabs(sum - lc)));
-    }
-    d = std::min(d, n - k + 1);
-    const int g = (d * k + n - 1) / n - 1;
-    return std::min(std::max(g, 1), k);
-}
-// Triple tables pay when the expected rounds save more tiles than the tables
-// take to build (a unit costs about 200 VALU instructions, a tile of 64 bases
-// 100: one tile per 32 units) and, on the plain path, than their launch takes:
-// about 8 us, 40000 tiles.
-bool triples_worth(int p, int n, int k, int nsym, uint32_t cap, u64 launch_tiles) {
-    if (!triples_fit(p, k, nsym)) return false;
-    const int sets = n / k + (n % k != 0), gm = expected_rounds(p, n, k);
-    u64 build = sat_mul(triple_tiles(p, k, -1), (u64)sets) + launch_tiles, saved = 0;
-    for (int g = TRIPLE_G; g <= gm && round_combos(p, g) < (1ull << 32); g++) {
-        u64 c3;
-        triple_round(p, k, g, cap, false, host_binom(), &c3);
-        const u64 c2 = pair_round_cost(p, k, g, cap, host_binom());
-        if (c2 > c3) saved = sat_add(saved, sat_mul(c2 - c3, (u64)sets));
-    }
-    return saved > build;
-}
-constexpr u64 TRIPLE_LAUNCH_TILES = 40000;
 // workgroups per code of a triple-table launch: about eight per compute unit in all
 int triple_blocks_per_code(int ncodes, int cu) { return std::max(1, std::min(8 * cu / std::max(ncodes, 1), 2 * cu)); }
 // the most 16-byte words a batch's or a server's tables may take with triples
@@ -459,16 +392,16 @@ void launch_op(int op, int blocks, hipStream_t s, int nvec, int words, const u32
     }
 }
 
-// sch: the table layout of the launch, or NO_TABLE
-int get_shape(DevCtx &c, int p, int n, int k, int W, int nsym, int grid, int sch, const Shape **out) {
-    const std::array<int, 7> key = {p, n, k, W, nsym, grid, sch};
+// sch: the table layout of the launch, or NO_TABLE; last: see expected_rounds
+int get_shape(DevCtx &c, int p, int n, int k, int W, int nsym, int grid, int sch, int last, const Shape **out) {
+    const std::array<int, 8> key = {p, n, k, W, nsym, grid, sch, last};
     auto it = c.shapes.find(key);
     if (it == c.shapes.end()) {
         RoundTable t;
         Shape sh;
         const uint32_t ops = sch != NO_TABLE ? table_sweep_ops(p) : plain_sweep_ops(p), cap = sweep_cap_for(p, W, ops);
         fill_round_table(p, k, W, (uint32_t)grid, ops, host_binom(), &t);
-        sh.triples = sch != NO_TABLE && triples_worth(p, n, k, nsym, cap, TRIPLE_LAUNCH_TILES);
+        sh.triples = sch != NO_TABLE && triples_worth(p, k, nsym, expected_sets(n, k), last, cap, TRIPLE_LAUNCH_TILES, host_binom());
         if (sh.triples) take_triples(p, k, cap, (uint32_t)grid, host_binom(), &t);
         HIP_OK(hipMalloc(&sh.rounds, sizeof(RoundTable)));
         if (hipMemcpy(sh.rounds, &t, sizeof(RoundTable), hipMemcpyHostToDevice) != hipSuccess) {
@@ -628,7 +561,8 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     // 58 us for five workgroups of the earlier kernel)
     const int deal = tables ? std::max(grid, c->cu * std::min(bpc, DEAL_GROUPS)) : grid;
     const Shape *shape = nullptr;
-    st = get_shape(*c, p, n, k, W, nsym, deal, sch, &shape);
+    const int last = expected_rounds(p, n, k, o.no_termination != 0, max_cw, host_binom());
+    st = get_shape(*c, p, n, k, W, nsym, deal, sch, last, &shape);
     if (st != BZ_OK) return st;
 
     const uint8_t *Gd = G;
@@ -810,7 +744,9 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
         b.sweep_ops = cd.sweep_ops > 0 ? (uint32_t)cd.sweep_ops : DEFAULT_SWEEP_OPS;
         const int nsym = processed_columns(cd.n, cd.k, o.identity_skip != 0);
         b.scheme = unit_scheme(cd.p, nsym);
-        bool triples = triples_worth(cd.p, cd.n, cd.k, nsym, sweep_cap_for(cd.p, b.W, b.sweep_ops), 0);
+        const int last = expected_rounds(cd.p, cd.n, cd.k, o.no_termination != 0, max_cw, host_binom());
+        bool triples = triples_worth(cd.p, cd.k, nsym, expected_sets(cd.n, cd.k), last,
+                                     sweep_cap_for(cd.p, b.W, b.sweep_ops), 0, host_binom());
         triples = triples && table_words + code_table_size(cd.p, cd.n, cd.k, nsym, true, false) <= TRIPLE_BUDGET;
         any_triples |= triples;
         b.triple_off = triples ? (uint32_t)unit_table_size(cd.p, cd.k, nsym) : 0u;
@@ -1367,8 +1303,9 @@ int server_round(bz_server *s) {
         b.sweep_ops = DEFAULT_SWEEP_OPS;
         const int nsym = processed_columns(r.n, r.k, s->o.identity_skip != 0);
         b.scheme = unit_scheme(r.p, nsym);
-        const bool triples =
-            s->triples && triples_worth(r.p, r.n, r.k, nsym, sweep_cap_for(r.p, b.W, DEFAULT_SWEEP_OPS), 0);
+        const bool triples = s->triples && triples_worth(r.p, r.k, nsym, expected_sets(r.n, r.k),
+                                                         expected_rounds(r.p, r.n, r.k, false, s->max_cw, host_binom()),
+                                                         sweep_cap_for(r.p, b.W, DEFAULT_SWEEP_OPS), 0, host_binom());
         any_triples |= triples;
         b.triple_off = triples ? (uint32_t)unit_table_size(r.p, r.k, nsym) : 0u;
         b.pair_stride = (uint32_t)set_table_size(r.p, r.k, nsym, triples);

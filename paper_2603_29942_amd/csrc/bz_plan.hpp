@@ -1,6 +1,9 @@
 // bz_plan.hpp -- what the host decides before a launch, from shapes and options
 // alone (no device calls, so that it is checked on the CPU).
 #pragma once
+#include <algorithm>
+#include <atomic>
+#include <cmath>
 #include <stdint.h>
 
 #include "bz_units.hpp"
@@ -13,5 +16,96 @@ namespace bz {
 // without tables, [48, 12] 66.8 us with three, 89.0 with four; [66, 11] 81.4
 // and 92.0; [108, 9], four words, 131.1 with two, 136.6 with three).
 inline int prefix_groups(int p, int W) { return p == 3 ? (W <= 2 ? 5 : 4) : W == 1 ? 4 : W == 2 ? 3 : 2; }
+
+// the columns processed per combination
+inline int processed_columns(int n, int k, bool skip) { return skip ? n - k : n; }
+
+// 16-byte words between the tables of two sets of a code: the pair table and,
+// with triples, the triple table behind it
+inline u64 set_table_size(int p, int k, int nsym, bool triples) {
+    return unit_table_size(p, k, nsym) + (triples ? triple_table_size(p, k, nsym) : 0);
+}
+// of every set a code can produce (slots 0 .. pair_sets - 1), plus, on the
+// plain path, the slot pair_sets that the workgroup computing the second set
+// ahead builds its table in
+inline u64 code_table_size(int p, int n, int k, int nsym, bool triples, bool ahead_slot) {
+    return (u64)(pair_sets(n, k) + (ahead_slot ? 1 : 0)) * set_table_size(p, k, nsym, triples);
+}
+// Triples only where a set's table is at most an XCD's L2 (4 MB): every
+// wavefront streams it again for each of its tasks.
+inline bool triples_fit(int p, int k, int nsym) { return k >= TRIPLE_G && triple_table_size(p, k, nsym) * 16 <= (4u << 20); }
+
+// the largest code_table_size of any code with n <= max_n (with the identity
+// skip when skip is 1, without it when 0, either when -1)
+inline u64 max_table_size(int max_n, int skip, bool triples, bool ahead_slot) {
+    u64 best = 0;
+    for (int p : {3, 7})
+        for (int n = 1; n <= max_n; n++)
+            for (int k = 1; k <= n && k <= BZ_MAX_K; k++)
+                for (int sk = 0; sk < 2; sk++) {
+                    const int nsym = processed_columns(n, k, sk != 0);
+                    if (skip < 0 || skip == sk)
+                        best = std::max(best, code_table_size(p, n, k, nsym, triples && triples_fit(p, k, nsym), ahead_slot));
+                }
+    return best;
+}
+
+// The minimum weight that a random [n, k] code is expected to have: about the
+// least d with p^(n-k) words within distance d.  Looked up by the shape after
+// the first call for it.
+inline int expected_distance(int p, int n, int k) {
+    static std::atomic<int16_t> known[2][BZ_MAX_N + 1][BZ_MAX_K + 1];  // 0: not computed yet
+    std::atomic<int16_t> &memo = known[p == 7][n][k];
+    if (const int d = memo.load(std::memory_order_relaxed)) return d;
+    const double goal = (n - k) * std::log((double)p) + std::log((double)(p - 1));
+    double lc = 0, sum = 0;  // ln of C(n, d) (p-1)^d, and of their sum
+    int d = 0;
+    while (d < n && (d == 0 || sum < goal)) {
+        d++;
+        lc += std::log((double)(n - d + 1) / d * (p - 1));
+        sum = d == 1 ? lc : std::max(sum, lc) + std::log1p(std::exp(-std::fabs(sum - lc)));
+    }
+    d = std::min(d, n - k + 1);
+    memo.store((int16_t)d, std::memory_order_relaxed);
+    return d;
+}
+// information sets of a random code
+inline int expected_sets(int n, int k) { return n / k + (n % k != 0); }
+
+// The last round that a call on a random [n, k] code is expected to run: the
+// one whose bound reaches the expected distance (round g raises it to about
+// (g + 1) n / k), or every round without termination, and none past the work
+// limit, where the schedule ends.  Only used to decide which tables are worth
+// building.
+inline int expected_rounds(int p, int n, int k, bool no_term, u64 max_codewords, const u64 *binom) {
+    int last = k;
+    if (!no_term) last = std::min(std::max((expected_distance(p, n, k) * k + n - 1) / n - 1, 1), k);
+    const u64 sets = (u64)expected_sets(n, k);
+    u64 cum = 0;
+    for (int g = 1; g <= last; g++) {
+        const u64 cw = round_codewords(p, k, g, binom);
+        if (sat_add(cum, cw) > max_codewords) return g - 1;  // not even its first stage
+        cum = sat_add(cum, sat_mul(cw, sets));
+    }
+    return last;
+}
+// Triple tables pay when the rounds up to `last` save more tiles than the
+// tables take to build (a unit costs about 200 VALU instructions, a tile of 64
+// bases 100: one tile per 32 units) and, on the plain path, than their launch
+// takes: about 8 us, 40000 tiles.
+// (batches of 512 with a work limit of 10^6, which ends them in round 4: 750 us
+// without triples, 1324 us with triples chosen as if they ran on)
+inline bool triples_worth(int p, int k, int nsym, int sets, int last, uint32_t cap, u64 launch_tiles, const u64 *binom) {
+    if (last < TRIPLE_G || !triples_fit(p, k, nsym)) return false;
+    u64 build = sat_mul(triple_tiles(p, k, -1), (u64)sets) + launch_tiles, saved = 0;
+    for (int g = TRIPLE_G; g <= last && round_combos(p, g) < (1ull << 32); g++) {
+        u64 c3;
+        triple_round(p, k, g, cap, false, binom, &c3);
+        const u64 c2 = pair_round_cost(p, k, g, cap, binom);
+        if (c2 > c3) saved = sat_add(saved, sat_mul(c2 - c3, (u64)sets));
+    }
+    return saved > build;
+}
+constexpr u64 TRIPLE_LAUNCH_TILES = 40000;
 
 }  // namespace bz
