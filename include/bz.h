@@ -143,11 +143,12 @@ typedef struct {
                                  from a second workgroup that computed it in parallel, if it
                                  has finished (BZ_INFO_AHEAD).  Results never depend on it */
     int32_t pair_tables;      /* 0 (default): the decomposition builds each information set's
-                                 table of row-pair sums for F_7 codes (with histograms: of 8
-                                 rows or more) and for F_3 codes of 14 rows or more without
-                                 histograms (the others measured no faster with it); 1:
-                                 always; -1: never (BZ_INFO_PAIRS tells which ran).  Results never depend on it;
-                                 bz_min_distance_noalloc never builds tables */
+                                 table of row-pair sums where the rounds g >= 4 make up for
+                                 it, by the shape, the work limit and the options (F_3: from
+                                 14 rows on, without histograms; F_7: two sets of 10 rows or
+                                 more, longer runs and spectra); 1: always; -1: never
+                                 (BZ_INFO_PAIRS tells which ran).  Results never depend on
+                                 it; bz_min_distance_noalloc never builds tables */
 } bz_options;
 
 /* Fill *o with the defaults above. */

@@ -72,7 +72,7 @@ struct DevCtx {
     CodeResult *b_host_res = nullptr;
     BatchState *b_host_state = nullptr;
     // what plain calls of one shape share, built once on first use (get_shape)
-    std::map<std::array<int, 8>, Shape> shapes;  // key: p, n, k, W, columns, grid, table layout, expected rounds
+    std::map<std::array<int, 9>, Shape> shapes;  // key: p, n, k, W, columns, grid, table layout, expected rounds, launch
     // the second information set computed ahead by a second workgroup of the
     // decomposition launch, and the value its flag takes in this call
     SpecBuf *spec = nullptr;
@@ -279,19 +279,6 @@ hipError_t launch_enum(int p, bool hist_mode, int sch, int W, int grid, CodeStat
     return hipGetLastError();
 }
 
-// Whether plain calls take pair tables by default.  Small codes end after the
-// rounds that use none, and building them only costs.
-// F_3 (rates 1/2 and 1/3, without -> with): k = 10 31.0 -> 32.2 us and 35.1 ->
-// 37.3, k = 12 31.9 -> 32.9 and 37.7 -> 40.6; k = 14 39.6 -> 38.0 and 53.3 ->
-// 48.0, k = 16 49.8 -> 42.3 and 55.4 -> 47.5, k = 30 59 -> 49 and 444 -> 183.
-// Histograms count every sum in LDS either way, and measured slower with
-// tables over F_3 ([45, 15]: 91 -> 116 us); over F_7 [20, 4] 68.7 -> 75.6 us,
-// [20, 7] 73.5 -> 75.5, [26, 9] 171 -> 142.
-bool tables_by_default(int p, int k, bool hist) {
-    if (p == 3) return k >= 14 && !hist;
-    return k >= 8 || !hist;
-}
-
 // workgroups per compute unit a plain call's schedule is made for
 constexpr int DEAL_GROUPS = 5;
 
@@ -393,15 +380,16 @@ void launch_op(int op, int blocks, hipStream_t s, int nvec, int words, const u32
 }
 
 // sch: the table layout of the launch, or NO_TABLE; last: see expected_rounds
-int get_shape(DevCtx &c, int p, int n, int k, int W, int nsym, int grid, int sch, int last, const Shape **out) {
-    const std::array<int, 8> key = {p, n, k, W, nsym, grid, sch, last};
+int get_shape(DevCtx &c, int p, int n, int k, int W, int nsym, int grid, int sch, int last,
+              u64 launch_tiles, const Shape **out) {
+    const std::array<int, 9> key = {p, n, k, W, nsym, grid, sch, last, (int)launch_tiles};
     auto it = c.shapes.find(key);
     if (it == c.shapes.end()) {
         RoundTable t;
         Shape sh;
         const uint32_t ops = sch != NO_TABLE ? table_sweep_ops(p) : plain_sweep_ops(p), cap = sweep_cap_for(p, W, ops);
         fill_round_table(p, k, W, (uint32_t)grid, ops, host_binom(), &t);
-        sh.triples = sch != NO_TABLE && triples_worth(p, k, nsym, expected_sets(n, k), last, cap, TRIPLE_LAUNCH_TILES, host_binom());
+        sh.triples = sch != NO_TABLE && triples_worth(p, k, nsym, expected_sets(n, k), last, cap, launch_tiles, host_binom());
         if (sh.triples) take_triples(p, k, cap, (uint32_t)grid, host_binom(), &t);
         HIP_OK(hipMalloc(&sh.rounds, sizeof(RoundTable)));
         if (hipMemcpy(sh.rounds, &t, sizeof(RoundTable), hipMemcpyHostToDevice) != hipSuccess) {
@@ -549,7 +537,8 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     if (W < 1) W = 1;
     // default: as many workgroups as fit (finer deals of the large stages)
     const int bpc = o.blocks_per_cu ? o.blocks_per_cu : 64;
-    const bool tables = o.pair_tables > 0 || (o.pair_tables == 0 && tables_by_default(p, k, o.histograms != 0));
+    const bool tables = o.pair_tables > 0 || (o.pair_tables == 0 && tables_by_default(p, n, k, W, o.histograms != 0, o.no_termination != 0,
+                                                                                     o.check == BZ_CHECK_ROUND, max_cw, host_binom()));
     const int nsym = processed_columns(n, k, o.identity_skip != 0), sch = tables ? unit_scheme(p, nsym) : NO_TABLE;
     const int grid = enum_grid(p, o.histograms != 0, sch, W, c->cu, bpc);
     if (grid < 1) return BZ_ERR_DEVICE;
@@ -562,7 +551,7 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     const int deal = tables ? std::max(grid, c->cu * std::min(bpc, DEAL_GROUPS)) : grid;
     const Shape *shape = nullptr;
     const int last = expected_rounds(p, n, k, o.no_termination != 0, max_cw, host_binom());
-    st = get_shape(*c, p, n, k, W, nsym, deal, sch, last, &shape);
+    st = get_shape(*c, p, n, k, W, nsym, deal, sch, last, triple_launch_tiles(p, n, k, o.no_termination != 0, last), &shape);
     if (st != BZ_OK) return st;
 
     const uint8_t *Gd = G;

@@ -83,16 +83,69 @@ inline int expected_rounds(int p, int n, int k, bool no_term, u64 max_codewords,
     const u64 sets = (u64)expected_sets(n, k);
     u64 cum = 0;
     for (int g = 1; g <= last; g++) {
+        if (max_codewords == ~0ull) break;
         const u64 cw = round_codewords(p, k, g, binom);
         if (sat_add(cum, cw) > max_codewords) return g - 1;  // not even its first stage
         cum = sat_add(cum, sat_mul(cw, sets));
     }
     return last;
 }
+// Combinations of the rounds g >= 4 (those that tables serve) that a call on a
+// random [n, k] code is expected to evaluate within its work limit: stage by
+// stage until L_{g,j}, tested after every stage or every round, reaches the
+// expected distance.
+inline u64 expected_work(int p, int n, int k, bool by_round, u64 max_codewords, const u64 *binom) {
+    const int d = expected_distance(p, n, k), full = n / k, rest = n % k;
+    u64 cum = 0, work = 0;
+    for (int g = 1; g <= k; g++) {
+        const u64 cw = round_codewords(p, k, g, binom);
+        const int sets = expected_sets(n, k);
+        for (int j = 1; j <= sets; j++) {
+            cum = sat_add(cum, cw);
+            if (cum > max_codewords) return work;
+            if (g > SUBSET_G) work = sat_add(work, cw);
+            const int in = std::min(j, full);
+            const int L = full * g + in + (rest ? std::max(0, (j > full ? g + 1 : g) - (k - rest)) : 0);
+            if (L >= d && (j == sets || !by_round)) return work;
+        }
+    }
+    return work;
+}
+// Whether plain calls take pair tables by default: where the rounds from 4 on
+// make up for building one per set.  A run that ends before those rounds has
+// them among the stages that start at once, so two or three sets of enough rows
+// take them whatever the expected work.  Without -> with, in us:
+// F_3  k = 12 30.2 -> 30.2 and 35.8 -> 37.0 (two and three sets), 13 40.3 ->
+//      42.4; 14 41.1 -> 38.2 and 49.2 -> 45.6, 16 49.9 -> 40.4; of more words
+//      by the work: [84, 14] 68.9 -> 76.5, [85, 19] 77.3 -> 79.7 (10^7),
+//      [90, 20] 115 -> 89.  With histograms without (they count every sum in
+//      LDS either way: [45, 15] ending early 91 -> 116).
+// F_7  two sets: k = 9 40.3 -> 46.6, 10 48.5 -> 43.5, 12 49.1 -> 46.1; three:
+//      11 and 12 the same, 13 76.7 -> 68.3; else by the work: [72, 12] 98.8 ->
+//      124 and [45, 13] 69.5 -> 82.0 (3.5 10^7), [66, 12] 143 -> 126 (5 10^7);
+//      of three words and more [110, 10] 155 -> 189 (1.2 10^7), [128, 10]
+//      264 -> 224 (2 10^7), [93, 11] 253 -> 155.
+//      Up to eight rows in up to four sets: within 3 us of 30 to 45 either way,
+//      and with histograms the same (k = 8); the tables of old stay there.
+// Spectra (no termination), F_7: [24, 8] 46.9 -> 49.7, [18, 9] 56.2 -> 62.2,
+//      [27, 9] 96.6 -> 87.5, [36, 9] 130 -> 73, [20, 10] 175 -> 74; F_3:
+//      [28, 14] 122 -> 130, [42, 14] 192 -> 72, [30, 15] 209 -> 135.
+inline bool tables_by_default(int p, int n, int k, int W, bool hist, bool no_term, bool by_round, u64 max_codewords,
+                              const u64 *binom) {
+    if (p == 3 && (hist || k < 14)) return false;
+    // the schedule has a round 4 at all
+    if (expected_rounds(p, n, k, true, max_codewords, binom) <= SUBSET_G) return false;
+    const int sets = expected_sets(n, k);
+    if (no_term) return k > (p == 3 ? 14 : 9) || (k == (p == 3 ? 14 : 9) && sets >= 3);
+    const u64 work = expected_work(p, n, k, by_round, max_codewords, binom);
+    if (p == 3) return W <= 2 || work >= 10000000;
+    if (k <= 8) return sets <= 4 && (k == 8 || !hist);
+    return (k >= 10 && sets <= 2) || (k >= 13 && sets == 3) || work >= (W <= 2 ? 40000000u : 18000000u);
+}
 // Triple tables pay when the rounds up to `last` save more tiles than the
 // tables take to build (a unit costs about 200 VALU instructions, a tile of 64
 // bases 100: one tile per 32 units) and, on the plain path, than their launch
-// takes: about 8 us, 40000 tiles.
+// takes.
 // (batches of 512 with a work limit of 10^6, which ends them in round 4: 750 us
 // without triples, 1324 us with triples chosen as if they ran on)
 inline bool triples_worth(int p, int k, int nsym, int sets, int last, uint32_t cap, u64 launch_tiles, const u64 *binom) {
@@ -106,6 +159,11 @@ inline bool triples_worth(int p, int k, int nsym, int sets, int last, uint32_t c
     }
     return saved > build;
 }
-constexpr u64 TRIPLE_LAUNCH_TILES = 40000;
+// The launch in tiles, 8 us of them; fewer for a run that its limit ends, which
+// has no stage beyond that starts at once and is thrown away (limits of 2 10^8:
+// [84, 14] over F_7 206 -> 155 us, [120, 30] over F_3 116 -> 101).
+inline u64 triple_launch_tiles(int p, int n, int k, bool no_term, int last) {
+    return last < expected_rounds(p, n, k, no_term, ~0ull, nullptr) ? 15000 : 40000;
+}
 
 }  // namespace bz

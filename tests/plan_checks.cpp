@@ -24,8 +24,9 @@ static u64 BINOM[65 * 65];
 constexpr u64 NO_LIMIT = 1ull << 44;
 static bool plain_triples(int p, int n, int k, bool no_term, u64 limit) {
     const int W = (n - k + 31) / 32;
-    return triples_worth(p, k, n - k, expected_sets(n, k), expected_rounds(p, n, k, no_term, limit, BINOM),
-                         sweep_cap_for(p, W, table_sweep_ops(p)), TRIPLE_LAUNCH_TILES, BINOM);
+    const int last = expected_rounds(p, n, k, no_term, limit, BINOM);
+    return triples_worth(p, k, n - k, expected_sets(n, k), last, sweep_cap_for(p, W, table_sweep_ops(p)),
+                         triple_launch_tiles(p, n, k, no_term, last), BINOM);
 }
 
 // Rounds that a call can run at all: none past its work limit, all of them
@@ -58,11 +59,56 @@ static void check_rounds() {
     CHECK(!plain_triples(7, 40, 14, false, NO_LIMIT) && plain_triples(7, 40, 14, true, NO_LIMIT));
 }
 
+static bool tables(int p, int n, int k, bool hist = false, bool no_term = false, u64 limit = NO_LIMIT) {
+    return tables_by_default(p, n, k, (n - k + 31) / 32 < 1 ? 1 : (n - k + 31) / 32, hist, no_term, false, limit, BINOM);
+}
+
+// The expected work against the stages written out, and the shapes on both
+// sides of each line of tables_by_default.
+static void check_tables() {
+    for (int p : {3, 7})
+        for (int n = 2; n <= BZ_MAX_N; n += 3)
+            for (int k = 1; k < n && k <= BZ_MAX_K; k++) {
+                const int m = expected_sets(n, k), d = expected_distance(p, n, k);
+                for (int t = 0; t < 6; t++) {
+                    const u64 limit = t % 3 == 0 ? 1000 : t % 3 == 1 ? 1000000 : NO_LIMIT;
+                    const bool by_round = t >= 3;
+                    u64 cum = 0, want = 0;
+                    bool end = false;
+                    for (int g = 1; g <= k && !end; g++)
+                        for (int j = 1; j <= m && !end; j++) {
+                            const u64 cw = round_codewords(p, k, g, BINOM);
+                            if (sat_add(cum, cw) > limit) {
+                                end = true;
+                                break;
+                            }
+                            cum += cw;
+                            if (g >= 4) want += cw;
+                            int L = 0;
+                            for (int i = 1; i <= m; i++) L += bound_c(i <= j ? g : g - 1, k, i <= n / k ? k : n % k);
+                            end = L >= d && (j == m || !by_round);
+                        }
+                    CHECK(expected_work(p, n, k, by_round, limit, BINOM) == want);
+                    // no round 4 within the limit: nothing to build tables for
+                    if (expected_rounds(p, n, k, true, limit, BINOM) < 4) CHECK(!tables(p, n, k, false, false, limit));
+                }
+            }
+    CHECK(!tables(3, 26, 13) && tables(3, 28, 14) && !tables(3, 84, 14) && tables(3, 90, 20) && !tables(3, 28, 14, true));
+    CHECK(!tables(7, 18, 9) && tables(7, 20, 10) && !tables(7, 36, 12) && tables(7, 39, 13) && !tables(7, 45, 13) &&
+          tables(7, 66, 12) && !tables(7, 72, 12) && !tables(7, 110, 10) && tables(7, 93, 11) && !tables(7, 24, 3) &&
+          tables(7, 16, 5) && !tables(7, 96, 8) && tables(7, 20, 8, true) && !tables(7, 72, 8, true));
+    CHECK(!tables(7, 18, 9, false, true) && tables(7, 27, 9, true, true) && !tables(3, 28, 14, false, true) &&
+          tables(3, 42, 14, false, true));
+    CHECK(tables(7, 56, 28) && !tables(7, 56, 28, false, false, 1000000) && !tables(3, 80, 40, false, false, 100000));
+}
+
 int main() {
     fill_binomials(BINOM);
     check_groups();
     std::printf("OK groups\n");
     check_rounds();
     std::printf("OK rounds\n");
+    check_tables();
+    std::printf("OK tables\n");
     return 0;
 }
