@@ -33,13 +33,6 @@ namespace {
 
 constexpr int MAX_DEV = 16;
 
-// A shape's round table on the device (fill_round_table, take_triples) and
-// whether its calls build triple tables.
-struct Shape {
-    RoundTable *rounds = nullptr;
-    bool triples = false;
-};
-
 struct DevCtx {
     bool ready = false;
     int cu = 0;
@@ -71,8 +64,10 @@ struct DevCtx {
     BatchState *b_state = nullptr;
     CodeResult *b_host_res = nullptr;
     BatchState *b_host_state = nullptr;
-    // what plain calls of one shape share, built once on first use (get_shape)
-    std::map<std::array<int, 9>, Shape> shapes;  // key: p, n, k, W, columns, grid, table layout, expected rounds, launch
+    // what plain calls share, built on first use: the rounds' task counts on the
+    // device, and whether a shape's calls build triple tables
+    std::map<RoundKey, RoundTable *> rounds;
+    std::map<std::array<int, 6>, bool> triples;  // key: p, k, columns, sets, expected rounds, launch
     // the second information set computed ahead by a second workgroup of the
     // decomposition launch, and the value its flag takes in this call
     SpecBuf *spec = nullptr;
@@ -169,8 +164,8 @@ void release_ctx(DevCtx &c) {
     // teardown: errors are not actionable here
     if (c.stream) (void)hipStreamSynchronize(c.stream);
     if (c.have_last && c.done_ev) (void)hipEventSynchronize(c.done_ev);
-    for (auto &kv : c.shapes) (void)hipFree(kv.second.rounds);
-    c.shapes.clear();
+    for (auto &kv : c.rounds) (void)hipFree(kv.second);
+    c.rounds.clear();
     for (void *p : {(void *)c.g_buf, (void *)c.cs, (void *)c.rows, (void *)c.pairs, (void *)c.binom, (void *)c.hist,
                     (void *)c.spec, (void *)c.reports, (void *)c.b_cs, (void *)c.b_claims, (void *)c.b_codes, (void *)c.b_rows,
                     (void *)c.b_pairs, (void *)c.b_g, (void *)c.b_state})
@@ -379,26 +374,36 @@ void launch_op(int op, int blocks, hipStream_t s, int nvec, int words, const u32
     }
 }
 
-// sch: the table layout of the launch, or NO_TABLE; last: see expected_rounds
-int get_shape(DevCtx &c, int p, int n, int k, int W, int nsym, int grid, int sch, int last,
-              u64 launch_tiles, const Shape **out) {
-    const std::array<int, 9> key = {p, n, k, W, nsym, grid, sch, last, (int)launch_tiles};
-    auto it = c.shapes.find(key);
-    if (it == c.shapes.end()) {
+// whether a plain call with tables builds triple tables (triples_worth)
+bool plain_triples(DevCtx &c, int p, int n, int k, int W, int nsym, bool no_term, u64 max_codewords) {
+    const int last = expected_rounds(p, n, k, no_term, max_codewords, host_binom()), sets = expected_sets(n, k);
+    if (last < TRIPLE_G) return false;
+    const u64 launch = triple_launch_tiles(p, n, k, no_term, last);
+    const auto at = c.triples.try_emplace({p, k, nsym, sets, last, (int)launch}, false);
+    if (at.second)
+        at.first->second = triples_worth(p, k, nsym, sets, last, sweep_cap_for(p, W, table_sweep_ops(p)), launch, host_binom());
+    return at.first->second;
+}
+
+int get_rounds(DevCtx &c, int p, int k, int W, int grid, bool tables, bool triples, const RoundTable **out) {
+    const auto at = c.rounds.try_emplace(RoundKey{p, k, W, grid, tables, triples}, nullptr);
+    RoundTable *&d = at.first->second;
+    if (d == nullptr) {
         RoundTable t;
-        Shape sh;
-        const uint32_t ops = sch != NO_TABLE ? table_sweep_ops(p) : plain_sweep_ops(p), cap = sweep_cap_for(p, W, ops);
+        const uint32_t ops = tables ? table_sweep_ops(p) : plain_sweep_ops(p);
         fill_round_table(p, k, W, (uint32_t)grid, ops, host_binom(), &t);
-        sh.triples = sch != NO_TABLE && triples_worth(p, k, nsym, expected_sets(n, k), last, cap, launch_tiles, host_binom());
-        if (sh.triples) take_triples(p, k, cap, (uint32_t)grid, host_binom(), &t);
-        HIP_OK(hipMalloc(&sh.rounds, sizeof(RoundTable)));
-        if (hipMemcpy(sh.rounds, &t, sizeof(RoundTable), hipMemcpyHostToDevice) != hipSuccess) {
-            (void)hipFree(sh.rounds);
+        if (triples) take_triples(p, k, sweep_cap_for(p, W, ops), (uint32_t)grid, host_binom(), &t);
+        if (hipMalloc(&d, sizeof(RoundTable)) != hipSuccess) {
+            d = nullptr;
             return BZ_ERR_DEVICE;
         }
-        it = c.shapes.emplace(key, sh).first;
+        if (hipMemcpy(d, &t, sizeof(RoundTable), hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipFree(d);
+            d = nullptr;
+            return BZ_ERR_DEVICE;
+        }
     }
-    *out = &it->second;
+    *out = d;
     return BZ_OK;
 }
 
@@ -549,9 +554,9 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     // for each other's checks ([45, 13] over F_7: 73 us of enumeration against
     // 58 us for five workgroups of the earlier kernel)
     const int deal = tables ? std::max(grid, c->cu * std::min(bpc, DEAL_GROUPS)) : grid;
-    const Shape *shape = nullptr;
-    const int last = expected_rounds(p, n, k, o.no_termination != 0, max_cw, host_binom());
-    st = get_shape(*c, p, n, k, W, nsym, deal, sch, last, triple_launch_tiles(p, n, k, o.no_termination != 0, last), &shape);
+    const bool triples = tables && plain_triples(*c, p, n, k, W, nsym, o.no_termination != 0, max_cw);
+    const RoundTable *rounds = nullptr;
+    st = get_rounds(*c, p, k, W, deal, tables, triples, &rounds);
     if (st != BZ_OK) return st;
 
     const uint8_t *Gd = G;
@@ -572,15 +577,15 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     a.grid = (uint32_t)deal;
     a.sweep_ops = tables ? table_sweep_ops(p) : plain_sweep_ops(p);
     a.timeout_ticks = timeout;
-    a.rounds = shape->rounds;
+    a.rounds = rounds;
     if (++c->spec_epoch == 0) c->spec_epoch = 1;
     a.spec = o.no_ahead ? nullptr : c->spec;
     a.epoch = c->spec_epoch;
     a.reports = tables ? c->reports : nullptr;
     a.pad = 0;
     a.pairs = tables ? c->pairs : nullptr;
-    a.pair_stride = (uint32_t)set_table_size(p, k, nsym, shape->triples);
-    a.triples = shape->triples;
+    a.pair_stride = (uint32_t)set_table_size(p, k, nsym, triples);
+    a.triples = triples;
     a.pair_w = (int16_t)W;
     a.pair_scheme = (int16_t)unit_scheme(p, nsym);
     a.pair_t0 = 1;  // a workgroup of the decomposition launch of its own builds set 0's table
@@ -588,7 +593,7 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     HIP_OK(p == 3 ? launch_decompose<3>(WF, Gd, c->cs, c->rows, a, s)
                   : launch_decompose<7>(WF, Gd, c->cs, c->rows, a, s));
     const uint32_t triple_off = (uint32_t)unit_table_size(p, k, nsym);
-    if (shape->triples) {
+    if (triples) {
         triple_kernel<<<triple_blocks_per_code(1, c->cu), 256, 0, s>>>(c->cs, c->rows, c->pairs, p, k, W, sch,
                                                                        a.pair_stride, triple_off);
         HIP_OK(hipGetLastError());

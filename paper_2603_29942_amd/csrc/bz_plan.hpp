@@ -2,6 +2,7 @@
 // alone (no device calls, so that it is checked on the CPU).
 #pragma once
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <stdint.h>
@@ -16,6 +17,11 @@ namespace bz {
 // without tables, [48, 12] 66.8 us with three, 89.0 with four; [66, 11] 81.4
 // and 92.0; [108, 9], four words, 131.1 with two, 136.6 with three).
 inline int prefix_groups(int p, int W) { return p == 3 ? (W <= 2 ? 5 : 4) : W == 1 ? 4 : W == 2 ? 3 : 2; }
+
+// What a plain call's round table depends on (fill_round_table, take_triples):
+// p, k, words per plane, the grid of the schedule, tables, triples.  The length
+// is no part of it, so calls on codes of many lengths share one.
+typedef std::array<int, 6> RoundKey;
 
 // the columns processed per combination
 inline int processed_columns(int n, int k, bool skip) { return skip ? n - k : n; }
