@@ -717,7 +717,7 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     // validate every code and lay out its rows
     std::vector<BatchCode> bc((size_t)ncodes);
     u64 row_words = 0, table_words = 0;
-    int wmax = 1;
+    int wmax = 1, units = 0;
     bool any_triples = false;
     for (int i = 0; i < ncodes; i++) {
         const bz_code &cd = codes[i];
@@ -747,6 +747,7 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
         b.pair_stride = (uint32_t)set_table_size(cd.p, cd.k, nsym, triples);
         b.pair_offset = table_words;
         if (b.W > wmax) wmax = b.W;
+        units = std::max(units, table_units(cd.p, cd.k));
         row_words += batch_row_words(cd.n, cd.k);
         table_words += code_table_size(cd.p, cd.n, cd.k, nsym, triples, false);
     }
@@ -771,7 +772,7 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     zero_batch_state<<<1, 1, 0, s>>>(c->b_state);
     HIP_OK(hipGetLastError());
     if (o.timing) HIP_OK(hipEventRecord(c->ev[0], s));
-    decompose_batch_kernel<<<ncodes, DECOMP_THREADS, 0, s>>>(Gd, c->b_codes, c->b_cs, c->b_claims, c->b_rows, c->b_pairs,
+    decompose_batch_kernel<<<ncodes, decomp_threads(ncodes, units, c->cu), 0, s>>>(Gd, c->b_codes, c->b_cs, c->b_claims, c->b_rows, c->b_pairs,
                                                 (uint32_t)grid, c->b_state, nullptr, nullptr, nullptr);
     HIP_OK(hipGetLastError());
     if (any_triples) {
@@ -1265,6 +1266,7 @@ int server_round(bz_server *s) {
     }
     double admitted_work = 0.0;
     bool any_triples = false;
+    int units = 0;
     for (int i = 0; i < s->slots && !s->queue.empty(); i++) {
         bz_server::Slot &sl = s->slot[(size_t)i];
         if (sl.state != 0) continue;
@@ -1297,6 +1299,7 @@ int server_round(bz_server *s) {
         b.sweep_ops = DEFAULT_SWEEP_OPS;
         const int nsym = processed_columns(r.n, r.k, s->o.identity_skip != 0);
         b.scheme = unit_scheme(r.p, nsym);
+        units = std::max(units, table_units(r.p, r.k));
         const bool triples = s->triples && triples_worth(r.p, r.k, nsym, expected_sets(r.n, r.k),
                                                          expected_rounds(r.p, r.n, r.k, false, s->max_cw, host_binom()),
                                                          sweep_cap_for(r.p, b.W, DEFAULT_SWEEP_OPS), 0, host_binom());
@@ -1315,7 +1318,7 @@ int server_round(bz_server *s) {
         HIP_OK(hipMemcpyAsync(s->codes, s->codes_h, sizeof(BatchCode) * (size_t)s->slots, hipMemcpyHostToDevice,
                               s->run));
         HIP_OK(hipMemcpyAsync(s->new_d, s->new_h, sizeof(int32_t) * (size_t)nf, hipMemcpyHostToDevice, s->run));
-        decompose_batch_kernel<<<nf, DECOMP_THREADS, 0, s->run>>>(s->g, s->codes, s->cs, s->claims, s->rows, s->pairs,
+        decompose_batch_kernel<<<nf, decomp_threads(nf, units, s->c->cu), 0, s->run>>>(s->g, s->codes, s->cs, s->claims, s->rows, s->pairs,
                                                       (uint32_t)s->decomp_grid, s->bs, s->new_d, s->done_dev,
                                                       s->res_dev);
         HIP_OK(hipGetLastError());

@@ -976,11 +976,6 @@ __device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32
     if (lane < (int)POOL_SLICES) cs->pool_next[lane][0] = 0;
 }
 
-// Wavefronts of a decomposition workgroup that builds tables: a table of 2000
-// units takes one wavefront about 20 us, more than the elimination; eight
-// build it in about 3 us.
-constexpr int DECOMP_THREADS = 512;
-
 template <int P, int WF>
 __global__ __launch_bounds__(DECOMP_THREADS) void decompose_kernel(const uint8_t *__restrict__ G, CodeState *cs,
                                                                    u32 *__restrict__ rows, RunArgs args) {

@@ -106,6 +106,11 @@ struct QEntry {
 // one pool of tiles, claimed by POOL_SLICES counters (see pool_stages).
 constexpr uint32_t POOL_SLICES = 32;
 
+// Threads of a decomposition workgroup that builds tables: a table of 2000
+// units takes one wavefront about 20 us, more than the elimination; eight
+// build it in about 3 us.
+constexpr int DECOMP_THREADS = 512;
+
 // Results the host reads back (kept contiguous and first in CodeState).
 struct CodeResult {
     int32_t status;       // BZ_OK or a negative status

@@ -44,3 +44,23 @@ def test_new_lengths_allocate_nothing():
             call(n, k)
     torch.cuda.synchronize()
     assert torch.cuda.mem_get_info()[0] == free
+
+
+@pytest.mark.gpu
+def test_many_small_codes():
+    """More codes than compute units, whose tables one wavefront builds: every
+    result is the kernel's without tables."""
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2603_29942_amd import bz
+    rng = np.random.default_rng(61)
+    codes = []
+    for i in range(600):
+        p = (3, 7)[i % 2]
+        k = int(rng.integers(1, 33 if p == 3 else 13))
+        codes.append((p, rng.integers(0, p, size=(k, int(rng.integers(k, k + 14))), dtype=np.uint8)))
+    got = bz.min_distance_batch(codes, device="cuda:0")
+    for (p, G), r in zip(codes, got):
+        ref = bz.min_distance(p, G, pair_tables=-1)
+        for key in ("status", "d", "m", "ranks", "stages", "codewords_total"):
+            assert r[key] == ref[key], (p, G.shape, key, r[key], ref[key])
