@@ -254,9 +254,15 @@ void bz_default_batch_options(bz_batch_options *o);
  * RANK, LIMIT).  Returns BZ_OK when the batch ran, BZ_ERR_ARG for an invalid
  * batch or code descriptor (nothing runs), BZ_ERR_NOMEM, or BZ_ERR_DEVICE.
  * The library keeps a batch workspace per device that grows to the largest
- * batch seen (about 28 KB per code plus the packed rows and the pair tables:
- * (n/k + 1) k(k-1)/2 W 16 bytes per code for F_3, six times that for F_7,
- * W = ceil((n-k)/32) with the identity skip, else ceil(n/32)). */
+ * batch seen, until bz_release: about 28 KB per code, the packed rows and the
+ * tables of its sets (n/k + 1 of them).  A pair table has k(k-1)/2 (p-1)
+ * entries; codes whose later rounds pay for it have a table of triples too, of
+ * C(k,3) (p-1)^2 entries, at most 4 MiB a set.  An entry is 16 bytes over F_3
+ * (32 from 65 processed columns on), 32 over F_7 (64 from 33 to 42 columns and
+ * from 65 on).  512 codes of 30 to 90 columns take 1.2 GB.  Tables with triples
+ * take up to 24 GiB, and up to an eighth of the device's free memory when the
+ * workspace grows; the codes beyond that, or all of them where the allocation
+ * fails, have pair tables only (no result depends on it). */
 int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, uint64_t g_bytes, int G_is_device,
                           bz_batch_options *o, bz_result *out, int32_t *status_out);
 
@@ -301,9 +307,12 @@ typedef struct {
 
 void bz_default_server_options(bz_server_options *o);
 /* Allocates the slots (about 28 KB + 4 KB x min(128, max_n) + 64 max_n bytes
- * each, plus the pair tables of the largest code a slot may hold: 0.39 MB for
- * max_n = 64, 1.7 MB for max_n = 128 with the identity skip, 0.77 / 2.3 MB
- * without). */
+ * each, plus the pair tables of the largest code a slot may hold: 0.77 MB for
+ * max_n = 64, 2.25 MB for max_n = 128 with the identity skip, 0.77 / 2.32 MB
+ * without), and one space for the triples of the codes that take them, 3 MiB a
+ * slot, at most 4 GiB and an eighth of the device's free memory.  A code that
+ * finds no room there, or every code where the device has none to give, runs
+ * with pair tables (no result depends on it). */
 int bz_server_start(const bz_server_options *o, bz_server **out);
 /* Queues one code (G: host, k x n row-major, copied); tag is returned with its result.
  * BZ_ERR_ARG for an invalid shape or n > max_n; the code's own errors (VALUE,

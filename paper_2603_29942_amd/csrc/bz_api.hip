@@ -106,9 +106,6 @@ const u64 *host_binom() {
 
 // workgroups per code of a triple-table launch: about eight per compute unit in all
 int triple_blocks_per_code(int ncodes, int cu) { return std::max(1, std::min(8 * cu / std::max(ncodes, 1), 2 * cu)); }
-// the most 16-byte words a batch's or a server's tables may take with triples
-// (24 GiB); what is beyond has pair tables only
-constexpr u64 TRIPLE_BUDGET = (24ull << 30) / 16;
 
 int init_ctx(int dev) {
     DevCtx &c = g_ctx[dev];
@@ -463,7 +460,11 @@ int grow_batch(DevCtx &c, size_t ncodes, size_t row_words, size_t table_words, s
         if (c.b_pairs) (void)hipFree(c.b_pairs);
         c.b_pairs = nullptr;
         c.b_pairs_cap = 0;
-        if (hipMalloc(&c.b_pairs, sizeof(uint4) * table_words) != hipSuccess) return BZ_ERR_NOMEM;
+        if (hipMalloc(&c.b_pairs, sizeof(uint4) * table_words) != hipSuccess) {
+            (void)hipGetLastError();  // (the caller tries again with less)
+            c.b_pairs = nullptr;
+            return BZ_ERR_NOMEM;
+        }
         c.b_pairs_cap = table_words;
     }
     if (g_bytes > c.b_g_cap) {
@@ -716,9 +717,9 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     const u64 max_cw = o.max_codewords ? o.max_codewords : DEFAULT_LIMIT;
     // validate every code and lay out its rows
     std::vector<BatchCode> bc((size_t)ncodes);
-    u64 row_words = 0, table_words = 0;
+    std::vector<char> want((size_t)ncodes);  // triples
+    u64 row_words = 0;
     int wmax = 1, units = 0;
-    bool any_triples = false;
     for (int i = 0; i < ncodes; i++) {
         const bz_code &cd = codes[i];
         if (check_args(cd.p, cd.n, cd.k, G, out) != BZ_OK || cd.sweep_ops < 0) return BZ_ERR_ARG;
@@ -739,17 +740,11 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
         const int nsym = processed_columns(cd.n, cd.k, o.identity_skip != 0);
         b.scheme = unit_scheme(cd.p, nsym);
         const int last = expected_rounds(cd.p, cd.n, cd.k, o.no_termination != 0, max_cw, host_binom());
-        bool triples = triples_worth(cd.p, cd.k, nsym, expected_sets(cd.n, cd.k), last,
-                                     sweep_cap_for(cd.p, b.W, b.sweep_ops), 0, host_binom());
-        triples = triples && table_words + code_table_size(cd.p, cd.n, cd.k, nsym, true, false) <= TRIPLE_BUDGET;
-        any_triples |= triples;
-        b.triple_off = triples ? (uint32_t)unit_table_size(cd.p, cd.k, nsym) : 0u;
-        b.pair_stride = (uint32_t)set_table_size(cd.p, cd.k, nsym, triples);
-        b.pair_offset = table_words;
+        want[(size_t)i] = triples_worth(cd.p, cd.k, nsym, expected_sets(cd.n, cd.k), last,
+                                        sweep_cap_for(cd.p, b.W, b.sweep_ops), 0, host_binom());
         if (b.W > wmax) wmax = b.W;
         units = std::max(units, table_units(cd.p, cd.k));
         row_words += batch_row_words(cd.n, cd.k);
-        table_words += code_table_size(cd.p, cd.n, cd.k, nsym, triples, false);
     }
     DevCtx *c = nullptr;
     int st = get_ctx(o.device, &c);
@@ -757,8 +752,21 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     std::lock_guard<std::mutex> lk(c->mu);
     HIP_OK(hipSetDevice(o.device));
     hipStream_t s = o.hip_stream ? (hipStream_t)o.hip_stream : c->stream;
-    st = grow_batch(*c, (size_t)ncodes, (size_t)row_words, (size_t)table_words, G_is_device ? 0 : (size_t)g_bytes);
+    // tables that the workspace holds already are taken as they are; more than
+    // that, with triples, within the budget
+    auto lay_out = [&](u64 budget) { return lay_out_tables(bc, want, budget); };
+    u64 budget = BATCH_TABLES;
+    if (lay_out(budget) > c->b_pairs_cap) {
+        size_t free_bytes = 0, total_bytes = 0;
+        HIP_OK(hipMemGetInfo(&free_bytes, &total_bytes));
+        budget = std::max(table_budget(budget, free_bytes), (u64)c->b_pairs_cap);
+    }
+    st = fit_tables(budget, lay_out, [&](u64 words) {
+        return grow_batch(*c, (size_t)ncodes, (size_t)row_words, (size_t)words, G_is_device ? 0 : (size_t)g_bytes);
+    });
     if (st != BZ_OK) return st;
+    bool any_triples = false;
+    for (const BatchCode &b : bc) any_triples |= b.triple_off != 0;
     const int bpc = o.blocks_per_cu ? o.blocks_per_cu : 64;  // default: as many as fit
     const int grid = batch_grid(wmax, c->cu, bpc);
     if (grid < 1) return BZ_ERR_DEVICE;
@@ -1128,6 +1136,7 @@ struct bz_server {
     std::deque<Req> queue;
     struct Slot {
         int state = 0;  // 0 free, 1 active
+        bool in_arena = false;  // its tables are in the arena (triples)
         int p = 0, n = 0, k = 0;
         u64 tag = 0;
         float prio = 0;       // predicted log10 work after the decomposition
@@ -1137,7 +1146,7 @@ struct bz_server {
     u64 seq = 0;
     u64 rounds = 0, yields = 0;
     bool running = false;
-    bool triples = false;  // the slots have room for triple tables
+    TableArena arena;  // the words of `pairs` behind the slots' own: tables with triples
     int wmax = 2;
     std::mutex mu;
 };
@@ -1192,6 +1201,9 @@ int server_harvest(bz_server *s, int max_out, uint64_t *tags, bz_result *results
                              s->codes_h[i].sweep_ops);
         (*n_out)++;
         sl.state = 0;
+        // (the next round's kernels, which follow this round's on its stream, may write there)
+        if (sl.in_arena) s->arena.give(s->codes_h[i].pair_offset - s->pairs_per_slot * (u64)s->slots);
+        sl.in_arena = false;
         __atomic_store_n(&s->done_h[i], 0u, __ATOMIC_RELEASE);
     }
     return BZ_OK;
@@ -1300,13 +1312,16 @@ int server_round(bz_server *s) {
         const int nsym = processed_columns(r.n, r.k, s->o.identity_skip != 0);
         b.scheme = unit_scheme(r.p, nsym);
         units = std::max(units, table_units(r.p, r.k));
-        const bool triples = s->triples && triples_worth(r.p, r.k, nsym, expected_sets(r.n, r.k),
-                                                         expected_rounds(r.p, r.n, r.k, false, s->max_cw, host_binom()),
-                                                         sweep_cap_for(r.p, b.W, DEFAULT_SWEEP_OPS), 0, host_binom());
+        u64 at = 0;
+        const bool triples = triples_worth(r.p, r.k, nsym, expected_sets(r.n, r.k),
+                                           expected_rounds(r.p, r.n, r.k, false, s->max_cw, host_binom()),
+                                           sweep_cap_for(r.p, b.W, DEFAULT_SWEEP_OPS), 0, host_binom()) &&
+                             s->arena.take(code_table_size(r.p, r.n, r.k, nsym, true, false), &at);
         any_triples |= triples;
+        sl.in_arena = triples;
         b.triple_off = triples ? (uint32_t)unit_table_size(r.p, r.k, nsym) : 0u;
         b.pair_stride = (uint32_t)set_table_size(r.p, r.k, nsym, triples);
-        b.pair_offset = (u64)i * s->pairs_per_slot;
+        b.pair_offset = triples ? s->pairs_per_slot * (u64)s->slots + at : (u64)i * s->pairs_per_slot;
         s->new_h[fresh.size()] = i;
         fresh.push_back(i);
     }
@@ -1409,9 +1424,7 @@ int bz_server_start(const bz_server_options *opt, bz_server **out) {
     const int max_n = o.max_n ? o.max_n : BZ_MAX_N;
     s->wmax = (max_n + 31) / 32 <= 2 ? 2 : 4;
     s->rows_per_slot = batch_row_words(max_n, 1);
-    s->pairs_per_slot = max_table_size(max_n, o.identity_skip ? 1 : 0, true, false);
-    s->triples = s->pairs_per_slot * (u64)s->slots <= TRIPLE_BUDGET;
-    if (!s->triples) s->pairs_per_slot = max_table_size(max_n, o.identity_skip ? 1 : 0, false, false);
+    s->pairs_per_slot = max_table_size(max_n, o.identity_skip ? 1 : 0, false, false);
     s->g_per_slot = (u64)(((max_n * BZ_MAX_K) + 255) / 256 * 256);
     s->grid = batch_grid(s->wmax, c->cu, o.blocks_per_cu ? o.blocks_per_cu : 64);  // default: as many as fit
     s->grid2 = batch_grid(2, c->cu, o.blocks_per_cu ? o.blocks_per_cu : 64);
@@ -1424,7 +1437,6 @@ int bz_server_start(const bz_server_options *opt, bz_server **out) {
               hipMalloc(&s->claims, sizeof(u64) * ns) == hipSuccess &&
               hipMalloc(&s->codes, sizeof(BatchCode) * ns) == hipSuccess &&
               hipMalloc(&s->rows, sizeof(u32) * s->rows_per_slot * ns) == hipSuccess &&
-              hipMalloc(&s->pairs, sizeof(uint4) * s->pairs_per_slot * ns) == hipSuccess &&
               hipMalloc(&s->g, s->g_per_slot * ns) == hipSuccess && hipMalloc(&s->bs, sizeof(BatchState)) == hipSuccess &&
               hipMalloc(&s->order_d, sizeof(int32_t) * ns) == hipSuccess &&
               hipMalloc(&s->new_d, sizeof(int32_t) * ns) == hipSuccess &&
@@ -1442,6 +1454,25 @@ int bz_server_start(const bz_server_options *opt, bz_server **out) {
               hipHostMalloc(&s->new_h, sizeof(int32_t) * ns, hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc(&s->pred_h, sizeof(float) * ns, hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc(&s->qfeat_h, sizeof(float) * 4 * ns, hipHostMallocDefault) == hipSuccess;
+    if (ok) {
+        // last: the slots' pair tables and, of what is left, the space for triples
+        size_t free_bytes = 0, total_bytes = 0;
+        if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
+        u64 arena = 0;
+        ok = fit_tables(
+                 free_bytes,
+                 [&](u64 room) {
+                     arena = server_triples(s->slots, max_n, o.identity_skip ? 1 : 0, room);
+                     return s->pairs_per_slot * (u64)ns + arena;
+                 },
+                 [&](u64 words) {
+                     if (hipMalloc(&s->pairs, sizeof(uint4) * words) == hipSuccess) return (int)BZ_OK;
+                     (void)hipGetLastError();  // (tried again with less)
+                     s->pairs = nullptr;
+                     return (int)BZ_ERR_NOMEM;
+                 }) == BZ_OK;
+        s->arena.reset(arena, ns);
+    }
     if (!ok) {
         server_free(s);
         return BZ_ERR_NOMEM;

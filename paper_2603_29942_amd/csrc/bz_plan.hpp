@@ -6,6 +6,7 @@
 #include <atomic>
 #include <cmath>
 #include <stdint.h>
+#include <vector>
 
 #include "bz_units.hpp"
 
@@ -65,6 +66,85 @@ inline u64 max_table_size(int max_n, int skip, bool triples, bool ahead_slot) {
                         best = std::max(best, code_table_size(p, n, k, nsym, triples && triples_fit(p, k, nsym), ahead_slot));
                 }
     return best;
+}
+
+// ---- memory for tables
+// What a batch's tables or a server's triples may take at most, in 16-byte
+// words (24 GiB, 4 GiB), and of the device's free memory: the rest of the
+// program has uses for it too, and every code runs with pair tables alone.
+constexpr u64 BATCH_TABLES = (24ull << 30) / 16, SERVER_TRIPLES = (4ull << 30) / 16;
+constexpr u64 FREE_SHARE = 8;
+inline u64 table_budget(u64 most, u64 free_bytes) { return std::min(most, free_bytes / FREE_SHARE / 16); }
+
+// Lays out the tables of a batch (offset, stride, triple offset of each code)
+// and returns their size.  want[i]: code i takes triples, as long as the tables
+// up to its own fit the budget.
+inline u64 lay_out_tables(std::vector<BatchCode> &codes, const std::vector<char> &want, u64 budget) {
+    u64 words = 0;
+    for (size_t i = 0; i < codes.size(); i++) {
+        BatchCode &b = codes[i];
+        const int nsym = processed_columns(b.n, b.k, (b.flags & FLAG_SKIP) != 0);
+        const bool triples = want[i] && words + code_table_size(b.p, b.n, b.k, nsym, true, false) <= budget;
+        b.triple_off = triples ? (uint32_t)unit_table_size(b.p, b.k, nsym) : 0u;
+        b.pair_stride = (uint32_t)set_table_size(b.p, b.k, nsym, triples);
+        b.pair_offset = words;
+        words += code_table_size(b.p, b.n, b.k, nsym, triples, false);
+    }
+    return words;
+}
+// Allocates what `lay_out(budget)` needs through `grow`, without triples (a
+// budget of 0) where that much cannot be had.
+template <typename LayOut, typename Grow>
+int fit_tables(u64 budget, LayOut &&lay_out, Grow &&grow) {
+    const u64 words = lay_out(budget);
+    const int st = grow(words);
+    if (st != BZ_ERR_NOMEM) return st;
+    const u64 least = lay_out((u64)0);
+    return least < words ? grow(least) : st;
+}
+
+// Ranges of one buffer, first fit: a server's space for the tables of the codes
+// that take triples.
+class TableArena {
+    struct Range {
+        u64 at, size;
+    };
+    std::vector<Range> used;  // by address
+    u64 size = 0;
+
+public:
+    void reset(u64 words, size_t most_ranges) {
+        size = words;
+        used.clear();
+        used.reserve(most_ranges);
+    }
+    bool take(u64 words, u64 *at) {
+        u64 from = 0;
+        size_t i = 0;
+        while (i < used.size() && used[i].at - from < words) {
+            from = used[i].at + used[i].size;
+            i++;
+        }
+        if (words == 0 || words > size || from > size - words) return false;
+        used.insert(used.begin() + (long)i, Range{from, words});
+        *at = from;
+        return true;
+    }
+    void give(u64 at) {
+        for (size_t i = 0; i < used.size(); i++)
+            if (used[i].at == at) {
+                used.erase(used.begin() + (long)i);
+                return;
+            }
+    }
+};
+// Words of that space: 3 MiB a slot (of requests of rate 1/2 with up to 40 rows,
+// 28 over F_7, one in two takes 2.8 MB on average, one in four 0.35 MB), and at least
+// one code of any kind.
+inline u64 server_triples(int slots, int max_n, int skip, u64 free_bytes) {
+    const u64 want = std::max((u64)slots * (3u << 20) / 16, max_table_size(max_n, skip, true, false));
+    const u64 words = std::min(want, table_budget(SERVER_TRIPLES, free_bytes));
+    return words < max_table_size(max_n, skip, true, false) ? 0 : words;
 }
 
 // The minimum weight that a random [n, k] code is expected to have: about the

@@ -1,6 +1,7 @@
 // Host checks of bz_plan.hpp: what is decided from shapes and options alone.
 #include <cstdio>
 #include <cstdlib>
+#include <random>
 
 #include "bz_plan.hpp"
 
@@ -109,6 +110,95 @@ static void check_threads() {
     CHECK(decomp_threads(257, table_units(3, 32), 256) == 64 && decomp_threads(257, table_units(3, 33), 256) == 512);
 }
 
+// Tables of a batch: side by side, triples only within the budget; an
+// allocation that fails with them is tried without.
+static void check_layout() {
+    std::mt19937 rng(5);
+    for (int t = 0; t < 200; t++) {
+        std::vector<BatchCode> codes(1 + rng() % 40);
+        std::vector<char> want(codes.size());
+        const int flags = rng() % 2 ? FLAG_SKIP : 0;
+        for (size_t i = 0; i < codes.size(); i++) {
+            BatchCode &b = codes[i];
+            b.p = rng() % 2 ? 3 : 7;
+            b.k = 1 + (int)(rng() % 30);
+            b.n = b.k + (int)(rng() % 60);
+            b.flags = flags;
+            want[i] = triples_fit(b.p, b.k, processed_columns(b.n, b.k, flags != 0));
+        }
+        for (u64 budget : {(u64)0, (u64)1 << 16, (u64)1 << 20, BATCH_TABLES}) {
+            const u64 words = lay_out_tables(codes, want, budget);
+            u64 at = 0;
+            bool any = false;
+            for (size_t i = 0; i < codes.size(); i++) {
+                const BatchCode &b = codes[i];
+                const int nsym = processed_columns(b.n, b.k, flags != 0);
+                CHECK(b.pair_offset == at && (b.triple_off == 0 || (want[i] && at + b.pair_stride * (u64)pair_sets(b.n, b.k) <= budget)));
+                CHECK(b.pair_stride == unit_table_size(b.p, b.k, nsym) + (b.triple_off ? triple_table_size(b.p, b.k, nsym) : 0));
+                at += b.pair_stride * (u64)pair_sets(b.n, b.k);
+                any |= b.triple_off != 0;
+            }
+            CHECK(at == words && (budget > 0 || !any));
+        }
+    }
+    int calls = 0;
+    u64 got = 0;
+    auto lay_out = [](u64 budget) { return 100 + budget; };
+    auto grow = [&](u64 room) {
+        return [&, room](u64 words) {
+            calls++;
+            got = words;
+            return words <= room ? (int)BZ_OK : (int)BZ_ERR_NOMEM;
+        };
+    };
+    CHECK(fit_tables(50, lay_out, grow(150)) == BZ_OK && calls == 1 && got == 150);
+    CHECK(fit_tables(50, lay_out, grow(149)) == BZ_OK && calls == 3 && got == 100);
+    CHECK(fit_tables(50, lay_out, grow(99)) == BZ_ERR_NOMEM && calls == 5);
+    CHECK(fit_tables(0, lay_out, grow(99)) == BZ_ERR_NOMEM && calls == 6);
+    CHECK(fit_tables(50, lay_out, [](u64) { return (int)BZ_ERR_DEVICE; }) == BZ_ERR_DEVICE);
+    // a server's space: bounded, of the free memory too, and none rather than less than one code's
+    const u64 one = max_table_size(128, 1, true, false), plenty = 1ull << 38;
+    CHECK(server_triples(1, 128, 1, plenty) == one && server_triples(1024, 128, 1, plenty) * 16 == 3ull << 30);
+    CHECK(server_triples(65536, 128, 1, plenty) == SERVER_TRIPLES && server_triples(1024, 128, 1, 8ull << 30) * 16 == 1ull << 30);
+    CHECK(server_triples(1024, 128, 1, one * 16 * 7) == 0 && server_triples(1024, 128, 1, 0) == 0);
+}
+
+// Ranges handed out never overlap, and one is found whenever a gap holds it.
+static void check_arena() {
+    std::mt19937 rng(6);
+    TableArena a;
+    u64 at = 0;
+    a.reset(0, 4);
+    CHECK(!a.take(1, &at));
+    for (u64 size : {10ull, 1000ull}) {
+        a.reset(size, 64);
+        CHECK(!a.take(size + 1, &at) && !a.take(0, &at) && a.take(size, &at) && at == 0 && !a.take(1, &at));
+        a.give(0);
+        std::vector<char> map(size, 0);
+        std::vector<std::pair<u64, u64>> held;
+        for (int t = 0; t < 4000; t++) {
+            if (!held.empty() && rng() % 2) {
+                const size_t i = rng() % held.size();
+                a.give(held[i].first);
+                for (u64 w = 0; w < held[i].second; w++) map[held[i].first + w] = 0;
+                held.erase(held.begin() + (long)i);
+                continue;
+            }
+            const u64 want = 1 + rng() % (size / 4);
+            u64 run = 0, best = 0;
+            for (char c : map) best = std::max(best, run = c ? 0 : run + 1);
+            const bool ok = a.take(want, &at);
+            CHECK(ok == (best >= want));
+            if (!ok) continue;
+            for (u64 w = at; w < at + want; w++) {
+                CHECK(w < size && !map[w]);
+                map[w] = 1;
+            }
+            held.push_back({at, want});
+        }
+    }
+}
+
 int main() {
     fill_binomials(BINOM);
     check_groups();
@@ -119,5 +209,9 @@ int main() {
     std::printf("OK tables\n");
     check_threads();
     std::printf("OK threads\n");
+    check_layout();
+    std::printf("OK layout\n");
+    check_arena();
+    std::printf("OK arena\n");
     return 0;
 }

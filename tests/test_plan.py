@@ -64,3 +64,48 @@ def test_many_small_codes():
         ref = bz.min_distance(p, G, pair_tables=-1)
         for key in ("status", "d", "m", "ranks", "stages", "codewords_total"):
             assert r[key] == ref[key], (p, G.shape, key, r[key], ref[key])
+
+
+@pytest.mark.gpu
+def test_server_memory():
+    """A server's device memory is what the header says: the slots with their
+    pair tables, and at most 3 MiB a slot for triples."""
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2603_29942_amd import bz
+    bz.Server(slots=1, max_n=8).stop()  # the context's own memory
+    for max_n, tables in ((48, 0.45e6), (64, 0.78e6), (128, 2.26e6)):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        server = bz.Server(max_n=max_n)
+        used = free - torch.cuda.mem_get_info()[0]
+        server.stop()
+        slot = 28e3 + 4096 * max_n + 64 * max_n + tables + 3 * 2**20
+        assert used <= 1024 * slot * 1.05 + 64e6, (max_n, used)
+
+
+@pytest.mark.gpu
+def test_server_without_room_for_triples():
+    """Four codes that would take triples, and room for one at a time: the
+    others run with pair tables, and every result is the plain call's."""
+    import time
+
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2603_29942_amd import bz
+    codes = [np.random.default_rng([62, i]).integers(0, 7, size=(28, 56), dtype=np.uint8) for i in range(12)]
+    server = bz.Server(slots=4, max_n=64)
+    out = {}
+    for tag, G in enumerate(codes):
+        server.submit(7, G, tag)
+    t0 = time.perf_counter()
+    while len(out) < len(codes):
+        out.update(server.poll())
+        assert time.perf_counter() - t0 < 60
+    server.stop()
+    took = [bool(out[tag]["info"] & bz.INFO_TRIPLES) for tag in range(len(codes))]
+    assert any(took) and not all(took)
+    for tag, G in enumerate(codes):
+        ref = bz.min_distance(7, G)
+        for key in ("status", "d", "m", "ranks", "stages", "terminated_by", "codewords_total"):
+            assert out[tag][key] == ref[key], (tag, key)
