@@ -275,7 +275,7 @@ __device__ __forceinline__ void build_units(u32 *__restrict__ tab, int k, const 
 // build_units for the words per plane and the layout of this code, by every
 // thread of the workgroup
 template <int P>
-__device__ void build_pair_table(uint4 *ptab, int k, int W, int sch, const uint4 *prow) {
+__device__ __forceinline__ void build_pair_table(uint4 *ptab, int k, int W, int sch, const uint4 *prow) {
     u32 *tab = reinterpret_cast<u32 *>(ptab);
     if constexpr (P == 3) {
         if (W == 1) build_units<3, 1, 0>(tab, k, prow);
@@ -326,7 +326,7 @@ __device__ __forceinline__ void build_triples(u32 *__restrict__ tab, int k, cons
     }
 }
 
-__device__ void triple_tables(const CodeState *cs, const u32 *__restrict__ rows, uint4 *tables, int p, int k, int W,
+__device__ __forceinline__ void triple_tables(const CodeState *cs, const u32 *__restrict__ rows, uint4 *tables, int p, int k, int W,
                               int sch, uint32_t stride, uint32_t off, uint4 *prow) {
     if (uni(cs->res.status) != BZ_OK) return;
     const int m = uni(cs->res.m), slot1 = uni(cs->pair_slot1);
@@ -474,7 +474,7 @@ struct RoundPrefetch {
 // pair_sets(n, k), and nothing else.  ROLE_TABLE0: the first set's
 // elimination and its pair table in slot 0, and nothing else.
 template <int P, int WF>
-__device__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32 *__restrict__ rows,
+__device__ __forceinline__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32 *__restrict__ rows,
                                const RunArgs args, DecompLDS &lds, int role = ROLE_MAIN,
                                RoundPrefetch pre = RoundPrefetch()) {
     const bool ahead = role == ROLE_AHEAD, main_wg = role == ROLE_MAIN;
@@ -1748,7 +1748,7 @@ __device__ __forceinline__ void run_subset(const u32 *__restrict__ rows, LdsRows
 // g <= SUBSET_G: one item per lane (a row, a pair of rows, a triple; colex
 // rank task * 64 + lane).  Adds the combinations the lane evaluated to lcnt.
 template <int P, int W, bool HIST>
-__device__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
+__device__ __forceinline__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
                                const u64 *sbin, const u64 *__restrict__ gbin, u64 task, u32 &lmin, u64 &lcnt,
                                u32 *lh, u32 woff, u32 cap) {
     const int lane = __lane_id();
@@ -1817,7 +1817,7 @@ __device__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows
 // prefixes are built here.  bound, seen (thread 0): F_7 with a table, see StageBound.
 constexpr int NO_TABLE = -1;
 template <int P, int W, bool HIST, int SCH>
-__device__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
+__device__ __forceinline__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
                               const u32 *__restrict__ ptab, uint32_t triple_off, const u64 *sbin,
                               const u64 *__restrict__ gbin, const QEntry *qtab, int nq, u64 task, StageBound bound, int seen, int nsym, u32 &lmin, u64 &lcnt, u32 *lh,
                               u32 woff, u32 cap) {
@@ -2420,7 +2420,7 @@ __global__ void features_kernel(const CodeState *__restrict__ css, const int32_t
 // The tiles of one part of a stage: tile_of(r, part, parts, rot) for r = 0, 1, ...
 // The lane's combinations are added to lcnt.
 template <int P, int W, int SCH>
-__device__ void run_part(const StageDesc &sd, StageBound bound, int *smin, uint32_t part, int k, const u32 *__restrict__ rows,
+__device__ __forceinline__ void run_part(const StageDesc &sd, StageBound bound, int *smin, uint32_t part, int k, const u32 *__restrict__ rows,
                          const u32 *__restrict__ ptab, uint32_t triple_off, const u64 *sbin,
                          const u64 *__restrict__ gbin, const QEntry *qtab, int nsym, u32 woff, u32 cap, u32 &lmin, u64 &lcnt) {
     const int wid = threadIdx.x >> 6;
@@ -2447,7 +2447,7 @@ __device__ void run_part(const StageDesc &sd, StageBound bound, int *smin, uint3
 // L >= U test (Alg. 6) ends the code or publishes the next stage's claim word.
 // Run by one whole wavefront; lane 0 applies the check.  done_flag (serving)
 // is raised when the code ends, after its result block went to res_out.
-__device__ void batch_check(CodeState *cs, u64 *claim, int s, const StageDesc &sd, BatchState *bs,
+__device__ __forceinline__ void batch_check(CodeState *cs, u64 *claim, int s, const StageDesc &sd, BatchState *bs,
                             uint32_t *done_flag, CodeResult *res_out) {
     int last = 0;
     if (__lane_id() == 0) {

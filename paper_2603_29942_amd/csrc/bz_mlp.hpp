@@ -147,6 +147,7 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(const float *__restrict__
             constexpr int R = (MLP_SUB + 15) / 16;
             float a[R][4] = {};
             const int sr = tid >> 4;
+#pragma unroll 2
             for (int i = 0; i < MLP_H; i += 4) {
                 float4 w[4], d[R];
 #pragma unroll
