@@ -719,7 +719,7 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     std::vector<BatchCode> bc((size_t)ncodes);
     std::vector<char> want((size_t)ncodes);  // triples
     u64 row_words = 0;
-    int wmax = 1, units = 0;
+    int wmax = 1;
     for (int i = 0; i < ncodes; i++) {
         const bz_code &cd = codes[i];
         if (check_args(cd.p, cd.n, cd.k, G, out) != BZ_OK || cd.sweep_ops < 0) return BZ_ERR_ARG;
@@ -743,7 +743,6 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
         want[(size_t)i] = triples_worth(cd.p, cd.k, nsym, expected_sets(cd.n, cd.k), last,
                                         sweep_cap_for(cd.p, b.W, b.sweep_ops), 0, host_binom());
         if (b.W > wmax) wmax = b.W;
-        units = std::max(units, table_units(cd.p, cd.k));
         row_words += batch_row_words(cd.n, cd.k);
     }
     DevCtx *c = nullptr;
@@ -780,7 +779,7 @@ int bz_min_distance_batch(int ncodes, const bz_code *codes, const uint8_t *G, ui
     zero_batch_state<<<1, 1, 0, s>>>(c->b_state);
     HIP_OK(hipGetLastError());
     if (o.timing) HIP_OK(hipEventRecord(c->ev[0], s));
-    decompose_batch_kernel<<<ncodes, decomp_threads(ncodes, units, c->cu), 0, s>>>(Gd, c->b_codes, c->b_cs, c->b_claims, c->b_rows, c->b_pairs,
+    decompose_batch_kernel<<<ncodes, DECOMP_THREADS, 0, s>>>(Gd, c->b_codes, c->b_cs, c->b_claims, c->b_rows, c->b_pairs,
                                                 (uint32_t)grid, c->b_state, nullptr, nullptr, nullptr);
     HIP_OK(hipGetLastError());
     if (any_triples) {
@@ -1278,7 +1277,6 @@ int server_round(bz_server *s) {
     }
     double admitted_work = 0.0;
     bool any_triples = false;
-    int units = 0;
     for (int i = 0; i < s->slots && !s->queue.empty(); i++) {
         bz_server::Slot &sl = s->slot[(size_t)i];
         if (sl.state != 0) continue;
@@ -1311,7 +1309,6 @@ int server_round(bz_server *s) {
         b.sweep_ops = DEFAULT_SWEEP_OPS;
         const int nsym = processed_columns(r.n, r.k, s->o.identity_skip != 0);
         b.scheme = unit_scheme(r.p, nsym);
-        units = std::max(units, table_units(r.p, r.k));
         u64 at = 0;
         const bool triples = triples_worth(r.p, r.k, nsym, expected_sets(r.n, r.k),
                                            expected_rounds(r.p, r.n, r.k, false, s->max_cw, host_binom()),
@@ -1333,7 +1330,7 @@ int server_round(bz_server *s) {
         HIP_OK(hipMemcpyAsync(s->codes, s->codes_h, sizeof(BatchCode) * (size_t)s->slots, hipMemcpyHostToDevice,
                               s->run));
         HIP_OK(hipMemcpyAsync(s->new_d, s->new_h, sizeof(int32_t) * (size_t)nf, hipMemcpyHostToDevice, s->run));
-        decompose_batch_kernel<<<nf, decomp_threads(nf, units, s->c->cu), 0, s->run>>>(s->g, s->codes, s->cs, s->claims, s->rows, s->pairs,
+        decompose_batch_kernel<<<nf, DECOMP_THREADS, 0, s->run>>>(s->g, s->codes, s->cs, s->claims, s->rows, s->pairs,
                                                       (uint32_t)s->decomp_grid, s->bs, s->new_d, s->done_dev,
                                                       s->res_dev);
         HIP_OK(hipGetLastError());

@@ -24,17 +24,6 @@ inline int prefix_groups(int p, int W) { return p == 3 ? (W <= 2 ? 5 : 4) : W ==
 // is no part of it, so calls on codes of many lengths share one.
 typedef std::array<int, 6> RoundKey;
 
-// units of a set's pair table
-inline int table_units(int p, int k) { return k * (k - 1) / 2 * (p - 1); }
-// Threads of a batch's decomposition workgroups.  Eight wavefronts of its
-// registers leave a compute unit one workgroup, a single one three.  Codes that
-// outnumber the compute units go through faster three at a time, as long as one
-// wavefront builds the tables in a few steps (1024 codes of 20 to 30 columns,
-// up to 525 units: 103 us with eight, 69 with one, 4096 of them 376 and 181;
-// with 1500 units and more the same).
-constexpr int DECOMP_ALONE = 1000;
-inline int decomp_threads(int ncodes, int units, int cu) { return ncodes > cu && units <= DECOMP_ALONE ? 64 : DECOMP_THREADS; }
-
 // the columns processed per combination
 inline int processed_columns(int n, int k, bool skip) { return skip ? n - k : n; }
 

@@ -103,13 +103,6 @@ static void check_tables() {
     CHECK(tables(7, 56, 28) && !tables(7, 56, 28, false, false, 1000000) && !tables(3, 80, 40, false, false, 100000));
 }
 
-// a decomposition workgroup per code: eight wavefronts unless many small codes share the device
-static void check_threads() {
-    CHECK(decomp_threads(1, table_units(7, 5), 256) == 512 && decomp_threads(256, table_units(7, 5), 256) == 512);
-    CHECK(decomp_threads(257, table_units(7, 18), 256) == 64 && decomp_threads(257, table_units(7, 19), 256) == 512);
-    CHECK(decomp_threads(257, table_units(3, 32), 256) == 64 && decomp_threads(257, table_units(3, 33), 256) == 512);
-}
-
 // Tables of a batch: side by side, triples only within the budget; an
 // allocation that fails with them is tried without.
 static void check_layout() {
@@ -207,8 +200,6 @@ int main() {
     std::printf("OK rounds\n");
     check_tables();
     std::printf("OK tables\n");
-    check_threads();
-    std::printf("OK threads\n");
     check_layout();
     std::printf("OK layout\n");
     check_arena();

@@ -48,8 +48,7 @@ def test_new_lengths_allocate_nothing():
 
 @pytest.mark.gpu
 def test_many_small_codes():
-    """More codes than compute units, whose tables one wavefront builds: every
-    result is the kernel's without tables."""
+    """More codes than compute units: every result is the kernel's without tables."""
     import torch
     assert torch.cuda.is_available(), "no GPU visible"
     from paper_2603_29942_amd import bz
