@@ -244,22 +244,24 @@ using EnumFn = void (*)(CodeState *, const u32 *, const uint4 *, const u64 *, u6
 
 template <bool H>
 EnumFn enum_fn_h(int p, int W, int sch) {
+    constexpr int H3 = H ? hist_copies(3, true) : 0, N3 = H ? hist_copies(3, false) : 0;
+    constexpr int H7 = H ? hist_copies(7, true) : 0, N7 = H ? hist_copies(7, false) : 0;
     if (p == 3) {
         if (sch == NO_TABLE)
-            return W == 1 ? enum_kernel<3, 1, H, NO_TABLE> : W == 2 ? enum_kernel<3, 2, H, NO_TABLE>
-                 : W == 3 ? enum_kernel<3, 3, H, NO_TABLE> : enum_kernel<3, 4, H, NO_TABLE>;
-        return W == 1 ? enum_kernel<3, 1, H, 0> : W == 2 ? enum_kernel<3, 2, H, 0>
-             : W == 3 ? enum_kernel<3, 3, H, 0> : enum_kernel<3, 4, H, 0>;
+            return W == 1 ? enum_kernel<3, 1, N3, NO_TABLE> : W == 2 ? enum_kernel<3, 2, N3, NO_TABLE>
+                 : W == 3 ? enum_kernel<3, 3, N3, NO_TABLE> : enum_kernel<3, 4, N3, NO_TABLE>;
+        return W == 1 ? enum_kernel<3, 1, H3, 0> : W == 2 ? enum_kernel<3, 2, H3, 0>
+             : W == 3 ? enum_kernel<3, 3, H3, 0> : enum_kernel<3, 4, H3, 0>;
     }
     switch (sch) {
-    case 1: return enum_kernel<7, 1, H, 1>;
-    case 2: return enum_kernel<7, 1, H, 2>;
-    case 3: return enum_kernel<7, 2, H, 3>;
-    case 4: return enum_kernel<7, 2, H, 4>;
-    case 5: return W == 3 ? enum_kernel<7, 3, H, 5> : enum_kernel<7, 4, H, 5>;
+    case 1: return enum_kernel<7, 1, H7, 1>;
+    case 2: return enum_kernel<7, 1, H7, 2>;
+    case 3: return enum_kernel<7, 2, H7, 3>;
+    case 4: return enum_kernel<7, 2, H7, 4>;
+    case 5: return W == 3 ? enum_kernel<7, 3, H7, 5> : enum_kernel<7, 4, H7, 5>;
     default:
-        return W == 1 ? enum_kernel<7, 1, H, NO_TABLE> : W == 2 ? enum_kernel<7, 2, H, NO_TABLE>
-             : W == 3 ? enum_kernel<7, 3, H, NO_TABLE> : enum_kernel<7, 4, H, NO_TABLE>;
+        return W == 1 ? enum_kernel<7, 1, N7, NO_TABLE> : W == 2 ? enum_kernel<7, 2, N7, NO_TABLE>
+             : W == 3 ? enum_kernel<7, 3, N7, NO_TABLE> : enum_kernel<7, 4, N7, NO_TABLE>;
     }
 }
 // the enumeration kernel for a field, words per plane, table layout (or NO_TABLE) and histograms
@@ -275,8 +277,9 @@ hipError_t launch_enum(int p, bool hist_mode, int sch, int W, int grid, CodeStat
 constexpr int DEAL_GROUPS = 5;
 
 // Largest grid the enumeration kernel may get for (p, W, histograms, table
-// layout): unless it is made for more (DEAL_GROUPS), the schedule is dealt to exactly this many workgroups.
-int enum_grid(int p, bool hist, int sch, int W, int cu, int bpc) {
+// layout) of `groups` workgroups per compute unit at most: unless it is made for
+// more (DEAL_GROUPS), the schedule is dealt to exactly this many workgroups.
+int enum_grid(int p, bool hist, int sch, int W, int groups, int cu, int bpc) {
     static std::atomic<int> max_bpc[2][2][5][8];  // 0: not asked yet
     std::atomic<int> &m = max_bpc[p == 7][hist][W][sch + 1];
     int nb = m.load(std::memory_order_relaxed);
@@ -285,7 +288,7 @@ int enum_grid(int p, bool hist, int sch, int W, int cu, int bpc) {
             return -1;
         m.store(nb, std::memory_order_relaxed);
     }
-    if (sch == NO_TABLE) nb = std::min(nb, prefix_groups(p, W));
+    nb = std::min(nb, groups);
     return cu * (bpc < nb ? bpc : nb);
 }
 
@@ -546,7 +549,9 @@ int bz_min_distance_ex(int p, int n, int k, const uint8_t *G, int G_is_device, c
     const bool tables = o.pair_tables > 0 || (o.pair_tables == 0 && tables_by_default(p, n, k, W, o.histograms != 0, o.no_termination != 0,
                                                                                      o.check == BZ_CHECK_ROUND, max_cw, host_binom()));
     const int nsym = processed_columns(n, k, o.identity_skip != 0), sch = tables ? unit_scheme(p, nsym) : NO_TABLE;
-    const int grid = enum_grid(p, o.histograms != 0, sch, W, c->cu, bpc);
+    const int groups = tables ? 64 : prefix_groups(p, W, o.histograms != 0,
+                                                   o.no_termination ? std::max(spectrum_size(p, n, k, max_cw, host_binom()), (u64)1) : 0);
+    const int grid = enum_grid(p, o.histograms != 0, sch, W, groups, c->cu, bpc);
     if (grid < 1) return BZ_ERR_DEVICE;
     const u64 timeout = c->ticks_per_s * (u64)(o.wait_timeout_s > 0 ? o.wait_timeout_s : 120);
     // the grid the schedule is made for: the stages that fit it start at once,
@@ -1040,7 +1045,7 @@ extern "C" int bz_min_distance_noalloc(int p, int n, int k, const uint8_t *G, co
     const int WF = (n + 31) / 32;
     int W = o.identity_skip ? (n - k + 31) / 32 : WF;
     if (W < 1) W = 1;
-    const int grid = enum_grid(p, false, NO_TABLE, W, na.cu, o.blocks_per_cu ? o.blocks_per_cu : 64);
+    const int grid = enum_grid(p, false, NO_TABLE, W, prefix_groups(p, W, false, 0), na.cu, o.blocks_per_cu ? o.blocks_per_cu : 64);
     if (grid < 1) return BZ_ERR_DEVICE;
     const u64 timeout = na.ticks_per_s * (u64)(o.wait_timeout_s > 0 ? o.wait_timeout_s : 120);
     NoAllocScratch *ws = na.ws;

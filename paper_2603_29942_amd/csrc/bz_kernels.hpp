@@ -1081,22 +1081,25 @@ __device__ __forceinline__ void add_scaled(u32 (&x)[3][W], const u32 (&r)[3][W],
     }
 }
 
-// Eight copies of a wavefront's histogram, side by side: weights crowd into a
-// few bins, and with one copy most of the 64 lanes of an LDS atomic met on the
-// same few addresses, which it serves one after the other.
-constexpr int HIST_COPIES = 8;
-constexpr int HIST_DUMP = (BZ_MAX_N + 1) * HIST_COPIES;  // behind the bins: a word per lane for what is not counted
-constexpr int HIST_WORDS = HIST_DUMP + 64;               // of a wavefront
-template <int P, int W, bool HIST>
+// HIST: 0, or the copies of a wavefront's histogram, side by side.  Weights
+// crowd into a few bins, and with one copy most of the 64 lanes of an LDS atomic
+// meet on the same few addresses, which it serves one after the other: eight
+// copies, except for the F_3 kernel without tables, which gained nothing and
+// lost two of its five workgroups per compute unit to the space ([21, 14], every
+// round: 178 us with one copy, 214 with eight).
+constexpr int hist_copies(int p, bool tables) { return p == 3 && !tables ? 1 : 8; }
+constexpr int hist_dump(int copies) { return (BZ_MAX_N + 1) * copies; }  // behind the bins: a word per lane for what is not counted
+constexpr int hist_words(int copies) { return hist_dump(copies) + (copies > 1 ? 64 : 0); }  // of a wavefront
+template <int P, int W, int HIST>
 __device__ __forceinline__ void count_hist(u32 *lh, u32 wt) {
-    if constexpr (HIST) atomicAdd(&lh[wt * HIST_COPIES + (__lane_id() & (HIST_COPIES - 1))], 1u);
+    if constexpr (HIST != 0) atomicAdd(&lh[wt * HIST + (__lane_id() & (HIST - 1))], 1u);
 }
 
 // Weights of the combinations prefix + h * row for the p-1 prefixes of one
 // lane and every multiplier h: F_3 needs v + w and v - w (Sec. 4.2); F_7 needs
 // v +- 2^e w, e = 0, 1, 2, the scaling being a rotation of the planes.
 // Isometric additions (Sec. 4.3) give the nonzero masks, popcount the weights.
-template <int P, int W, int NA, bool HIST>
+template <int P, int W, int NA, int HIST>
 __device__ __forceinline__ void complete_all(const u32 (&Pv)[NA][3][W], const u32 (&anyP)[NA][W],
                                              const Row<W> &R, u32 &lmin, u32 *lh, u32 woff, u32 cap) {
 #pragma unroll
@@ -1109,7 +1112,7 @@ __device__ __forceinline__ void complete_all(const u32 (&Pv)[NA][3][W], const u3
                 ws += __builtin_popcount(f3_iso_sub(Pv[a][0][w], Pv[a][1][w], R.p[0][w], R.p[1][w]));
             }
             lmin = min(lmin, min(wa, ws));
-            if constexpr (HIST) {
+            if constexpr (HIST != 0) {
                 count_hist<P, W, HIST>(lh, min(wa + woff, cap));
                 count_hist<P, W, HIST>(lh, min(ws + woff, cap));
             }
@@ -1129,7 +1132,7 @@ __device__ __forceinline__ void complete_all(const u32 (&Pv)[NA][3][W], const u3
                     wa += __builtin_popcount(~(x0 & x1 & x2) & anyPR[w]);  // prefix + 2^e row
                 }
                 lmin = min(lmin, min(wa, ws));
-                if constexpr (HIST) {
+                if constexpr (HIST != 0) {
                     count_hist<P, W, HIST>(lh, min(wa + woff, cap));
                     count_hist<P, W, HIST>(lh, min(ws + woff, cap));
                 }
@@ -1141,7 +1144,7 @@ __device__ __forceinline__ void complete_all(const u32 (&Pv)[NA][3][W], const u3
 // Prefixes Q + h * Rs for the NA coefficients h = 1..NA of row s, then every
 // last row L = s+1..k-1 for all of them.  Returns the last rows combined
 // (each gives NA (p-1) combinations per lane).
-template <int P, int W, int NA, bool HIST>
+template <int P, int W, int NA, int HIST>
 __device__ __forceinline__ int extend_and_sweep(const u32 *__restrict__ rows, int j, int s, int k,
                                                 const u32 (&Q)[3][W], const Row<W> &Rs, u32 &lmin, u32 *lh,
                                                 u32 woff, u32 cap) {
@@ -1322,7 +1325,7 @@ __device__ __forceinline__ bool bound_pays(int nsym, int best) {
 // The bound is shared: see StageBound.
 // sweep_units for CT column tiles (32 bases each): their slots, weights and
 // whether a lane's column holds a base.
-template <int P, int W, int SCH, bool HIST, int CT>
+template <int P, int W, int SCH, int HIST, int CT>
 __device__ __forceinline__ void sweep_columns(const u32 *__restrict__ tab, int u0, int u1, int nsym,
                                               const u32 (&pl)[CT][unit_pieces(SCH, W)],
                                               const u32 (&nz)[CT][unit_pieces(SCH, W)],
@@ -1388,13 +1391,13 @@ __device__ __forceinline__ void sweep_columns(const u32 *__restrict__ tab, int u
     // the lane's own word behind the bins (one word for all lanes would be
     // served lane by lane)
     [[maybe_unused]] float hist0[CT];
-    if constexpr (HIST) {
+    if constexpr (HIST != 0) {
 #pragma unroll
         for (int ct = 0; ct < CT; ct++)
-            hist0[ct] = in[ct] ? (float)(((wx[ct] + woff) * HIST_COPIES + (u32)(lane & (HIST_COPIES - 1))) * 4) : -8.0f * MASKED;
+            hist0[ct] = in[ct] ? (float)(((wx[ct] + woff) * HIST + (u32)(lane & (HIST - 1))) * 4) : -8.0f * MASKED;
     }
     auto count = [&](int ct, float v) {
-        const u32 at = min((u32)fmaf(v, -2.0f * HIST_COPIES, hist0[ct]), (u32)(HIST_DUMP + lane) * 4u);
+        const u32 at = min((u32)fmaf(v, -2.0f * HIST, hist0[ct]), (u32)(hist_dump(HIST) + lane) * 4u);
         __hip_atomic_fetch_add((lds_u32 *)((__attribute__((address_space(3))) char *)(lds_u32 *)lh + at), 1u,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
@@ -1438,7 +1441,7 @@ __device__ __forceinline__ void sweep_columns(const u32 *__restrict__ tab, int u
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int ct = 0; ct < CT; ct++) {
-                if constexpr (HIST) {
+                if constexpr (HIST != 0) {
 #pragma unroll
                     for (int r = 0; r < 16; r++) {
                         count(ct, e[ct][r] + o[ct][r]);
@@ -1516,7 +1519,7 @@ __device__ __forceinline__ void sweep_columns(const u32 *__restrict__ tab, int u
             for (int ct = 0; ct < CT; ct++) signed_operands(pl[ct], nz[ct], sg[ct], bf[ct], bo[ct]);
             tiles([&](int t, const u32 (&rec)[REC]) {
                 signed_sums(t, rec, bf, bo, [&](int ct, const v16f_t &d, const v16f_t &o) {
-                    if constexpr (HIST) {
+                    if constexpr (HIST != 0) {
 #pragma unroll
                         for (int r = 0; r < 16; r++) {
                             count(ct, d[r] + o[r]);
@@ -1616,7 +1619,7 @@ __device__ __forceinline__ void sweep_columns(const u32 *__restrict__ tab, int u
     if constexpr (P == 7 && !HIST) bound.offer(w + woff, known);
 }
 
-template <int P, int W, int SCH, bool HIST>
+template <int P, int W, int SCH, int HIST>
 __device__ __forceinline__ void sweep_units(const u32 *__restrict__ tab, int u0, int u1, int nsym,
                                             const u32 (&Q)[3][W], int ncol, u32 &lmin, StageBound bound, u32 *lh,
                                             u32 woff, u32 cap) {
@@ -1694,7 +1697,7 @@ __device__ __forceinline__ u64 binom_at(const u64 *sbin, const u64 *__restrict__
 
 // Prefixes Q + a R for a = a0 .. a0+NA-1 and their nonzero masks, then every
 // multiple of the last row T through complete_all.
-template <int P, int W, int NA, bool HIST>
+template <int P, int W, int NA, int HIST>
 __device__ __forceinline__ void prefixes_then_complete(const u32 (&Q)[3][W], const Row<W> &R, int a0, const Row<W> &T,
                                                        u32 &lmin, u32 *lh, u32 woff, u32 cap) {
     u32 Pv[NA][3][W], anyP[NA][W];
@@ -1716,7 +1719,7 @@ __device__ __forceinline__ void prefixes_then_complete(const u32 (&Q)[3][W], con
 // prefixes, one at a time to keep the registers in check), the top row every
 // multiplier through complete_all.
 // Adds the combinations completed to the lane's count ncomb.
-template <int P, int W, int G, bool HIST>
+template <int P, int W, int G, int HIST>
 __device__ __forceinline__ void run_subset(const u32 *__restrict__ rows, LdsRows lrows, int j,
                                            const int (&r)[G], u32 &lmin, u32 &ncomb, u32 *lh, u32 woff, u32 cap) {
     constexpr int NA = 1;  // one prefix at a time (registers)
@@ -1747,7 +1750,7 @@ __device__ __forceinline__ void run_subset(const u32 *__restrict__ rows, LdsRows
 
 // g <= SUBSET_G: one item per lane (a row, a pair of rows, a triple; colex
 // rank task * 64 + lane).  Adds the combinations the lane evaluated to lcnt.
-template <int P, int W, bool HIST>
+template <int P, int W, int HIST>
 __device__ __forceinline__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
                                const u64 *sbin, const u64 *__restrict__ gbin, u64 task, u32 &lmin, u64 &lcnt,
                                u32 *lh, u32 woff, u32 cap) {
@@ -1761,7 +1764,7 @@ __device__ __forceinline__ void run_small_task(int g, int k, int j, const u32 *_
 #pragma unroll
             for (int w = 0; w < W; w++) wt += __builtin_popcount(r.any[w]);
             lmin = min(lmin, wt);
-            if constexpr (HIST) count_hist<P, W, HIST>(lh, min(wt + woff, cap));
+            if constexpr (HIST != 0) count_hist<P, W, HIST>(lh, min(wt + woff, cap));
             lcnt += 1;
         }
         return;
@@ -1816,7 +1819,7 @@ __device__ __forceinline__ void run_small_task(int g, int k, int j, const u32 *_
 // SCH: the layout of the set's pair table (unit_scheme), or NO_TABLE: the
 // prefixes are built here.  bound, seen (thread 0): F_7 with a table, see StageBound.
 constexpr int NO_TABLE = -1;
-template <int P, int W, bool HIST, int SCH>
+template <int P, int W, int HIST, int SCH>
 __device__ __forceinline__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
                               const u32 *__restrict__ ptab, uint32_t triple_off, const u64 *sbin,
                               const u64 *__restrict__ gbin, const QEntry *qtab, int nq, u64 task, StageBound bound, int seen, int nsym, u32 &lmin, u64 &lcnt, u32 *lh,
@@ -1991,7 +1994,7 @@ __device__ void run_checker(CodeState *cs, const StageDesc *sdesc, int ns, const
 // SCH: the layout of the launch's pair tables (the base rounds take their two
 // highest rows from them; no prefix path is compiled), or NO_TABLE.
 // (workgroups per compute unit: what the registers allow without spills)
-template <int P, int W, bool HIST, int SCH>
+template <int P, int W, int HIST, int SCH>
 __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2) void enum_kernel(CodeState *cs, const u32 *__restrict__ rows,
                                                    const uint4 *__restrict__ pairs, const u64 *__restrict__ gbin,
                                                    u64 *__restrict__ hist, EnumArgs ea) {
@@ -2002,7 +2005,7 @@ __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2
     __shared__ u64 sbin[BZ_MAX_K * BIN_I];
     __shared__ StageDesc sdesc[BZ_MAX_STAGES];
     __shared__ QEntry qtab[BZ_MAX_K];
-    __shared__ u32 lhist[HIST ? WAVES_PER_GROUP * HIST_WORDS : 1];
+    __shared__ u32 lhist[HIST ? WAVES_PER_GROUP * hist_words(HIST) : 1];
     __shared__ u32 red_min[WAVES_PER_GROUP];
     __shared__ u64 red_cnt[WAVES_PER_GROUP];
     __shared__ u32 s_best;  // see StageBound
@@ -2057,7 +2060,7 @@ __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2
     const int ns = uni(ns0);
     const bool skip = (ea.flags & FLAG_SKIP) != 0;
     u64 *wake = &cs->wake[b % WAKE_COPIES][0];
-    u32 *lh = HIST ? &lhist[wid * HIST_WORDS] : nullptr;
+    u32 *lh = HIST ? &lhist[wid * hist_words(HIST)] : nullptr;
     const u32 cap = (u32)n;
     const LdsRows lrows{lrow_buf, LSETS};  // (filled before the first barrier)
     // the pool (see pool_stages): its stages complete when all their tiles
@@ -2088,8 +2091,8 @@ __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2
         const u64 task = tile * WAVES_PER_GROUP + (u64)wid;
         if (task >= tasks) return;  // a missing task only happens in the last tile
         const u32 woff = skip ? (u32)sg : 0u;
-        if constexpr (HIST) {
-            for (int w = lane; w < (n + 1) * HIST_COPIES; w += 64) lh[w] = 0;
+        if constexpr (HIST != 0) {
+            for (int w = lane; w < (n + 1) * HIST; w += 64) lh[w] = 0;
         }
         if (sg > SUBSET_G) {
             const int sj = uni(sd.j - 1);
@@ -2100,11 +2103,11 @@ __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2
         }
         else
             run_small_task<P, W, HIST>(sg, k, uni(sd.j - 1), rows, lrows, sbin, gbin, task, lmin, lcnt, lh, woff, cap);
-        if constexpr (HIST) {
+        if constexpr (HIST != 0) {
             for (int w = lane; w <= n; w += 64) {
                 u32 c = 0;
 #pragma unroll
-                for (int i = 0; i < HIST_COPIES; i++) c += lh[w * HIST_COPIES + i];
+                for (int i = 0; i < HIST; i++) c += lh[w * HIST + i];
                 if (c) atomicAdd((unsigned long long *)&hist[(size_t)s * (BZ_MAX_N + 1) + w], (unsigned long long)c);
             }
         }
@@ -2125,7 +2128,7 @@ __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2
             red_min[wid] = lmin;
             red_cnt[wid] = lcnt;
         }
-        if constexpr (HIST) drain_vmem();  // this wave's histogram atomics are performed
+        if constexpr (HIST != 0) drain_vmem();  // this wave's histogram atomics are performed
         __syncthreads();
         if (wid == 0) {
             uint32_t done = 0;

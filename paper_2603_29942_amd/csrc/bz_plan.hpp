@@ -17,7 +17,15 @@ namespace bz {
 // at once, whose work is thrown away when an earlier one ends the run (F_7
 // without tables, [48, 12] 66.8 us with three, 89.0 with four; [66, 11] 81.4
 // and 92.0; [108, 9], four words, 131.1 with two, 136.6 with three).
-inline int prefix_groups(int p, int W) { return p == 3 ? (W <= 2 ? 5 : 4) : W == 1 ? 4 : W == 2 ? 3 : 2; }
+// With histograms over F_3, three measured better in the runs of up to two
+// words that end early ([24, 16] 112 us with five, 88 with three; of three words
+// [114, 19] took 174 with four, 219 with three) and in spectra of more than
+// 2 10^8 combinations ([54, 18] 4622 and 3815, while [30, 15] took 424 and 447).
+// spectrum: its combinations, 0 for a run that ends early.
+inline int prefix_groups(int p, int W, bool hist, u64 spectrum) {
+    if (p == 3 && hist && (spectrum ? spectrum > 200000000 : W <= 2)) return 3;
+    return p == 3 ? (W <= 2 ? 5 : 4) : W == 1 ? 4 : W == 2 ? 3 : 2;
+}
 
 // What a plain call's round table depends on (fill_round_table, take_triples):
 // p, k, words per plane, the grid of the schedule, tables, triples.  The length
@@ -158,6 +166,12 @@ inline int expected_distance(int p, int n, int k) {
 // information sets of a random code
 inline int expected_sets(int n, int k) { return n / k + (n % k != 0); }
 
+// Combinations of a run without termination, within the work limit.
+inline u64 spectrum_size(int p, int n, int k, u64 max_codewords, const u64 *binom) {
+    u64 sum = 0;
+    for (int g = 1; g <= k; g++) sum = sat_add(sum, sat_mul(round_codewords(p, k, g, binom), (u64)expected_sets(n, k)));
+    return std::min(sum, max_codewords);
+}
 // The last round that a call on a random [n, k] code is expected to run: the
 // one whose bound reaches the expected distance (round g raises it to about
 // (g + 1) n / k), or every round without termination, and none past the work

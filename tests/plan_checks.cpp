@@ -15,14 +15,21 @@ using namespace bz;
         }                                                                \
     } while (0)
 
+static u64 BINOM[65 * 65];
+constexpr u64 NO_LIMIT = 1ull << 44;
+
 // the kernel without tables is dealt to the workgroups that it was measured with
 static void check_groups() {
     const int f3[] = {5, 5, 4, 4}, f7[] = {4, 3, 2, 2};
-    for (int W = 1; W <= 4; W++) CHECK(prefix_groups(3, W) == f3[W - 1] && prefix_groups(7, W) == f7[W - 1]);
+    for (int W = 1; W <= 4; W++) {
+        CHECK(prefix_groups(3, W, false, 0) == f3[W - 1] && prefix_groups(7, W, false, 0) == f7[W - 1]);
+        CHECK(prefix_groups(3, W, true, 100000000) == f3[W - 1] && prefix_groups(3, W, true, 300000000) == 3);
+        CHECK(prefix_groups(3, W, true, 0) == (W <= 2 ? 3 : 4) && prefix_groups(7, W, true, 0) == f7[W - 1]);
+    }
+    // 3^k - 1 over 2 combinations per set
+    CHECK(spectrum_size(3, 28, 14, NO_LIMIT, BINOM) == 4782968 && spectrum_size(3, 28, 14, 1000, BINOM) == 1000);
 }
 
-static u64 BINOM[65 * 65];
-constexpr u64 NO_LIMIT = 1ull << 44;
 static bool plain_triples(int p, int n, int k, bool no_term, u64 limit) {
     const int W = (n - k + 31) / 32;
     const int last = expected_rounds(p, n, k, no_term, limit, BINOM);
