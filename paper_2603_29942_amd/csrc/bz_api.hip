@@ -41,7 +41,7 @@ struct DevCtx {
     uint8_t *g_buf = nullptr;
     CodeState *cs = nullptr;
     u32 *rows = nullptr;
-    uint4 *pairs = nullptr;  // the pair tables of the sets (pair_table_units per set)
+    uint4 *pairs = nullptr;  // the tables of the sets (set_table_size)
     u64 *binom = nullptr;
     u64 *hist = nullptr;
     CodeResult *host_res = nullptr;

@@ -4,16 +4,23 @@
 //                     planes, computes the information-set decomposition
 //                     Gamma_1..Gamma_m by Gauss-Jordan on bit-sliced rows (one
 //                     row per lane), packs each Gamma_j for the enumeration
-//                     (with its table of pair sums, see pair_units), and
-//                     writes the stage schedule and the initial completion state.
+//                     (with tables: its pair sums as matrix operands, see
+//                     bz_units.hpp, built by the workgroup's other wavefronts),
+//                     and writes the stage schedule and the initial completion state.
+//   triple_kernel     the tables of three-row sums, where rounds take them.
 //   enum_kernel       persistent: every workgroup walks the stages in order and
 //                     takes its share of each stage's tiles; a lane builds the
-//                     exact prefix sums of its item in registers (the two
-//                     highest rows from the pair table when there is one),
-//                     finishes every combination with the isometric addition,
-//                     takes the weight by popcount and min-reduces it.  The workgroup that
-//                     completes a stage last applies the L >= U test; workgroups
-//                     that already moved on to later stages stop when it holds.
+//                     exact sum of its base in registers.  With tables, 64
+//                     bases and 32 table entries at a time meet in matrix
+//                     instructions, which give the weights as inner products
+//                     (sweep_columns).  Without, the lane finishes every
+//                     combination with the isometric addition and takes the
+//                     weight by popcount.  Weights are min-reduced.  The
+//                     workgroup that completes a stage last applies the L >= U
+//                     test; workgroups that already moved on to later stages
+//                     stop when it holds.
+//   enum_batch_kernel the same sweeps for many codes, work handed out by code,
+//                     stage and part.
 //
 // Paper: Hernando & Quintana-Orti, arXiv 2603.29942 (Sec. 2-4, Algorithm 6).
 #pragma once
@@ -293,7 +300,7 @@ __device__ __forceinline__ void build_pair_table(uint4 *ptab, int k, int W, int 
 }
 
 // The triple tables of a code's sets, one unit per thread and step.  A table
-// has 36 (F_7) or 4 (F_3) units per triple, up to 130000: a launch of its own
+// has 36 (F_7) or 4 (F_3) units per triple, up to 166656 (F_3, 64 rows): a launch of its own
 // spreads it over the chip (blockIdx.x of gridDim.x workgroups per code).
 template <int P, int W, int SCH>
 __device__ __forceinline__ void build_triples(u32 *__restrict__ tab, int k, const uint4 *prow) {

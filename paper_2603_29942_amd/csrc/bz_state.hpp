@@ -21,21 +21,13 @@ typedef uint64_t u64;
 constexpr int ROW_WORDS = 16;
 constexpr uint64_t DEFAULT_LIMIT = 1ull << 44;
 
-// Pair tables: for each information set, the exact sums of two of its rows,
-// R_s + c R_L for s < L and every c in F_p^* up to the sign that the isometric
-// subtraction supplies (Sec. 4.2-4.3): F_3 keeps R_s + R_L and R_s - R_L
-// (planes 0 and 1 of each, one 16-byte unit per word), F_7 keeps c = 1..6 (six
-// units per pair, each word planes 0..2 and their OR).  A combination
-// base + h_s R_s + h_L R_L equals base + h_s T with T = R_s + (h_L / h_s) R_L,
-// so a lane with an exact base finishes all (p-1)^2 multipliers of the pair
-// from these units without an exact addition of its own.  Pairs are stored
-// row-major in s (all L > s of row s, ascending), so the pairs of a run of
-// rows s form one contiguous range.  Unit u of pair e, word w: at (e * units +
-// u) * W + w, in units of 16 bytes.
-BZ_HD int pair_units(int p) { return p == 3 ? 1 : p - 1; }
-// pairs (s', L) with s' < s: those of rows 0 .. s-1
+// Pairs of rows s < L.  A combination base + h_s R_s + h_L R_L equals base +
+// h_s T with T = R_s + (h_L / h_s) R_L, so that the tables of such sums
+// (bz_units.hpp) save the exact additions of the two highest rows.  In
+// row-major order (all L > s of row s, ascending) the pairs of a run of rows s
+// are one range:
+// pairs (s', L) with s' < s, those of rows 0 .. s-1
 BZ_HD u64 pair_first(int s, int k) { return (u64)s * (u64)(k - 1) - (u64)s * (u64)(s - 1) / 2; }
-BZ_HD u64 pair_table_units(int p, int k, int W) { return (u64)k * (u64)(k - 1) / 2 * (u64)pair_units(p) * (u64)W; }
 // pair e = (s, s + 1 + rem) in that order: advance (s, rem) by d pairs
 BZ_HD void pair_advance(int k, int &s, int &rem, int d) {
     rem += d;
@@ -44,9 +36,11 @@ BZ_HD void pair_advance(int k, int &s, int &rem, int d) {
         s++;
     }
 }
-// units past the last table of a buffer that a sweep's group of loads may
-// read (a group of UR units of W words, at most 8 of 16 bytes, is loaded whole)
-constexpr int PAIR_PAD_UNITS = 16;
+// Distinct sums of a pair up to the sign that an isometric subtraction
+// supplies (Sec. 4.2-4.3): R_s + R_L and R_s - R_L in one over F_3, c = 1..6 over F_7;
+// and words of them per set.  The host checks count the coefficient pairs with these.
+BZ_HD int pair_units(int p) { return p == 3 ? 1 : p - 1; }
+BZ_HD u64 pair_table_units(int p, int k, int W) { return (u64)k * (u64)(k - 1) / 2 * (u64)pair_units(p) * (u64)W; }
 // information sets a decomposition can produce: every full-rank set takes k
 // unused columns and the first deficient one ends it
 BZ_HD int pair_sets(int n, int k) { return n / k + 1 < BZ_MAX_M ? n / k + 1 : BZ_MAX_M; }
@@ -261,8 +255,8 @@ BZ_HD int bound_c(int g, int k, int kj) {
 constexpr uint32_t DEFAULT_SWEEP_OPS = BZ_SWEEP_OPS;
 // Task size of the plain path: F_3 tasks of 3000 operations (the F_3 [72,36]
 // codes run 3% faster than with 4500, F_7 [48,24] 4% slower); F_7 tasks of
-// 6000 (with the pair tables the F_7 [48,24] codes run 2% faster than with
-// 4500 or 9000, 18% slower with 3000).
+// 6000 (taken when F_7 calls swept tables of bit planes: [48,24] 2% faster than
+// with 4500 or 9000, 18% than with 3000).  The kernel without tables takes these.
 BZ_HD uint32_t plain_sweep_ops(int p) { return p == 3 ? 3000u : 6000u; }
 // With tables, twice that: a matrix sweep takes a quarter of the time and its
 // set-up the same (per call, 1x -> 2x -> 4x: [48,24] F_7 131 -> 126 -> 134 us,

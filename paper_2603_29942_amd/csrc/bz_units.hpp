@@ -49,9 +49,8 @@ constexpr int unit_pieces(int sch, int W) {
 // 32-bit words of a unit that one lane (one half) holds: its planes, then its signs
 constexpr int unit_rec_words(int sch, int W) { return sch == 0 ? 2 * ((W + 1) / 2) : sch == 3 || sch == 5 ? 8 : 4; }
 
-// units of a pair: R_s + c R_L for c in F_p^*
-BZ_HD int units_per_pair(int p) { return p - 1; }
-// units of a pair table and the tiles of 32 that hold them
+// units of a pair table (R_s + c R_L for s < L and every c in F_p^*) and the
+// tiles of 32 that hold them
 BZ_HD u64 table_tiles(int p, int k) { return ((u64)k * (u64)(k - 1) / 2 * (u64)(p - 1) + 31) / 32; }
 // 16-byte words of a pair table over nsym columns: per tile, the records of 64 lanes
 BZ_HD u64 unit_table_size(int p, int k, int nsym) {
