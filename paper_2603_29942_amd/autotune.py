@@ -8,28 +8,28 @@ last-row sweeps add up to about `sweep_ops` VALU operations; small values cut
 stages into many short tasks (better balance, more per-task decoding), large
 values into few long ones.  The best value depends on the field and on W (the
 words per plane a combination takes), so codes are grouped by (p, W) and each
-group is timed as its own batch for every candidate (the smallest size within
-1% of the fastest is taken); then the grid shape is timed on the whole sample
-with the chosen sizes (the most workgroups per CU within 1% of the fastest is
-taken).  Results never depend on
-these knobs (the tests check it); only time does.
+group is timed as its own batch for every candidate (pick_ops says which is
+taken); then the grid shape is timed on the whole sample with the chosen sizes.
+Results never depend on these knobs (the tests check it); only time does.
 
 The table is JSON: {"sweep_ops": {"p,W": ops, ...}, "blocks_per_cu": b,
 "kernel_source_hash": h, ...}; it is used only while the kernel sources hash
 to h (a table taken on other kernels is ignored, and load_checked says so).
 The persistent batched kernel fits two workgroups per compute unit for W <= 2
-(its registers); larger candidates are clamped to that by the library.
+and one beyond (its registers); the library clamps what is asked for to that.
 """
 import argparse
 import hashlib
 import json
+import math
 import os
 import time
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "tuning_gfx950.json")
-SWEEP_CANDIDATES = (1500, 3000, 6000, 12000, 24000, 48000, 96000, 192000)
-BPC_CANDIDATES = (1, 2, 3, 4, 5, 6)
+DEFAULT_OPS = 18000  # the library's own size
+SWEEP_CANDIDATES = (1500, 3000, 6000, 12000, DEFAULT_OPS, 24000, 48000, 96000, 192000)
+BPC_CANDIDATES = (0, 1)  # 0: as many as fit, two with the kernel of up to two words
 KERNEL_SOURCES = ("bz_kernels.hpp", "bz_arith.hpp", "bz_state.hpp", "bz_units.hpp")
 
 
@@ -80,7 +80,17 @@ def _time_batch(bz, codes, dev, reps, **kw):
     return best
 
 
-def tune(codes, reps=2, sweep_candidates=SWEEP_CANDIDATES, bpc_candidates=BPC_CANDIDATES, log=print):
+def pick_ops(row, whole):
+    """The size for a group from its times (size -> ms): the one nearest the
+    default whose time is within 1% of the fastest, or within half a percent of
+    the whole sample's time (whole, ms).  The times are flat over a wide range
+    and a small group's are noise; sizes near the default are the ones the rest of
+    the library is measured with."""
+    limit = min(row.values()) + max(0.01 * min(row.values()), 0.005 * whole)
+    return min((o for o, t in row.items() if t <= limit), key=lambda o: (abs(math.log(o / DEFAULT_OPS)), o))
+
+
+def tune(codes, reps=5, sweep_candidates=SWEEP_CANDIDATES, bpc_candidates=BPC_CANDIDATES, log=print):
     import torch
     from . import bz
     dev = torch.device("cuda:0")
@@ -94,25 +104,23 @@ def tune(codes, reps=2, sweep_candidates=SWEEP_CANDIDATES, bpc_candidates=BPC_CA
         row = {}
         for ops in sweep_candidates:
             row[ops] = _time_batch(bz, cs, dev, reps, sweep_ops=ops)
-        # the smallest size within 1% of the fastest: the times are flat over a
-        # wide range, and smaller parts let a serving round yield sooner
-        tmin = min(row.values())
-        best = min(o for o, t in row.items() if t <= 1.01 * tmin)
-        chosen[key] = best
-        timings[f"{key[0]},{key[1]}"] = {str(o): round(t, 4) for o, t in row.items()}
-        log(f"  p={key[0]} W={key[1]} ({len(cs)} codes): " +
-            " ".join(f"{o}:{t:.3f}ms" for o, t in row.items()) + f" -> {best}")
+        timings[key] = row
+        log(f"  p={key[0]} W={key[1]} ({len(cs)} codes): " + " ".join(f"{o}:{t:.3f}ms" for o, t in row.items()))
+    whole = sum(min(row.values()) for row in timings.values())
+    for key, row in timings.items():
+        chosen[key] = pick_ops(row, whole)
+        log(f"  p={key[0]} W={key[1]} -> {chosen[key]}")
     fn = (lambda p, W: chosen.get((p, W), 0))
     bpc_t = {b: _time_batch(bz, codes, dev, reps, sweep_ops=fn, blocks_per_cu=b) for b in bpc_candidates}
-    # the most workgroups per CU within 1% of the fastest: the 256-code sample
-    # cannot tell counts that close apart, and on the full 512-code batch
-    # five per CU ran 2.3% faster than four (interleaved runs of one build)
+    # as many as fit (0), or the most, unless fewer are over 1% faster
     tmin = min(bpc_t.values())
-    bpc = max(b for b, t in bpc_t.items() if t <= 1.01 * tmin)
+    bpc = min((b for b, t in bpc_t.items() if t <= 1.01 * tmin), key=lambda b: (b != 0, -b))
     log("  blocks_per_cu: " + " ".join(f"{b}:{t:.3f}ms" for b, t in bpc_t.items()) + f" -> {bpc}")
     return {"sweep_ops": {f"{p},{W}": ops for (p, W), ops in sorted(chosen.items())},
             "blocks_per_cu": bpc,
-            "timings_ms": {"sweep_ops": timings, "blocks_per_cu": {str(b): round(t, 4) for b, t in bpc_t.items()}},
+            "timings_ms": {"sweep_ops": {f"{p},{W}": {str(o): round(t, 4) for o, t in row.items()}
+                                         for (p, W), row in timings.items()},
+                           "blocks_per_cu": {str(b): round(t, 4) for b, t in bpc_t.items()}},
             "sample": f"{len(codes)} codes of the mixed batch distribution",
             "device": torch.cuda.get_device_properties(0).name}
 
@@ -121,7 +129,7 @@ def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--seed", type=int, default=100)
     ap.add_argument("--count", type=int, default=256)
-    ap.add_argument("--reps", type=int, default=2)
+    ap.add_argument("--reps", type=int, default=5)
     ap.add_argument("--out", default=TABLE)
     args = ap.parse_args()
     from . import synth

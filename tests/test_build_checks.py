@@ -42,3 +42,14 @@ def test_spills_calls_and_scratch_are_refused(remarks, listing):
 
 def test_the_function_is_named():
     assert list(outside_registers(LISTING.format(a="", b="\tscratch_store_dword off, v40, s33"))) == ["helper"]
+
+
+def test_autotuner_picks_no_noise():
+    """Flat times and small groups keep the default size; a real gain is taken,
+    at the nearest size that has it."""
+    from paper_2603_29942_amd.autotune import DEFAULT_OPS, pick_ops
+    flat = {1500: 0.430, 12000: 0.457, DEFAULT_OPS: 0.455, 192000: 0.429}
+    assert pick_ops(flat, 36.0) == DEFAULT_OPS  # 6% of 0.4 ms in a sample of 36 ms
+    assert pick_ops(flat, 0.43) == 192000  # the group is the sample; 1500 is further off: a factor of 12, not 10.7
+    assert pick_ops({6000: 7.7, DEFAULT_OPS: 6.9, 24000: 6.85, 96000: 6.84}, 7.0) == DEFAULT_OPS
+    assert pick_ops({6000: 7.7, DEFAULT_OPS: 6.9, 48000: 6.3, 96000: 6.28, 192000: 6.27}, 7.0) == 48000
