@@ -7,8 +7,8 @@ random codes of mixed field and size (half F_3, half F_7, n uniform in
 [30, 90], rate 1/2 or 1/3; F_7 n <= 56 at rate 1/2 and n <= 63 at rate 1/3),
 their generators already resident in GPU memory: one information-set
 decomposition launch and one persistent enumeration launch compute every
-code's minimum distance (the stages of Algorithm 6 with the isometric last
-addition, popcount weights, min-reduce and the L >= U test).  The same codes
+code's minimum distance (the stages of Algorithm 6, the weights by isometric
+additions or as inner products, min-reduce and the L >= U test).  The same codes
 then run on the plain path (one call per code), and the two are compared:
 combinations evaluated per second and each code's time to d (p50 / p99).
 
@@ -40,10 +40,10 @@ sys.path.insert(0, ROOT)
 # CU per clock against 128 and 64).
 FULL_RATE_TOPS = 256 * 128 * 2.4e9 / 1e12
 HALF_RATE_TOPS = 256 * 64 * 2.4e9 / 1e12
-# The sweeps take their weights from products on the matrix unit, so the vector
-# unit's ceiling is a yardstick that they may pass.
-MATRIX_NOTE = ("the sweeps run on the matrix unit, so frac is the speed over the vector unit's ceiling for the "
-               "bit-sliced method, not a utilisation")
+# The sweeps with tables take the weights from FP4 products: a 32 x 32 x 64
+# instruction is 131072 operations in 32 cycles of one of 1024 SIMDs (one
+# wavefront alone measured 37 cycles at 2.4 GHz).
+MATRIX_TFLOPS = 1024 * 131072 / 32 * 2.4e9 / 1e12
 CONFIG_NAMES = {1: "F_3 [40,10]", 2: "F_3 [72,36]", 3: "F_7 [48,24]"}
 
 
@@ -70,6 +70,29 @@ def peak_seconds_per_codeword(p, W):
 def peak_tops(p, W):
     """Peak algorithmic operations per second for the op mix of (p, W), in T/s."""
     return ops_per_codeword(p, W) / peak_seconds_per_codeword(p, W) / 1e12
+
+
+def matrix_flops(p, nsym):
+    """Operations of the matrix unit per combination over nsym processed columns.
+    F_3: two inner products (positions where both symbols are nonzero, and their
+    signed agreement) give the weights of two combinations: one of 2 nsym
+    operations each.  F_7: three inner products over the three planes of the
+    exponents bound six combinations' weights: 3 x 2 x 3 nsym / 6.  The exact
+    weights of the tiles that pass the bound, the units' own weights and unused
+    columns are not counted."""
+    return 2 * nsym if p == 3 else 3 * nsym
+
+
+MATRIX_NOTE = (f"FP4 matrix instructions, 131072 operations in 32 cycles on 1024 SIMDs at 2.4 GHz; operations per "
+               f"combination: 2 columns (F_3), 3 columns (F_7), the n-k processed ones")
+
+
+def matrix_roofline(kernel, flops, seconds, workload, launches):
+    achieved = flops / seconds / 1e12
+    return {"kernel": kernel, "bound": "mfma", "achieved": achieved, "peak": MATRIX_TFLOPS,
+            "unit": "TFLOP/s (FP4 products, algorithmic)", "frac": achieved / MATRIX_TFLOPS,
+            "traffic": traffic_for(kernel, workload), "peak_note": MATRIX_NOTE,
+            "avg_launch_ms": seconds * 1e3 / launches}
 
 
 def pct(xs, q):
@@ -341,8 +364,17 @@ def bench_plain(cfg, K, Wm, blocks_per_cu=0):
     W = (n - k + 31) // 32  # words per plane over the non-pivot columns
     opc = ops_per_codeword(p, W)
     total_cw = sum(cws)
-    achieved = total_cw * opc / (sum(enum_ms) / 1e3) / 1e12
-    peak = peak_tops(p, W)
+    if all(r.info & bz.INFO_PAIRS for r in outs):
+        roofline = matrix_roofline("enum_kernel", total_cw * matrix_flops(p, n - k), sum(enum_ms) / 1e3,
+                                   f"f{p}_{n}_{k}", K)
+    else:
+        achieved, peak = total_cw * opc / (sum(enum_ms) / 1e3) / 1e12, peak_tops(p, W)
+        roofline = {"kernel": "enum_kernel", "bound": "alu", "achieved": achieved, "peak": peak,
+                    "unit": "T int32 VALU lane-ops/s (algorithmic)", "frac": achieved / peak,
+                    "traffic": traffic_for("enum_kernel", f"f{p}_{n}_{k}"),
+                    "ops_per_codeword": opc, "op_mix": {"bitwise": op_mix(p, W)[0], "popcount_min": op_mix(p, W)[1]},
+                    "peak_note": f"bitwise at {FULL_RATE_TOPS:.1f} T/s, popcount and min at {HALF_RATE_TOPS:.1f} T/s",
+                    "avg_launch_ms": sum(enum_ms) / K}
     return {
         "workload": f"one random {CONFIG_NAMES[cfg]} code per step (seeds 0..{K - 1}), plain path, "
                     "generator resident on the GPU",
@@ -353,13 +385,7 @@ def bench_plain(cfg, K, Wm, blocks_per_cu=0):
         "codewords_per_step": {"mean": total_cw / K, "min": min(cws), "max": max(cws)},
         "d": [r.d for r in outs],
         "kernel_ms_per_step": {"decompose": sum(dec_ms) / K, "enum": sum(enum_ms) / K},
-        "roofline": {"kernel": "enum_kernel", "bound": "alu", "achieved": achieved, "peak": peak,
-                     "unit": "T int32 VALU lane-ops/s (algorithmic)", "frac": achieved / peak,
-                     "traffic": traffic_for("enum_kernel", f"f{p}_{n}_{k}"),
-                     "ops_per_codeword": opc, "op_mix": {"bitwise": op_mix(p, W)[0], "popcount_min": op_mix(p, W)[1]},
-                     "peak_note": f"bitwise at {FULL_RATE_TOPS:.1f} T/s, popcount and min at {HALF_RATE_TOPS:.1f} T/s; "
-                                  + MATRIX_NOTE,
-                     "avg_launch_ms": sum(enum_ms) / K},
+        "roofline": roofline,
     }
 
 
@@ -598,20 +624,15 @@ def bench_batch(args):
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
     cws = [sum(r.codewords_total for _, r in res) for res in results]
-    ops_total, ideal_s = 0.0, 0.0
+    flops = 0.0
     for (buf, descs), res in zip(packed, results):
         for i, (_, r) in enumerate(res):
-            d = descs[i]
-            W = max((d.n - d.k + 31) // 32, 1)
-            ops_total += r.codewords_total * ops_per_codeword(d.p, W)
-            ideal_s += r.codewords_total * peak_seconds_per_codeword(d.p, W)
+            flops += float(r.codewords_total) * matrix_flops(descs[i].p, descs[i].n - descs[i].k)
     dec = [o.decompose_ms for o in opts]
     enum = [o.enum_ms for o in opts]
     statuses = [s_i for res in results for s_i, _ in res]
     total_cw = sum(cws)
     enum_s = sum(enum) / 1e3
-    achieved = ops_total / enum_s / 1e12
-    frac = ideal_s / enum_s  # the batch's op mix at the peak rates, against the launches' time
     batched_code_ms = np.concatenate(code_ms).tolist()
     gpu_first = [{"d": r.d, "codewords_total": r.codewords_total} for _, r in results[0]]
     line = {
@@ -625,7 +646,7 @@ def bench_batch(args):
                                "(rate 1/2) / 63 (rate 1/3); draws are not redrawn for rank (a rank-deficient "
                                "draw, probability below p^-(n-k), returns the RANK status); generators resident "
                                "on the GPU",
-                   "codes_per_step": 512, "identity_skip": True, "blocks_per_cu": bpc or 4,
+                   "codes_per_step": 512, "identity_skip": True, "blocks_per_cu": bpc or "as many as fit",
                    "sweep_ops": tune_note, "rank_deficient_codes": sum(1 for x in statuses if x == bz.ERR_RANK)},
         "time_to_d_ms": {"batched_per_code": {"p50": pct(batched_code_ms, 50), "p99": pct(batched_code_ms, 99),
                                               "note": "device time from the start of the batch's decomposition "
@@ -634,14 +655,7 @@ def bench_batch(args):
                                           "note": "host time of one 512-code call"}},
         "codewords_per_step": {"mean": total_cw / K, "min": min(cws), "max": max(cws)},
         "kernel_ms_per_step": {"decompose": sum(dec) / K, "enum": sum(enum) / K},
-        "roofline": {"kernel": "enum_batch_kernel", "bound": "alu", "achieved": achieved, "peak": achieved / frac,
-                     "unit": "T int32 VALU lane-ops/s (algorithmic)", "frac": frac,
-                     "traffic": traffic_for("enum_batch_kernel", "mixed_512"),
-                     "ops_per_codeword": "3W+1 (F_3: 2W bitwise, W+1 popcount and min), 4W+1 (F_7: 3W bitwise, "
-                                         "W+1 popcount and min), W = words over the n-k non-pivot columns",
-                     "peak_note": f"the batch's op mix at bitwise {FULL_RATE_TOPS:.1f} T/s, popcount and min "
-                                  f"{HALF_RATE_TOPS:.1f} T/s; {MATRIX_NOTE}",
-                     "avg_launch_ms": sum(enum) / K},
+        "roofline": matrix_roofline("enum_batch_kernel", flops, enum_s, "mixed_512", K),
     }
     if not args.no_plain:
         # the plain path on the same codes: one call per code, device pointers
