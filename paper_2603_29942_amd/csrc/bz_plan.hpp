@@ -234,13 +234,16 @@ inline bool tables_by_default(int p, int n, int k, int W, bool hist, bool no_ter
                               const u64 *binom) {
     if (p == 3 && (hist || k < 14)) return false;
     // the schedule has a round 4 at all
-    if (expected_rounds(p, n, k, true, max_codewords, binom) <= SUBSET_G) return false;
     const int sets = expected_sets(n, k);
+    u64 cum = 0;
+    for (int g = 1; g <= SUBSET_G; g++) cum = sat_add(cum, sat_mul(round_codewords(p, k, g, binom), (u64)sets));
+    if (k <= SUBSET_G || sat_add(cum, round_codewords(p, k, SUBSET_G + 1, binom)) > max_codewords) return false;
     if (no_term) return k > (p == 3 ? 14 : 9) || (k == (p == 3 ? 14 : 9) && sets >= 3);
+    if (p == 3 && W <= 2) return true;
+    if (p == 7 && k <= 8) return sets <= 4 && (k == 8 || !hist);
+    if (p == 7 && ((k >= 10 && sets <= 2) || (k >= 13 && sets == 3))) return true;
     const u64 work = expected_work(p, n, k, by_round, max_codewords, binom);
-    if (p == 3) return W <= 2 || work >= 10000000;
-    if (k <= 8) return sets <= 4 && (k == 8 || !hist);
-    return (k >= 10 && sets <= 2) || (k >= 13 && sets == 3) || work >= (W <= 2 ? 40000000u : 18000000u);
+    return work >= (p == 3 ? 10000000u : W <= 2 ? 40000000u : 18000000u);
 }
 // Triple tables pay when the rounds up to `last` save more tiles than the
 // tables take to build (a unit costs about 200 VALU instructions, a tile of 64
