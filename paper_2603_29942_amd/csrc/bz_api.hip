@@ -220,18 +220,23 @@ __global__ void zero_u64(u64 *p, size_t n) {
 }
 
 // ---- kernel dispatch over (P, words)
+// only the tables (and what goes with them) take more than one wavefront
+template <int P, int WF>
+void launch_decompose_wf(int nb, const uint8_t *G, CodeState *cs, u32 *rows, const RunArgs &a, hipStream_t s) {
+    if (a.pairs) decompose_kernel<P, WF, true><<<nb, DECOMP_THREADS, 0, s>>>(G, cs, rows, a);
+    else decompose_kernel<P, WF, false><<<nb, 64, 0, s>>>(G, cs, rows, a);
+}
 template <int P>
 hipError_t launch_decompose(int WF, const uint8_t *G, CodeState *cs, u32 *rows, RunArgs a,
                             hipStream_t s) {
     // workgroup 1 computes the second information set ahead; one more builds
     // the first set's pair table (see ROLE_TABLE0)
     const int nb = 1 + (a.spec ? 1 : 0) + (a.pairs && a.pair_t0 ? 1 : 0);
-    const int nt = a.pairs ? DECOMP_THREADS : 64;  // only the tables (and what goes with them) take more than one wavefront
     switch (WF) {
-    case 1: decompose_kernel<P, 1><<<nb, nt, 0, s>>>(G, cs, rows, a); break;
-    case 2: decompose_kernel<P, 2><<<nb, nt, 0, s>>>(G, cs, rows, a); break;
-    case 3: decompose_kernel<P, 3><<<nb, nt, 0, s>>>(G, cs, rows, a); break;
-    default: decompose_kernel<P, 4><<<nb, nt, 0, s>>>(G, cs, rows, a); break;
+    case 1: launch_decompose_wf<P, 1>(nb, G, cs, rows, a, s); break;
+    case 2: launch_decompose_wf<P, 2>(nb, G, cs, rows, a, s); break;
+    case 3: launch_decompose_wf<P, 3>(nb, G, cs, rows, a, s); break;
+    default: launch_decompose_wf<P, 4>(nb, G, cs, rows, a, s); break;
     }
     return hipGetLastError();
 }

@@ -258,7 +258,7 @@ template <int P, int W, int SCH>
 __device__ __forceinline__ void build_units(u32 *__restrict__ tab, int k, const uint4 *prow) {
     constexpr int UP = P - 1;
     const int nu = k * (k - 1) / 2 * UP;
-    for (int u = (int)threadIdx.x; u < nu; u += (int)blockDim.x) {
+    for (int u = (int)threadIdx.x - 64; u < nu; u += (int)blockDim.x - 64) {  // (by the helpers)
         const int r = u / UP, c = u - r * UP + 1, i = tri_root(r);
         const int s = k - 1 - i, L = k - 1 - (r - i * (i - 1) / 2);
         u32 y[3][W];
@@ -279,8 +279,7 @@ __device__ __forceinline__ void build_units(u32 *__restrict__ tab, int k, const 
     }
 }
 
-// build_units for the words per plane and the layout of this code, by every
-// thread of the workgroup
+// build_units for the words per plane and the layout of this code
 template <int P>
 __device__ __forceinline__ void build_pair_table(uint4 *ptab, int k, int W, int sch, const uint4 *prow) {
     u32 *tab = reinterpret_cast<u32 *>(ptab);
@@ -378,15 +377,15 @@ __global__ __launch_bounds__(256) void triple_batch_kernel(const CodeState *css,
 }
 
 // The first wavefront of a decomposition workgroup eliminates; the others
-// only help to build the pair tables.  It calls share_table for each table
-// (its rows are in lds.prow) and ends with release_helpers, which lets the
-// waiting wavefronts go; both sides pass the same barriers.
-template <int P>
-__device__ __forceinline__ void share_table(DecompLDS &lds, uint4 *ptab, int k, int W, int sch) {
+// build the pair tables.  It calls share_table for each table (its rows are in
+// lds.prow) and ends with release_helpers, which lets the waiting wavefronts go;
+// both sides pass the same barriers.  (It does not build itself: the code of
+// every layout would be there once more for each call, and F_7 calls took 1.2 us
+// longer for fetching it.)
+__device__ __forceinline__ void share_table(DecompLDS &lds, uint4 *ptab) {
     if (threadIdx.x == 0) lds.table = ptab;
     __syncthreads();
-    build_pair_table<P>(ptab, k, W, sch, lds.prow);
-    __syncthreads();
+    __syncthreads();  // built
 }
 __device__ __forceinline__ void release_helpers(DecompLDS &lds) {
     if (threadIdx.x == 0) lds.table = nullptr;
@@ -480,7 +479,9 @@ struct RoundPrefetch {
 // as used, packed into args.spec, then (with tables) its pair table in slot
 // pair_sets(n, k), and nothing else.  ROLE_TABLE0: the first set's
 // elimination and its pair table in slot 0, and nothing else.
-template <int P, int WF>
+// TAB: false where the caller never has tables (calls without them, most of them
+// small: their code is 1 us shorter without the tables' and the triples').
+template <int P, int WF, bool TAB>
 __device__ __forceinline__ void decompose_code(const uint8_t *__restrict__ G, CodeState *cs, u32 *__restrict__ rows,
                                const RunArgs args, DecompLDS &lds, int role = ROLE_MAIN,
                                RoundPrefetch pre = RoundPrefetch()) {
@@ -489,17 +490,16 @@ __device__ __forceinline__ void decompose_code(const uint8_t *__restrict__ G, Co
     u64 *binom = lds.binom;
     int32_t *sranks = lds.sranks;
     const int lane = threadIdx.x;
-    // the arguments arrive in vector registers (a call, not inlined): pin them
-    // to scalars so that everything derived from them is wave-uniform
+    // a batch's arguments come from memory: pinned to scalars, everything derived
+    // from them is wave-uniform
     const int n = uni(args.n), k = uni(args.k), flags = uni(args.flags);
     CodeResult &res = cs->res;
     const bool tracing = main_wg && (flags & FLAG_TRACE) != 0;
     const u64 t_start = tracing ? (u64)wall_clock64() : 0;
     SpecBuf *spec = args.spec;
-    uint4 *const pairs = args.pairs;
-    const int pair_w = uni((int)args.pair_w), pair_sch = uni((int)args.pair_scheme);
+    uint4 *const pairs = TAB ? args.pairs : nullptr;
     const uint32_t pair_stride = uni(args.pair_stride);
-    const bool t0_elsewhere = uni(args.pair_t0) != 0, triples = uni(args.triples) != 0;
+    const bool t0_elsewhere = TAB && uni(args.pair_t0) != 0, triples = TAB && uni(args.triples) != 0;
     const bool have_rt = pre.have;
     const u64 rt_tasks = pre.tasks;
     const uint32_t rt_vcap = pre.vcap;
@@ -764,12 +764,12 @@ __device__ __forceinline__ void decompose_code(const uint8_t *__restrict__ G, Co
             }
         }
         if (role == ROLE_TABLE0) {
-            if (pairs != nullptr) share_table<P>(lds, pairs, k, pair_w, pair_sch);
+            if (pairs != nullptr) share_table(lds, pairs);
             return;
         }
         // (m < pair_sets(n, k) always holds, see pair_sets)
         if (main_wg && pairs != nullptr && m < pair_sets(n, k) && !(m == 0 && t0_elsewhere))
-            share_table<P>(lds, pairs + (size_t)m * pair_stride, k, pair_w, pair_sch);
+            share_table(lds, pairs + (size_t)m * pair_stride);
         if (ahead) {
             // publish: the rows and the set's description, then the flag
             if (lane == 0) {
@@ -781,7 +781,7 @@ __device__ __forceinline__ void decompose_code(const uint8_t *__restrict__ G, Co
             __threadfence();
             if (lane == 0) __hip_atomic_store(&spec->flag, args.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             if (pairs != nullptr)
-                share_table<P>(lds, pairs + (size_t)pair_sets(n, k) * pair_stride, k, pair_w, pair_sch);
+                share_table(lds, pairs + (size_t)pair_sets(n, k) * pair_stride);
             return;
         }
         if (lane == 0) sranks[m] = kj;
@@ -967,7 +967,7 @@ __device__ __forceinline__ void decompose_code(const uint8_t *__restrict__ G, Co
         cs->trace[1][1] = 0;
     }
     for (int j = lane; j < m; j += 64) res.ranks[j] = sranks[j];
-    const bool any_triples = __any((vcaps & TRIPLES) != 0);
+    const bool any_triples = TAB && __any((vcaps & TRIPLES) != 0);
     if (lane == 0) {
         res.status = status;
         res.m = m;
@@ -983,21 +983,24 @@ __device__ __forceinline__ void decompose_code(const uint8_t *__restrict__ G, Co
     if (lane < (int)POOL_SLICES) cs->pool_next[lane][0] = 0;
 }
 
-template <int P, int WF>
-__global__ __launch_bounds__(DECOMP_THREADS) void decompose_kernel(const uint8_t *__restrict__ G, CodeState *cs,
-                                                                   u32 *__restrict__ rows, RunArgs args) {
+template <int P, int WF, bool TAB>
+__global__ __launch_bounds__(TAB ? DECOMP_THREADS : 64) void decompose_kernel(const uint8_t *__restrict__ G,
+                                                                              CodeState *cs, u32 *__restrict__ rows,
+                                                                              RunArgs args) {
     __shared__ DecompLDS lds;
-    if (threadIdx.x >= 64) {
-        if (blockIdx.x == 0 && args.reports != nullptr) {
-            ReportState &rep = *args.reports;
-            constexpr int N = (int)REPORT_COPIES * BZ_MAX_STAGES;
-            for (int i = (int)threadIdx.x - 64; i < N; i += DECOMP_THREADS - 64) {
-                (&rep.word[0][0])[i] = 0;
-                (&rep.min[0][0])[i] = (int)BIG;
+    if constexpr (TAB) {
+        if (threadIdx.x >= 64) {
+            if (blockIdx.x == 0 && args.reports != nullptr) {
+                ReportState &rep = *args.reports;
+                constexpr int N = (int)REPORT_COPIES * BZ_MAX_STAGES;
+                for (int i = (int)threadIdx.x - 64; i < N; i += DECOMP_THREADS - 64) {
+                    (&rep.word[0][0])[i] = 0;
+                    (&rep.min[0][0])[i] = (int)BIG;
+                }
             }
+            help_tables<P>(lds, args.k, args.pair_w, args.pair_scheme);
+            return;
         }
-        help_tables<P>(lds, args.k, args.pair_w, args.pair_scheme);
-        return;
     }
     RoundPrefetch pre;
     if (args.rounds != nullptr && blockIdx.x == 0) {
@@ -1009,9 +1012,9 @@ __global__ __launch_bounds__(DECOMP_THREADS) void decompose_kernel(const uint8_t
     }
     // workgroup 1: the second information set ahead (with args.spec), else
     // the first set's pair table; workgroup 2: the first set's pair table
-    const int role = blockIdx.x == 0 ? ROLE_MAIN : (blockIdx.x == 1 && args.spec != nullptr) ? ROLE_AHEAD : ROLE_TABLE0;
-    decompose_code<P, WF>(G, cs, rows, args, lds, role, pre);
-    release_helpers(lds);
+    const int role = blockIdx.x == 0 ? ROLE_MAIN : !TAB || (blockIdx.x == 1 && args.spec != nullptr) ? ROLE_AHEAD : ROLE_TABLE0;
+    decompose_code<P, WF, TAB>(G, cs, rows, args, lds, role, pre);
+    if constexpr (TAB) release_helpers(lds);
 }
 
 // =====================================================================
@@ -1758,7 +1761,7 @@ __device__ __forceinline__ void run_subset(const u32 *__restrict__ rows, LdsRows
 // g <= SUBSET_G: one item per lane (a row, a pair of rows, a triple; colex
 // rank task * 64 + lane).  Adds the combinations the lane evaluated to lcnt.
 template <int P, int W, int HIST>
-__device__ __forceinline__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
+__device__ void run_small_task(int g, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
                                const u64 *sbin, const u64 *__restrict__ gbin, u64 task, u32 &lmin, u64 &lcnt,
                                u32 *lh, u32 woff, u32 cap) {
     const int lane = __lane_id();
@@ -1827,7 +1830,7 @@ __device__ __forceinline__ void run_small_task(int g, int k, int j, const u32 *_
 // prefixes are built here.  bound, seen (thread 0): F_7 with a table, see StageBound.
 constexpr int NO_TABLE = -1;
 template <int P, int W, int HIST, int SCH>
-__device__ __forceinline__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
+__device__ void run_base_task(const StageDesc &sd, int k, int j, const u32 *__restrict__ rows, LdsRows lrows,
                               const u32 *__restrict__ ptab, uint32_t triple_off, const u64 *sbin,
                               const u64 *__restrict__ gbin, const QEntry *qtab, int nq, u64 task, StageBound bound, int seen, int nsym, u32 &lmin, u64 &lcnt, u32 *lh,
                               u32 woff, u32 cap) {
@@ -2383,17 +2386,17 @@ __global__ __launch_bounds__(DECOMP_THREADS) void decompose_batch_kernel(const u
     u32 *r = rows + bc.row_offset;
     if (bc.p == 3) {
         switch (bc.WF) {
-        case 1: decompose_code<3, 1>(g, cs, r, a, lds); break;
-        case 2: decompose_code<3, 2>(g, cs, r, a, lds); break;
-        case 3: decompose_code<3, 3>(g, cs, r, a, lds); break;
-        default: decompose_code<3, 4>(g, cs, r, a, lds); break;
+        case 1: decompose_code<3, 1, true>(g, cs, r, a, lds); break;
+        case 2: decompose_code<3, 2, true>(g, cs, r, a, lds); break;
+        case 3: decompose_code<3, 3, true>(g, cs, r, a, lds); break;
+        default: decompose_code<3, 4, true>(g, cs, r, a, lds); break;
         }
     } else {
         switch (bc.WF) {
-        case 1: decompose_code<7, 1>(g, cs, r, a, lds); break;
-        case 2: decompose_code<7, 2>(g, cs, r, a, lds); break;
-        case 3: decompose_code<7, 3>(g, cs, r, a, lds); break;
-        default: decompose_code<7, 4>(g, cs, r, a, lds); break;
+        case 1: decompose_code<7, 1, true>(g, cs, r, a, lds); break;
+        case 2: decompose_code<7, 2, true>(g, cs, r, a, lds); break;
+        case 3: decompose_code<7, 3, true>(g, cs, r, a, lds); break;
+        default: decompose_code<7, 4, true>(g, cs, r, a, lds); break;
         }
     }
     release_helpers(lds);
