@@ -223,7 +223,7 @@ __global__ void zero_u64(u64 *p, size_t n) {
 // only the tables (and what goes with them) take more than one wavefront
 template <int P, int WF>
 void launch_decompose_wf(int nb, const uint8_t *G, CodeState *cs, u32 *rows, const RunArgs &a, hipStream_t s) {
-    if (a.pairs) decompose_kernel<P, WF, true><<<nb, DECOMP_THREADS, 0, s>>>(G, cs, rows, a);
+    if (a.pairs) decompose_kernel<P, WF, true><<<nb, PLAIN_DECOMP_THREADS, 0, s>>>(G, cs, rows, a);
     else decompose_kernel<P, WF, false><<<nb, 64, 0, s>>>(G, cs, rows, a);
 }
 template <int P>

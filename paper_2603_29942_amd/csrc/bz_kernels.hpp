@@ -984,7 +984,7 @@ __device__ __forceinline__ void decompose_code(const uint8_t *__restrict__ G, Co
 }
 
 template <int P, int WF, bool TAB>
-__global__ __launch_bounds__(TAB ? DECOMP_THREADS : 64) void decompose_kernel(const uint8_t *__restrict__ G,
+__global__ __launch_bounds__(TAB ? PLAIN_DECOMP_THREADS : 64) void decompose_kernel(const uint8_t *__restrict__ G,
                                                                               CodeState *cs, u32 *__restrict__ rows,
                                                                               RunArgs args) {
     __shared__ DecompLDS lds;
@@ -993,7 +993,7 @@ __global__ __launch_bounds__(TAB ? DECOMP_THREADS : 64) void decompose_kernel(co
             if (blockIdx.x == 0 && args.reports != nullptr) {
                 ReportState &rep = *args.reports;
                 constexpr int N = (int)REPORT_COPIES * BZ_MAX_STAGES;
-                for (int i = (int)threadIdx.x - 64; i < N; i += DECOMP_THREADS - 64) {
+                for (int i = (int)threadIdx.x - 64; i < N; i += PLAIN_DECOMP_THREADS - 64) {
                     (&rep.word[0][0])[i] = 0;
                     (&rep.min[0][0])[i] = (int)BIG;
                 }

@@ -105,6 +105,10 @@ constexpr uint32_t POOL_SLICES = 32;
 // build it in about 3 us.  (Batches of 4096 small codes decompose as fast as
 // with one: LDS fits three workgroups to a compute unit either way.)
 constexpr int DECOMP_THREADS = 512;
+// (on the plain path one more, so that eight build beside the one that
+// eliminates: the 468 units of 13 rows over F_7 in one step; nine of a batch's
+// would leave a compute unit two workgroups)
+constexpr int PLAIN_DECOMP_THREADS = 576;
 
 // Results the host reads back (kept contiguous and first in CodeState).
 struct CodeResult {
