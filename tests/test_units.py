@@ -137,3 +137,19 @@ def test_histograms_of_triples(p, n, k, skip):
     got = bz.min_distance(p, G, pair_tables=1, **kw)
     assert got["info"] & bz.INFO_TRIPLES
     assert got["stages"] == ref["stages"] and np.array_equal(got["hist"], ref["hist"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,k", [(7, 6), (7, 12), (7, 23), (3, 20), (3, 64)])
+@pytest.mark.parametrize("tables", [-1, 0, 1])
+@pytest.mark.parametrize("skip", [True, False])
+def test_whole_space(p, k, tables, skip):
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2603_29942_amd import bz
+    # n = k, no column left to process: a codeword of g rows has weight g
+    G = np.eye(k, dtype=np.uint8)
+    r = bz.min_distance(p, G, no_termination=True, max_codewords=10**8, pair_tables=tables, identity_skip=skip)
+    assert r["d"] == 1
+    assert [s[3] for s in r["stages"]] == [s[0] for s in r["stages"]]
+    assert [s[4] for s in r["stages"]] == [1] * len(r["stages"])
