@@ -2150,11 +2150,9 @@ __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2
                     bm = min(bm, red_min[w]);
                     bc += red_cnt[w];
                 }
-                // BIG: no weight met here (F_7: every tile passed over, see StageBound)
-                u32 v = bm != BIG ? bm + woff : BIG;
                 if (TAB && sd.parts > REPORT_DIRECT) {
                     // to this workgroup's copy; its last report carries the sums on (see ReportState)
-                    if (v != BIG) atomicMin(&rep->min[rcopy][s], (int)v);
+                    if (bm != BIG) atomicMin(&rep->min[rcopy][s], (int)(bm + woff));
                     const u64 rest = bc >> REPORT_COUNT_BITS << REPORT_COUNT_BITS;
                     if (rest) atomicAdd((unsigned long long *)&cs->res.stage_count[s], (unsigned long long)rest);
                     drain_vmem();  // minimum and count performed before the report counts
@@ -2165,10 +2163,12 @@ __global__ __launch_bounds__(256, SCH == NO_TABLE ? 2 : P == 3 && W <= 2 ? 3 : 2
                                  : report_groups(sd.rot, sd.parts, grid, rcopy, copies);
                     last = (uint32_t)(sum >> 48) == add;
                     bc = sum & ((1ull << 48) - 1);
-                    if (last) v = (u32)rd_atomic(&rep->min[rcopy][s]);
+                    if (last) bm = (u32)rd_atomic(&rep->min[rcopy][s]) - woff;
                 }
                 if (last) {
-                    if (v != BIG) atomicMin(&cs->res.stage_min[s], (int)v);
+                    // unsigned: where no weight was met (F_7: every tile passed over, see StageBound)
+                    // bm + woff is BIG from a copy and above it from here, and lowers no minimum
+                    if (bm + woff != BIG) atomicMin((u32 *)&cs->res.stage_min[s], bm + woff);
                     atomicAdd((unsigned long long *)&cs->res.stage_count[s], (unsigned long long)bc);
                     drain_vmem();  // minimum and count performed before done counts them
                     done = __hip_atomic_fetch_add(&cs->stage_done[s], add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
